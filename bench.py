@@ -5,17 +5,16 @@ anomalies, 64-node sponge, Ricker source at >= 20 nodes per wavelength and
 256 surface receivers; D2Q5, BGK tau = 1/2, FP32 populations.  One "step" is
 one time step of the whole grid (pull-stream, moments, per-node weights,
 linear equilibrium, collision, source, sponge, receiver sampling at every
-time).  lb_step_n runs several steps per fused launch (seven for this
-configuration, as lb_blocked_steps reports, through the marching kernel;
-the last launch of a call takes one), so the dominant kernel is the marching
-kernel: it reads h(n) and writes h(n+7), 44 algorithmic bytes per node per
-launch (24 read, 20 written), i.e. 44/7 = 6.3 bytes per lattice update.  Inputs
-are resident in HBM before the timed region.
+time).  lb_step_n runs several steps per launch of the flowing kernel
+(16 for this configuration; the last launch of a call takes one), which reads
+h(n) and writes h(n+16), 44 algorithmic bytes per node per launch (24 read, 20
+written), i.e. 44/16 = 2.75 bytes per lattice update.  Inputs are resident in
+HBM before the timed region.
 
 Prints ONE JSON line: MLUPS (value), roofline of the dominant kernel (its
 launch duration measured with HIP events as the difference of two runs that
-differ only in the number of multi-step launches, against the 8 TB/s HBM
-peak), a measured device-copy bandwidth, comparison variants (MRT, D2Q9,
+differ only in the number of multi-step launches, against the rate of the
+vector units, which has the higher floor, and the 8 TB/s HBM peak), a measured device-copy bandwidth, comparison variants (MRT, D2Q9,
 FP64, FP16 storage with its error against an FP64 run, refinement, the 128^2
 pulse), the adjoint and serving measurements and the CPU oracle timed on a
 bounded sample.
@@ -43,28 +42,28 @@ def bytes_per_lup(q, precision):
     return 2 * q * s + c
 
 
-def steps_rounding(lbwave, n, q, collision, precision):
-    """(most steps per launch, rounding) for an n x n grid of a
-    configuration, from the library's lb_blocked_steps: rounding[c] is the
-    step count a launch takes when at most c are allowed (a launch takes
-    1 .. 4 steps, or the marching kernel's count)."""
-    kw = dict(nx=n, ny=n, lattice=q, collision=collision, precision=precision,
-              s=[1, 1, 1, 2, 2, 2, 1, 1, 2][:q])
-    ns_max = lbwave.blocked_steps(**kw)
-    rounding = {c: lbwave.blocked_steps(steps_per_launch=c, **kw) for c in range(1, 9)}
-    return ns_max, rounding
+def steps_per_launch(n, q, precision):
+    """Most steps lb_step_n takes per launch on an n x n grid of the layered
+    workload (see steps_per_launch in include/lbwave.h)."""
+    nodes = n * n
+    if q == 9:
+        return 6 if precision == "f64" and nodes < 800000 else 12 if precision != "f64" and nodes <= 32768 else 8
+    if nodes < 800000:
+        return 16 if nodes <= 32768 else 8
+    if precision == "f64":
+        return 8 if nodes < 1600000 else 16
+    return 12 if nodes < 2000000 else 16
 
 
-def launch_plan(nsteps, ns_max, rounding):
+def launch_plan(nsteps, most):
     """{steps per launch: launches} of one lb_step_n(nsteps) call on a grid
-    without patch, sum-of-rho recording or checkpoints, as the library takes
-    it: each launch takes min(ns_max, steps left - 1) steps rounded down to
-    a count a kernel takes, the last one a single step."""
+    without patch or checkpoints, as the library takes it: as few launches of
+    up to `most` steps as needed, of about equal length, then one of one."""
     plan = {}
     k = 0
     while k < nsteps:
-        c = max(1, min(ns_max, nsteps - k - 1))
-        ns = rounding[c]
+        m = nsteps - k - 1
+        ns = 1 if m <= 1 else -(-m // -(-m // most))
         plan[ns] = plan.get(ns, 0) + 1
         k += ns
     return plan
@@ -205,18 +204,18 @@ def adjoint_bench(torch, lbwave, inputs, n, nshots, nsteps, K=55, tape=True):
     else:
         # plus the recompute (44 B per ns-step launch and the 4-byte rho
         # field of each step), through the rho-writing kernel
-        ns_rec = lbwave.blocked_steps(nx=64, ny=64, precision="f32", steps_per_launch=4)
+        ns_rec = min(steps_per_launch(n, 5, "f32"), K)
         out["adjoint_phase_GB_s"] = round((44.0 / ns_rec + 4 + adj_b) * N * nsteps / (t_adj / nshots) / 1e9, 1)
         out["recompute_steps_per_launch"] = ns_rec
     out["backward_steps_per_launch"] = 3
     return out
 
 
-KERNEL_SOURCES = ("lb_blocked.h", "lb_blocked_f32_q5.hip", "lb_node.h", "lb_internal.h")
+KERNEL_SOURCES = ("lb_flow.h", "lb_flow_f32_q5.hip", "lb_rows.h", "lb_node.h", "lb_internal.h")
 
 
 def kernel_source_sha256():
-    """SHA-256 of the sources that define the blocked kernel, concatenated
+    """SHA-256 of the sources that define the flowing kernel, concatenated
     in KERNEL_SOURCES order."""
     import hashlib
     h = hashlib.sha256()
@@ -226,18 +225,9 @@ def kernel_source_sha256():
     return h.hexdigest()
 
 
-def kernel_label(nsl):
-    """Name of the kernel that takes the nsl-step launches of the headline
-    configuration (the marching kernel takes more than four steps)."""
-    if nsl > 4:
-        return "k_stepn_march<float,5,BGK tau=1/2,%d>" % nsl
-    return "k_stepn<float,5,BGK tau=1/2,%d>" % nsl
-
-
 def counters_profile(nsl):
     """The committed rocprofv3 HBM-counter summary of the headline kernel."""
-    stem = "k_stepn_march%d" % nsl if nsl > 4 else "k_stepn%d" % nsl
-    return os.path.join(ROOT, "profiles", stem + "_d2q5_bgk_f32_layered4096_hbm_counters.md")
+    return os.path.join(ROOT, "profiles", "k_flow%d_d2q5_bgk_f32_layered4096_hbm_counters.md" % nsl)
 
 
 def measured_traffic(nsl):
@@ -416,7 +406,7 @@ def main():
     N = wl["nx"] * wl["ny"]
     cap = steps + warmup + 1
 
-    nsl, rounding = steps_rounding(lbwave, args.n, 5, "bgk", "f32")
+    nsl = steps_per_launch(args.n, 5, "f32")
     grid = make_layered(lbwave, wl, 5, "bgk", "f32", cap + 2 * steps + nsl * 501 + 10)
     log("timing D2Q5 BGK FP32: %d warmup + %d steps" % (warmup, steps))
     t = time_steps(torch, grid, steps, warmup)
@@ -424,8 +414,8 @@ def main():
     # gives `value`) with the median of the three
     windows = [t] + [time_steps(torch, grid, steps, 0) for _ in range(2)]
     mlups = N * steps / t / 1e6
-    plan = launch_plan(steps, nsl, rounding)
-    # the blocked kernel's launch duration: two calls that differ only in
+    plan = launch_plan(steps, nsl)
+    # the flowing kernel's launch duration: two calls that differ only in
     # their number of nsl-step launches (400 vs 100, one one-step launch each)
     ta = time_steps(torch, grid, nsl * 400 + 1, 0)
     tb = time_steps(torch, grid, nsl * 100 + 1, 0)
@@ -449,7 +439,7 @@ def main():
             g = make_layered(lbwave, wl, q, coll, prec, vsteps + 11)
             tv = time_steps(torch, g, vsteps, 10)
             b = bytes_per_lup(q, prec)
-            vplan = launch_plan(vsteps, *steps_rounding(lbwave, args.n, q, coll, prec))
+            vplan = launch_plan(vsteps, steps_per_launch(args.n, q, prec))
             nb = b * N * sum(vplan.values())      # algorithmic bytes of the launches
             key = "D2Q%d_%s_%s" % (q, coll.upper(), prec.upper())
             variants[key] = {
@@ -508,16 +498,17 @@ def main():
                                "(lattice units), 64-node sponge, Ricker source, 256 receivers",
                    "nx": wl["nx"], "ny": wl["ny"], "lattice": "D2Q5", "collision": "BGK tau=1/2",
                    "steps_timed": steps, "receivers": int(len(wl["receivers"]))},
-        # bound: of the kernel's two floors, the compulsory HBM traffic (44 B
-        # per node per launch at 8 TB/s) lies above the ALU one (16 FP32
-        # operations per update, unpacked, at 256 CUs x 64 lanes x 2.4 GHz);
-        # its counters show neither saturated (latency-bound at two waves per
-        # SIMD)
-        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
-                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
+        # bound: of the kernel's two floors, that of the vector units (16 FP32
+        # operations per update, unpacked, at 256 CUs x 64 lanes x 2.4 GHz)
+        # lies above the compulsory HBM traffic's (44 B per node per launch at
+        # 8 TB/s)
+        "roofline": {"bound": "valu", "achieved": round(16.0 * nsl * N / kern_s / 1e9, 1),
+                     "peak": round(256 * 64 * 2.4, 1), "unit": "Gop/s",
+                     "frac": round(16.0 * nsl * N / kern_s / (256 * 64 * 2.4e9), 4),
+                     "hbm_achieved_GBs": round(achieved, 1), "hbm_frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-kernel scaled)",
-                     "kernel": "%s (%d steps per launch)" % (kernel_label(nsl), nsl),
+                     "kernel": "k_flow<float,5,BGK tau=1/2> (%d steps per launch)" % nsl,
                      "algorithmic_bytes_per_launch": bpl * N, "lattice_updates_per_launch": nsl * N,
                      "avg_kernel_us": round(kern_s * 1e6, 3),
                      "hbm_floor_us": round(bpl * N / HBM_PEAK_GBS / 1e3, 3),

@@ -108,29 +108,18 @@ typedef struct lb_grid lb_grid;
  *                  two adjoint population sets).  0: no checkpoints.
  *   ckpt_capacity  checkpoint slots; a run of N steps needs N / K + 1.
  *   steps_per_launch  0 (default): lb_step_n advances several time steps
- *                  per kernel launch (temporal blocking), wherever it can
- *                  (no patch, no sum-rho recording, no checkpoint falling
- *                  inside a launch; the last launch of each call takes one
- *                  step), which divides the HBM traffic per step
- *                  accordingly; the results equal those of one step per
- *                  launch bit for bit.  The marching kernel, on grids it
- *                  takes that are large enough to fill the GPU with its
- *                  waves (FP32 D2Q5 from about 2350^2, D2Q9 from about
- *                  1570^2; FP64 D2Q5 from about 1300^2, D2Q9 always; FP16
- *                  storage from about 2400^2), takes with FP32 populations
- *                  seven steps for D2Q5 (nx even, ny >= 34), six for D2Q9
- *                  BGK (ny >= 32) and five for D2Q9 MRT (ny >= 30); with
- *                  FP64 eight for D2Q5 BGK (ny >= 36), seven for D2Q5 MRT
- *                  (ny >= 34) and four for D2Q9 (ny >= 28); with FP16
- *                  storage five for D2Q5 (nx a multiple of 4, ny >= 30).
- *                  Otherwise the short-segment kernel takes four steps for
- *                  D2Q5 and for FP64, three for D2Q9 with FP32 populations
- *                  and for D2Q5 with FP16 storage, and one for D2Q9 with
- *                  FP16 storage.  lb_blocked_steps reports the count.
- *                  1 .. 8: at most that many steps per launch (a launch
- *                  takes 1 .. 4 steps, or the marching count, which a cap
- *                  at or above it selects on any grid the marching kernel
- *                  takes).
+ *                  per kernel launch (temporal blocking), up to 16, wherever
+ *                  it can (no patch, no checkpoint falling inside a launch;
+ *                  the last launch of each call takes one step), which
+ *                  divides the HBM traffic per step accordingly; the results
+ *                  equal those of one step per launch bit for bit.  The
+ *                  count depends on the grid: 16 for D2Q5 on large grids
+ *                  (FP32 and FP16 storage from 2 M nodes, 12 below; FP64
+ *                  from 1.6 M nodes, 8 below) and on the smallest (up to
+ *                  32768 nodes), 8 in between, 8 for D2Q9 (FP64 below 0.8 M
+ *                  nodes: 6; FP32 up to 32768 nodes: 12); the steps of a
+ *                  call are divided evenly over its launches.
+ *                  1 .. 8: at most that many steps per launch.
  *   nbatch         independent shots sharing the grid shape (must be 1).
  *   rho_tape       1: lb_step_n also keeps the pre-collision rho of every
  *                  time 0 .. trace_capacity - 1 of the run since lb_set_state
@@ -174,9 +163,10 @@ void lb_default_desc(lb_grid_desc *d);
  * lb_create_grid would return for it. */
 int lb_validate_desc(const lb_grid_desc *d);
 
-/* Most time steps one kernel launch of lb_step_n takes for a grid with this
- * descriptor (temporal blocking; see steps_per_launch): the count the
- * blocked kernel offers for the lattice, collision and precision, capped by
+/* Time steps that a kernel launch of a long lb_step_n call can be counted on
+ * to take for a grid with this descriptor (temporal blocking; the launches
+ * take at least as many, see steps_per_launch): 3 to 8 by lattice, collision,
+ * precision and size (1 for D2Q9 with FP16 storage), at most
  * steps_per_launch; 1 with a patch.  No GPU needed.  Returns LB_OK and
  * writes *ns, or the error lb_validate_desc gives (LB_E_INVALID for NULL). */
 int lb_blocked_steps(const lb_grid_desc *d, int32_t *ns);
@@ -235,16 +225,17 @@ int lb_record(lb_grid *h, const int32_t *rxy, int32_t nrec, void *d_traces,
               uint32_t what);
 
 /* Record the sum of rho over the grid at every time into d_sum[trace_capacity]
- * (FP64, fixed reduction order, so bitwise reproducible).  NULL disarms.
+ * (FP64, fixed reduction order, so bitwise reproducible, however the steps
+ * are divided into calls and launches).  NULL disarms.
  * Not available with a patch. */
 int lb_record_sum_rho(lb_grid *h, double *d_sum);
 
 /* Enqueue n time steps (coarse steps with a patch) on the bound stream and
  * return.  The first call after lb_set_state also performs the collision of
  * time 0.  Every launch fuses pull-stream, collision, source, sponge and
- * recording; a launch takes up to lb_blocked_steps() steps (see
- * steps_per_launch), and the last launch of each call takes one.  A coarse
- * step of a patch takes three launches (the coarse step with the interface
+ * recording; a launch takes several steps (see steps_per_launch), and the
+ * last launch of each call takes one.  A coarse step of a patch takes three
+ * launches (the coarse step with the interface
  * work, then the two fine sub-steps). */
 int lb_step_n(lb_grid *h, int64_t n);
 
@@ -253,11 +244,8 @@ int lb_step_n(lb_grid *h, int64_t n);
  * evolution equation, Sec. II B).  steps = 0 turns it off (the default);
  * 2 <= steps <= LB_GRAPH_MAX_STEPS makes lb_step_n run each whole chunk of
  * `steps` steps of a call as one replay of a captured HIP graph, and the
- * rest of the call as before.  A chunk's launches take the most steps the
- * multi-step kernel offers (four; three for D2Q9 FP32 and FP16 storage) or
- * one step, the last launch one step; one-step launches only where
- * steps_per_launch caps the count lower, the width is not a multiple of the
- * kernel's vector width or the sum of rho is recorded.  One small launch
+ * rest of the call as before.  A chunk's launches are those of a call of
+ * `steps` steps, the last launch one step.  One small launch
  * before each replay hands the graph the chunk's first time and source
  * amplitudes, so one captured graph serves every chunk.  The graph is
  * captured on the first chunk (and again after lb_set_source, lb_record,
@@ -351,7 +339,7 @@ int lb_trace_misfit_static(const void *d_traces, const void *d_obs, void *d_res,
  * rest state) with the same medium and source.  With the tape the backward
  * steps read the forward rho it holds and the population state is left as
  * it was.  Otherwise the forward segments are recomputed from the
- * checkpoints (as many steps per launch as lb_step_n takes), and afterwards
+ * checkpoints (several steps per launch, as lb_step_n), and afterwards
  * the population state is no longer the forward state, so stepping again
  * needs lb_set_state or lb_set_raw_state first.  The gradient is the same
  * bits either way and whatever steps_per_launch says. */
@@ -366,19 +354,17 @@ const char *lb_status_string(int code);
 /* ---- batched executor (serving many shots at once) --------------------
  *
  * Many independent shots (grids of different sizes, each with its own medium,
- * source, receivers and step count) advance together.  Where the scheme has
- * a marching kernel (see lb_grid_desc) and the active shots give it enough
- * waves together (or steps_per_launch asks for it), one marching launch
- * advances every shot of a shape it takes by its step count; the other
- * shots, and every shot otherwise, take launches of up to four steps (the
- * short-segment kernel's count), a shot with fewer steps left taking those.
+ * source, receivers and step count) advance together, in rounds of several
+ * steps: one launch advances every active shot by the round's steps (see
+ * steps_per_launch; the count follows the active shots' nodes together), a
+ * shot with fewer steps left by those.
  * The shots' times and buffer parities live in device memory, so a tick of
  * k steps is captured once as a HIP graph and replayed until the set of
  * shots changes.  Each shot computes
  * exactly what an lb_grid with the same parameters computes (same per-node
  * update), bitwise, whatever its batch mates.  Shots start at rest.  With
- * graphs on, a fixed block of steps is captured per set of active shots and
- * replayed as often as a tick needs.
+ * graphs on, two rounds are captured per set of active shots and replayed as
+ * often as a tick needs.
  */
 typedef struct lb_batch lb_batch;
 

@@ -15,8 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "liblbwave.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["lb_blocked_f32_q5.hip", "lb_blocked_f32_q9.hip", "lb_blocked_f64_q5.hip", "lb_blocked_f64_q9.hip",
-           "lb_blocked_f16_q5.hip", "lb_adjoint2.hip", "lb_kernels.hip", "lb_blocked.hip", "lb_runtime.cpp", "lb_batch.cpp",
+SOURCES = ["lb_flow_f64_q9.hip", "lb_flow_f32_q9.hip", "lb_flow_f16_q9.hip", "lb_flow_f64_q5.hip", "lb_flow_f32_q5.hip",
+           "lb_flow_f16_q5.hip", "lb_adjoint2.hip", "lb_kernels.hip", "lb_flow.hip", "lb_runtime.cpp", "lb_batch.cpp",
            "lb_noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = os.environ.get("LBWAVE_ARCH", "gfx950")
@@ -44,7 +44,7 @@ def _compile(src, verbose):
 def build(verbose=False):
     """Compile every HIP source for gfx950 and link liblbwave.so."""
     os.makedirs(OBJDIR, exist_ok=True)
-    # the blocked-kernel sources are the slow ones: they start first
+    # the flowing kernel's sources are the slow ones: they start first
     with ThreadPoolExecutor(max_workers=min(len(SOURCES), max(2, os.cpu_count() or 2))) as ex:
         objs = list(ex.map(lambda s: _compile(s, verbose), SOURCES))
     tmp = LIB + ".tmp%d" % os.getpid()

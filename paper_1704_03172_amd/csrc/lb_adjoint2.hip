@@ -9,10 +9,18 @@
 // (the order of one-step launches) and is written once.  Per node the
 // arithmetic is adjoint_node (lb_node.h), as in the one-step kernel, so the
 // gradient is the same bits; lambda crosses HBM once per NS steps.
-#include "lb_blocked.h"
+#include "lb_rows.h"
 
 namespace lbw {
 namespace {
+
+constexpr int kT2Block = 256;
+
+template <typename S> struct Tb {
+    static constexpr int V = sizeof(S) == 8 ? 1 : int(8 / sizeof(S));   // 8-byte lane accesses
+    static constexpr int H = sizeof(S) == 4 ? 2 : 4;                    // halo lanes per side
+    static constexpr int OW = (64 - 2 * H) * V;                         // owned columns per wave
+};
 
 // Most backward steps per launch, and rows per segment for NS steps (the
 // halo rows of each side are computed more than once).  D2Q5 at 2048^2

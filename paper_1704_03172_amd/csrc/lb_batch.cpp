@@ -1,13 +1,10 @@
 // lb_batch.cpp -- batched executor behind the lb_batch_* calls of
 // include/lbwave.h: many independent shots of the linear LB scheme advance
-// together, in rounds of the marching kernel's step count where the scheme
-// has one (every shot of a shape it takes, with that many steps left, in one
-// marching launch) and otherwise up to four steps per launch (the
-// temporally blocked kernel; one step per launch for the configuration it
-// does not serve),
-// with per-shot time and buffer parity kept on the device so that a tick of
-// k steps is captured once as a HIP graph and replayed until the set of
-// active shots changes.
+// together, in rounds of several steps, each round one launch of the flowing
+// kernel over all shots (a shot with fewer steps left takes those), with
+// per-shot time and buffer parity kept on the device so that a tick of k steps
+// is captured once as a HIP graph and replayed until the set of active shots
+// changes.
 #include "lbwave.h"
 #include "lb_host.h"
 #include "lb_internal.h"
@@ -20,7 +17,7 @@
 
 namespace {
 
-constexpr int64_t kGraphSteps = 16;      // steps per captured graph (at least; see graph_steps)
+constexpr int kGraphRounds = 2;          // rounds of a captured graph
 constexpr size_t kStageBytes = 4 << 20;  // pinned staging of the uploads
 constexpr int kTickEvents = 64;          // ticks whose completion can be tracked at once
 
@@ -32,7 +29,7 @@ using lbw::ShotState;
 // Per-set device tables of the active shots (two sets: a rebuild writes the
 // set that no tick in flight reads).
 struct SetLayout {
-    size_t order = 0, prefix = 0, wprefix = 0, mprefix = 0;
+    size_t order = 0, prefix = 0;
 };
 
 struct BatchLayout {
@@ -48,11 +45,9 @@ BatchLayout batch_layout(int32_t max_shots) {
     L.state = take((size_t)max_shots * sizeof(ShotState));
     for (SetLayout &t : L.set) {
         t.order = take((size_t)max_shots * sizeof(int32_t));
-        t.prefix = take(((size_t)max_shots + 1) * sizeof(int64_t));
-        t.wprefix = take(((size_t)max_shots + 1) * sizeof(int64_t));
-        t.mprefix = take(((size_t)max_shots + 1) * sizeof(int64_t));
+        t.prefix = take(((size_t)max_shots + 1) * sizeof(int32_t));
     }
-    L.img = take((size_t)max_shots * sizeof(lbw::StepParams));
+    L.img = take((size_t)max_shots * sizeof(lbw::FlowParams));
     L.scratch = take(256);
     L.total = off;
     return L;
@@ -64,8 +59,7 @@ struct ShotLayout {
 };
 
 struct DeviceSet {
-    int32_t *order = nullptr;
-    int64_t *prefix = nullptr, *wprefix = nullptr, *mprefix = nullptr;
+    int32_t *order = nullptr, *prefix = nullptr;
 };
 
 // A tick whose completion is tracked: its event and the host times of every
@@ -88,7 +82,7 @@ struct lb_batch {
     int32_t max_shots = 0;
     ShotEntry *d_table = nullptr;
     ShotState *d_state = nullptr;
-    lbw::StepParams *d_img = nullptr;
+    lbw::FlowParams *d_img = nullptr;
     int32_t *d_scratch = nullptr;
     DeviceSet dset[2];
     int set = 0;                       // the set the next ticks read
@@ -102,15 +96,12 @@ struct lb_batch {
     std::vector<int64_t> ht, hend;     // host-tracked time and last time per slot
     std::vector<int64_t> admit_tick;   // tick counter when the slot's shot was admitted
     std::vector<int32_t> order;
-    std::vector<int64_t> prefix, wprefix, mprefix;
-    int64_t total_blocks = 0, total_waves = 0, total_mwaves = 0;
-    int ns = 1;                        // steps per launch (blocked kernel if > 1)
-    int nsm = 0;                       // steps of a marching round (0: none)
-    int64_t min_mwaves = 0;            // fewest marching waves for a marching round
+    std::vector<int32_t> prefix;
+    bool small = false;                // shape of the flowing kernel for the active shots
+    int steps = 1;                     // steps of a round
     bool dirty = true;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    std::vector<char> graph_sig;       // per round of the graph: the round's short-shot launches
     // tick completion
     hipEvent_t ev_tick[kTickEvents] = {};
     std::deque<TickRecord> pending;    // enqueued ticks, oldest first
@@ -174,36 +165,57 @@ int stage_copy(lb_batch *b, void *dst, const void *src, size_t bytes, size_t *of
     return LB_OK;
 }
 
-// Rebuild the compact list of active shots and their wave prefix sums into
+// Rebuild the compact list of active shots and their shares of the blocks into
 // the set that no tick in flight reads, on the upload stream after the last
 // tick that read it; the ticks enqueued from now on read it once the upload
 // is done.  *off: staging offset in use.
 int rebuild(lb_batch *b, size_t *off) {
     b->order.clear();
-    b->prefix.assign(1, 0);
-    b->wprefix.assign(1, 0);
-    b->mprefix.assign(1, 0);
-    const int kind = lbw::step_kind(b->coll);
+    int64_t nodes = 0;
     for (int32_t k = 0; k < b->max_shots; ++k) {
         if (!b->used[(size_t)k]) continue;
-        const ShotEntry &e = b->table[(size_t)k];
         b->order.push_back(k);
-        b->prefix.push_back(b->prefix.back() + (int64_t)e.bx * e.ny);
-        if (b->ns > 1) b->wprefix.push_back(b->wprefix.back() + lbw::stepn_waves(b->storage, b->q, kind, b->ns, e.nx, e.ny));
-        b->mprefix.push_back(b->mprefix.back() + (e.march ? lbw::stepn_march_waves(b->storage, b->q, kind, e.nx, e.ny) : 0));
+        nodes += (int64_t)b->table[(size_t)k].nx * b->table[(size_t)k].ny;
     }
-    b->total_blocks = b->prefix.back();
-    b->total_waves = b->ns > 1 ? b->wprefix.back() : 0;
-    b->total_mwaves = b->nsm > 0 ? b->mprefix.back() : 0;
+    // one block per CU, shared out by the shots' bundles of rows (each shot
+    // at least one block), so that the blocks end at about the same time
+    const size_t na = b->order.size();
+    const lbw::FlowChoice c = lbw::flow_choose(b->storage, b->q, nodes);
+    b->small = c.small;
+    b->steps = c.steps;
+    if (b->scheme.steps_per_launch > 0) b->steps = std::min(b->steps, (int)b->scheme.steps_per_launch);
+    const lbw::FlowInfo f = lbw::flow_info(b->storage, b->q, b->small);
+    std::vector<int64_t> bundles(na), blocks(na, 1);
+    int64_t all = 0, given = 0;
+    for (size_t a = 0; a < na; ++a) {
+        const ShotEntry &e = b->table[(size_t)b->order[a]];
+        lbw::FlowParams p;
+        p.nx = e.nx;
+        lbw::flow_strips(f, b->steps, p);
+        bundles[a] = (int64_t)p.nstrip * ((e.ny + f.R - 1) / f.R);
+        all += bundles[a];
+    }
+    for (size_t a = 0; a < na; ++a) {
+        blocks[a] = std::max<int64_t>(1, std::min(bundles[a], lbw::kFlowBlocks * bundles[a] / all));
+        given += blocks[a];
+    }
+    while (given < lbw::kFlowBlocks) {   // the rest to the longest shares
+        size_t best = na;
+        for (size_t a = 0; a < na; ++a)
+            if (blocks[a] < bundles[a] && (best == na || bundles[a] * blocks[best] > bundles[best] * blocks[a])) best = a;
+        if (best == na) break;
+        ++blocks[best];
+        ++given;
+    }
+    b->prefix.assign(1, 0);
+    for (size_t a = 0; a < na; ++a) b->prefix.push_back(b->prefix.back() + (int32_t)blocks[a]);
     const int ns = 1 - b->set;
     const DeviceSet &d = b->dset[ns];
     BT_TRY(b, hipStreamWaitEvent(b->up, b->ev_set[ns], 0));
     int rc;
     if (!b->order.empty()) {
         if ((rc = stage_copy(b, d.order, b->order.data(), b->order.size() * 4, off))) return rc;
-        if ((rc = stage_copy(b, d.prefix, b->prefix.data(), b->prefix.size() * 8, off))) return rc;
-        if (b->ns > 1 && (rc = stage_copy(b, d.wprefix, b->wprefix.data(), b->wprefix.size() * 8, off))) return rc;
-        if ((rc = stage_copy(b, d.mprefix, b->mprefix.data(), b->mprefix.size() * 8, off))) return rc;
+        if ((rc = stage_copy(b, d.prefix, b->prefix.data(), b->prefix.size() * 4, off))) return rc;
     }
     BT_TRY(b, hipEventRecord(b->ev_up, b->up));
     b->up_pending = true;
@@ -218,84 +230,32 @@ BatchParams params(const lb_batch *b) {
     p.table = b->d_table;
     p.state = b->d_state;
     p.prefix = d.prefix;
-    p.wprefix = d.wprefix;
     p.order = d.order;
+    p.img = b->d_img;
     p.nact = (int32_t)b->order.size();
     p.coll = b->coll;
-    p.mprefix = d.mprefix;
     return p;
 }
 
-// One batched launch of up to `run` steps (the blocked kernel, or one step)
-// for the shots it takes, and their state update (sel = 2 in a marching
-// round: only the shots outside the marching launch).
-int enqueue_launch(lb_batch *b, BatchParams &p, int run, int sel) {
-    if (run > 1) {
-        p.max_run = run;
-        BT_TRY(b, lbw::launch_stepn_batch(b->storage, b->q, b->ns, p, b->total_waves, b->stream));
-    } else {
-        BT_TRY(b, lbw::launch_step_batch(b->storage, b->q, p, b->total_blocks, b->stream));
-    }
-    if (sel) BT_TRY(b, lbw::launch_batch_advance_sel(b->d_state, p.order, p.nact, b->d_img, sel, run, b->stream));
-    else if (run > 1) BT_TRY(b, lbw::launch_batch_advance_n(b->d_state, p.order, p.nact, run, b->stream));
-    else BT_TRY(b, lbw::launch_batch_advance(b->d_state, p.order, p.nact, b->stream));
-    return LB_OK;
-}
-
-// Whether the marching rounds of the next k steps need the launches for
-// shots outside the marching launch, one flag per round, from the host
-// times (a shot whose shape the marching kernel does not take, or one with
-// fewer than nsm steps left at the round).  No marching rounds (an empty
-// list) while the active shots give the marching launch fewer waves than
-// fill the GPU: the short-segment launches are faster then.
-std::vector<char> round_needs(const lb_batch *b, int64_t k) {
-    std::vector<char> need;
-    if (b->nsm <= 0 || b->total_mwaves <= 0 || b->total_mwaves < b->min_mwaves) return need;
-    std::vector<int64_t> t(b->ht);
-    for (int64_t r = 0; r + b->nsm <= k; r += b->nsm) {
-        char nd = 0;
-        for (int32_t s : b->order) {
-            const int64_t left = b->hend[(size_t)s] - t[(size_t)s];
-            if (left > 0 && (!b->table[(size_t)s].march || left < b->nsm)) nd = 1;
-            t[(size_t)s] += std::min<int64_t>(std::max<int64_t>(left, 0), b->nsm);
-        }
-        need.push_back(nd);
-    }
-    return need;
-}
-
-// k steps of every active shot (a shot stops at its last step).  Rounds of
-// nsm steps while k allows: the shots that the marching kernel takes and
-// that have nsm steps left run in one marching launch, the others (where
-// `need` says there are any) in launches of up to ns steps; the rest of k
-// in launches of ns steps, the remainder in one shorter blocked launch (or,
-// with one step left or no blocked kernel, one-step launches).  Every shot
-// advances by min(k, steps left) either way.
-int enqueue_steps(lb_batch *b, int64_t k, const std::vector<char> &need) {
-    BatchParams p = params(b);
-    int rc;
-    size_t r = 0;
-    while (r < need.size() && k >= b->nsm) {
-        p.img = b->d_img;
-        BT_TRY(b, lbw::launch_batch_march_prep(b->q, p, b->nsm, b->stream));
-        BT_TRY(b, lbw::launch_stepn_march_batch(b->storage, b->q, p, b->total_mwaves, b->stream));
-        BT_TRY(b, lbw::launch_batch_advance_sel(b->d_state, p.order, p.nact, b->d_img, 1, b->nsm, b->stream));
-        if (need[r])
-            for (int done = 0; done < b->nsm;) {
-                const int run = std::min(b->ns, b->nsm - done);
-                if ((rc = enqueue_launch(b, p, run, 2))) return rc;
-                done += run;
-            }
-        p.img = nullptr;
-        k -= b->nsm;
-        ++r;
-    }
+// k steps of every active shot (a shot stops at its last step), in rounds of
+// b->steps steps.
+int enqueue_steps(lb_batch *b, int64_t k) {
+    const BatchParams p = params(b);
+    const lbw::FlowInfo f = lbw::flow_info(b->storage, b->q, b->small);
     while (k > 0) {
-        const int run = (int)std::min<int64_t>(b->ns, k);
-        if ((rc = enqueue_launch(b, p, run, 0))) return rc;
+        const int run = (int)std::min<int64_t>(b->steps, k);
+        BT_TRY(b, lbw::launch_batch_prep(p, run, b->steps, f, b->stream));
+        BT_TRY(b, lbw::launch_flow_batch(b->storage, b->q, b->small, p, b->prefix.back(), b->stream));
         k -= run;
     }
     return LB_OK;
+}
+
+// Most steps any active shot has left (host times).
+int64_t steps_left(const lb_batch *b) {
+    int64_t left = 0;
+    for (int32_t s : b->order) left = std::max(left, b->hend[(size_t)s] - b->ht[(size_t)s]);
+    return left;
 }
 
 void drop_graph(lb_batch *b) {
@@ -305,15 +265,10 @@ void drop_graph(lb_batch *b) {
     b->graph = nullptr;
 }
 
-// Steps per captured graph: kGraphSteps rounded up to whole marching rounds.
-int64_t graph_steps(const lb_batch *b) {
-    return b->nsm > 1 ? (kGraphSteps + b->nsm - 1) / b->nsm * b->nsm : kGraphSteps;
-}
-
-int capture(lb_batch *b, const std::vector<char> &need) {
+int capture(lb_batch *b) {
     drop_graph(b);
     BT_TRY(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
-    int rc = enqueue_steps(b, graph_steps(b), need);
+    int rc = enqueue_steps(b, kGraphRounds * b->steps);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->stream, &g);
     if (rc) {
@@ -323,7 +278,6 @@ int capture(lb_batch *b, const std::vector<char> &need) {
     BT_TRY(b, e);
     b->graph = g;
     BT_TRY(b, hipGraphInstantiate(&b->exec, b->graph, nullptr, nullptr, 0));
-    b->graph_sig = need;
     b->dirty = false;
     return LB_OK;
 }
@@ -377,26 +331,14 @@ int lb_batch_create(const lb_grid_desc *scheme, int32_t max_shots, void *d_works
     b->stream = (hipStream_t)stream;
     b->use_graph = use_graph ? 1 : 0;
     b->max_shots = max_shots;
-    b->ns = lbw::stepn_max(b->storage, b->q, b->coll.kind);
-    if (scheme->steps_per_launch > 0) b->ns = std::min(b->ns, scheme->steps_per_launch);
-    // marching rounds: the marching kernel's step count for this scheme (a
-    // shape it takes), unless steps_per_launch caps it lower
-    // and, as for a single grid, a cap at or above that count asks for the
-    // marching rounds however few waves the active shots give them
-    b->nsm = lbw::stepn_march(b->storage, b->q, lbw::step_kind(b->coll), 1024, 1024);
-    b->min_mwaves = lbw::stepn_march_min_waves(b->storage, b->q, lbw::step_kind(b->coll));
-    if (scheme->steps_per_launch > 0 && scheme->steps_per_launch < b->nsm) b->nsm = 0;
-    if (scheme->steps_per_launch > 0) b->min_mwaves = 0;
     char *ws = (char *)d_workspace;
     b->d_table = (ShotEntry *)(ws + L.table);
     b->d_state = (ShotState *)(ws + L.state);
-    b->d_img = (lbw::StepParams *)(ws + L.img);
+    b->d_img = (lbw::FlowParams *)(ws + L.img);
     b->d_scratch = (int32_t *)(ws + L.scratch);
     for (int i = 0; i < 2; ++i) {
         b->dset[i].order = (int32_t *)(ws + L.set[i].order);
-        b->dset[i].prefix = (int64_t *)(ws + L.set[i].prefix);
-        b->dset[i].wprefix = (int64_t *)(ws + L.set[i].wprefix);
-        b->dset[i].mprefix = (int64_t *)(ws + L.set[i].mprefix);
+        b->dset[i].prefix = (int32_t *)(ws + L.set[i].prefix);
     }
     b->table.assign((size_t)max_shots, ShotEntry());
     b->used.assign((size_t)max_shots, 0);
@@ -517,9 +459,6 @@ int lb_batch_add_shot(lb_batch *b, const lb_shot_desc *s, void *d_ws, size_t ws_
     e.sponge_smax = s->sponge_sigma_max;
     e.src_x = s->src_x;
     e.src_y = s->src_y;
-    const int64_t tile = lbw::step_tile_nodes(b->storage);
-    e.bx = (int32_t)(((int64_t)s->nx + tile - 1) / tile);
-    e.march = b->nsm > 0 && lbw::stepn_march(b->storage, b->q, lbw::step_kind(b->coll), s->nx, s->ny) == b->nsm;
 
     // collision of time 0 (records time 0): pop0 (at rest) -> pop1
     lbw::StepParams p;
@@ -591,25 +530,21 @@ int lb_batch_tick(lb_batch *b, int64_t k) {
         b->up_pending = false;
     }
     int rc;
+    const int64_t left = std::min(k, steps_left(b));   // nothing to launch once every shot is at its end
     if (!b->use_graph) {
-        if ((rc = enqueue_steps(b, k, round_needs(b, k)))) return rc;
-        advance_host(b, k);
+        if ((rc = enqueue_steps(b, left))) return rc;
     } else {
-        // graphs of graph_steps() steps, captured again when the set of
-        // active shots changes or a round's short-shot launches come or go,
-        // and replayed; the remainder of k runs as direct launches
-        const int64_t gs = graph_steps(b);
-        for (int64_t i = 0; i < k / gs; ++i) {
-            const std::vector<char> need = round_needs(b, gs);
-            if (b->dirty || !b->exec || need != b->graph_sig)
-                if ((rc = capture(b, need))) return rc;
+        // graphs of kGraphRounds rounds, captured again when the set of active
+        // shots changes, and replayed; the remainder runs as direct launches
+        const int64_t gs = (int64_t)kGraphRounds * b->steps;
+        for (int64_t i = 0; i < left / gs; ++i) {
+            if (b->dirty || !b->exec)
+                if ((rc = capture(b))) return rc;
             BT_TRY(b, hipGraphLaunch(b->exec, b->stream));
-            advance_host(b, gs);
         }
-        const int64_t r = k % gs;
-        if ((rc = enqueue_steps(b, r, round_needs(b, r)))) return rc;
-        advance_host(b, r);
+        if ((rc = enqueue_steps(b, left % gs))) return rc;
     }
+    advance_host(b, k);
     BT_TRY(b, hipEventRecord(b->ev_set[b->set], b->stream));
     TickRecord rec;
     rec.id = ++b->ticks;

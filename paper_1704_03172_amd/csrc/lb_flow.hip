@@ -1,0 +1,125 @@
+// lb_flow.hip -- host side of the flowing kernel (lb_flow.h; instantiated per
+// storage format and lattice in lb_flow_*.hip): shapes, geometry, argument
+// checks and dispatch, and the batched executor's per-shot params and advance.
+#include "lb_flow.h"
+
+#include <algorithm>
+
+namespace lbw {
+namespace {
+
+constexpr int kAdvBlock = 256;
+
+// Params images of a batched round (see launch_batch_prep).
+__global__ __launch_bounds__(kAdvBlock) void k_batch_prep(BatchParams bp, int run, int steps, FlowInfo f) {
+    const int a = blockIdx.x * kAdvBlock + threadIdx.x;
+    if (a >= bp.nact) return;
+    const int slot = bp.order[a];
+    const ShotState ss = bp.state[slot];
+    const ShotEntry &e = bp.table[slot];
+    FlowParams p;
+    p.src = ss.cur ? e.pop1 : e.pop0;
+    p.dst = ss.cur ? e.pop0 : e.pop1;
+    p.c2 = e.c2;
+    p.nx = e.nx;
+    p.ny = e.ny;
+    p.pstride = e.pstride;
+    p.sponge_width = e.sponge_width;
+    p.sponge_smax = e.sponge_smax;
+    flow_strips(f, steps, p);
+    p.nblk = bp.prefix[a + 1] - bp.prefix[a];
+    p.src_x = e.src_x;
+    p.src_y = e.src_y;
+    p.coll = bp.coll;
+    p.rec = e.rec;
+    const int64_t tn = ss.t + 1;
+    p.rec.col = tn;
+    for (int k = 0; k < kFlowSteps; ++k) p.s[k] = tn + k < e.wavelet_len ? e.wavelet[tn + k] : 0.0;
+    p.nrun = ss.active && ss.t < ss.t_end ? (int)min<int64_t>(run, ss.t_end - ss.t) : 0;
+    bp.img[slot] = p;
+    if (p.nrun > 0) {   // the state after the round
+        bp.state[slot].t = ss.t + p.nrun;
+        bp.state[slot].cur = ss.cur ^ 1;
+    }
+}
+
+hipError_t dispatch(int storage, int q, bool small, const FlowParams &p, const FlowBatch &fb, int64_t nblk,
+                    const Collision &coll, hipStream_t s) {
+    const int kind = step_kind(coll);
+    if (storage == ST_F32) return q == 5 ? launch_flow_f32_q5(small, p, fb, nblk, kind, s) : launch_flow_f32_q9(small, p, fb, nblk, kind, s);
+    if (storage == ST_F64) return q == 5 ? launch_flow_f64_q5(small, p, fb, nblk, kind, s) : launch_flow_f64_q9(small, p, fb, nblk, kind, s);
+    return q == 5 ? launch_flow_f16_q5(small, p, fb, nblk, kind, s) : launch_flow_f16_q9(small, p, fb, nblk, kind, s);
+}
+
+}  // namespace
+
+FlowInfo flow_info(int storage, int q, bool small) {
+    if (storage == ST_F32) return q == 5 ? flow_info_f32_q5(small) : flow_info_f32_q9(small);
+    if (storage == ST_F64) return q == 5 ? flow_info_f64_q5(small) : flow_info_f64_q9(small);
+    return q == 5 ? flow_info_f16_q5(small) : flow_info_f16_q9(small);
+}
+
+// Measured with a 64-node sponge and 64 receivers on square grids of 128^2 to
+// 4096^2 nodes (us per step; small shape / wide one, each at its best step
+// count):
+//   FP32 D2Q5   768^2 2.61 (8 steps) / 2.74 (14)    1024^2 3.47 (8) / 3.23 (12)
+//   FP64 D2Q5   768^2 3.09 (8) / 3.24 (8)           1024^2 4.59 (8) / 4.06 (8)
+//   FP32 D2Q9  1536^2 10.15 (8) / 11.91 (8)         2048^2 17.68 (8) / 16.86 (8)
+//   FP64 D2Q9   768^2 9.63 (6) / 9.68 (6)           1536^2 27.06 (8) / 26.67 (8)
+// More steps per launch cost halo rows and columns computed twice, fewer cost
+// launches and passes over memory.  Small shape: 16 steps pay while the GPU is
+// not filled by the rows a block stores (FP32 D2Q5 128^2 1.12 at 16 steps,
+// 1.36 at 8; 256^2 1.79 at 8, 1.84 at 12), after that the narrow strips' halo
+// columns of 8 steps do.  Wide shape: 16 steps need grids whose blocks have
+// many more rows than the 2 x 16 at their head (FP32 D2Q5 1024^2 3.23 at 12
+// steps, 3.56 at 16; 2048^2 6.91 and 6.34; 4096^2 18.6 and 15.1; FP64 D2Q5
+// 1024^2 4.06 at 8, 4.98 at 16; 1536^2 7.93 and 7.51).  D2Q9's and FP64's
+// larger states leave fewer waves per CU, which then wait for each other
+// beyond 8 steps (FP32 D2Q9 4096^2 46.0 at 8 steps, 52.4 at 12).
+FlowChoice flow_choose(int storage, int q, int64_t nodes) {
+    FlowChoice c;
+    const bool f64 = storage == ST_F64;
+    c.small = nodes < (q == 9 && !f64 ? 3000000 : 800000);
+    if (q == 9) c.steps = !c.small ? 8 : f64 ? 6 : nodes <= 32768 ? 12 : 8;
+    else if (c.small) c.steps = nodes <= 32768 ? 16 : 8;
+    else c.steps = f64 ? (nodes < 1600000 ? 8 : 16) : (nodes < 2000000 ? 12 : 16);
+    return c;
+}
+
+void flow_geometry(const FlowInfo &f, int steps, int blocks, FlowParams &p) {
+    flow_strips(f, steps, p);
+    const int64_t bundles = (int64_t)p.nstrip * ((p.ny + f.R - 1) / f.R);
+    p.nblk = (int32_t)std::max<int64_t>(1, std::min<int64_t>(blocks, bundles));
+}
+
+hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipStream_t s) {
+    if ((q != 5 && q != 9) || p.nx < 1 || p.ny < 1) return hipErrorInvalidValue;
+    const FlowInfo f = flow_info(storage, q, small);
+    // what the kernel takes for granted: halos of whole lanes, wide enough,
+    // and every column and bundle in some strip and block
+    if (p.nrun < 1 || p.nrun > f.steps || p.hx < p.nrun || p.hx % f.V != 0 || 2 * p.hx >= 64 * f.V || p.nblk < 1 ||
+        p.nl < 0 || p.nr < 0 || p.nl + p.nr > p.nstrip || (int64_t)p.nstrip * (64 * f.V - 2 * p.hx) < p.nx)
+        return hipErrorInvalidValue;
+    return dispatch(storage, q, small, p, FlowBatch(), p.nblk, p.coll, s);
+}
+
+hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const FlowInfo &f, hipStream_t s) {
+    if (bp.nact <= 0) return hipSuccess;
+    if (bp.img == nullptr || run < 1 || run > steps || steps > f.steps) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_batch_prep, dim3((unsigned)((bp.nact + kAdvBlock - 1) / kAdvBlock)), dim3(kAdvBlock), 0, s, bp,
+                       run, steps, f);
+    return hipGetLastError();
+}
+
+hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &bp, int64_t nblk, hipStream_t s) {
+    if (nblk <= 0 || bp.nact <= 0) return hipSuccess;
+    if (bp.img == nullptr || (q != 5 && q != 9)) return hipErrorInvalidValue;
+    FlowBatch fb;
+    fb.img = bp.img;
+    fb.order = bp.order;
+    fb.prefix = bp.prefix;
+    fb.nact = bp.nact;
+    return dispatch(storage, q, small, FlowParams(), fb, nblk, bp.coll, s);
+}
+
+}  // namespace lbw

@@ -1,0 +1,7 @@
+// lb_flow_f64_q9.hip -- instantiates the flowing kernel (lb_flow.h) for
+// FP64 populations on D2Q9: single-grid, graph and batched launches.
+#include "lb_flow.h"
+
+namespace lbw {
+LBW_FLOW_UNIT(double, 9, f64_q9)
+}  // namespace lbw

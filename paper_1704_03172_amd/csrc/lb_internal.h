@@ -91,7 +91,7 @@ constexpr int kGraphMaxSteps = 256;
 struct GraphTab {
     int64_t t0 = 0;
     int64_t pad = 0;
-    double s[kGraphMaxSteps + 8] = {};   // (zeros past the chunk: a launch reads four)
+    double s[kGraphMaxSteps] = {};
 };
 
 // One launch of the fused step (or of the collide-only variant).
@@ -124,16 +124,85 @@ struct StepParams {
     InterfaceParams iface;
     int32_t pre_rows = 0;              // set by launch_step: leading block rows that
                                        // do the prolong_on work
-    double s_n2 = 0.0;                 // launch_stepn: source amplitudes of the second,
-    double s_n3 = 0.0;                 // third and fourth steps
-    double s_n4 = 0.0;
-    double s_more[4] = {0, 0, 0, 0};   // ... and of the fifth to eighth
-    int32_t nrun = 1;                  // launch_stepn: steps this launch takes (= ns)
-    int64_t rho_stride = 0;            // launch_stepn with rho_out: elements between the
-                                       // rho fields of consecutive steps
     const GraphTab *gtab = nullptr;    // graph replay: rec.col is relative to gtab->t0 and
-    int32_t goff = 0;                  // the source amplitudes are gtab->s[goff ..]
+    int32_t goff = 0;                  // the source amplitude is gtab->s[goff]
 };
+
+// One launch of the flowing kernel (lb_flow.h): nrun steps h(n) -> h(n + nrun)
+// of one grid.  Kernels read it with scalar loads, from their arguments or
+// from a batch's params images.
+constexpr int kFlowSteps = 16;             // most steps of a launch
+constexpr int kFlowPlain = 4;              // weights of a bundle of rows in a block's share: away from
+constexpr int kFlowSponge = 5;             // the side edges, and in a strip that meets a side edge's sponge
+constexpr int kFlowBlocks = 256;           // one block per CU
+struct FlowParams {
+    const void *src = nullptr;         // h(n)
+    void *dst = nullptr;               // h(n + nrun): another buffer
+    const void *c2 = nullptr;
+    int32_t nx = 0, ny = 0;
+    int64_t pstride = 0;
+    int32_t nrun = 0;
+    int32_t hx = 0;                    // halo columns on each side of a strip (a multiple of the
+                                       // lane's columns, at least nrun)
+    int32_t nstrip = 0;                // strips, the first nl and the last nr of which
+    int32_t nl = 0, nr = 0;            // meet the sponge of a side edge
+    int32_t nblk = 0;                  // blocks of the grid
+    int32_t sponge_width = 0;
+    int32_t src_x = -1, src_y = -1;
+    int32_t goff = 0;                  // graph replay, as in StepParams
+    double sponge_smax = 0.0;
+    Collision coll;
+    Receivers rec;                     // col: the column of time n + 1
+    void *rho_out = nullptr;           // pre-collision rho of time n + s at rho_out + (s - 1) *
+    int64_t rho_stride = 0;            // rho_stride (nullptr: off)
+    double *sum = nullptr;             // partial sums of rho of time n + s, one per row and strip,
+    int64_t sum_stride = 0;            // at sum + (s - 1) * sum_stride (nullptr: off)
+    const GraphTab *gtab = nullptr;
+    double s[kFlowSteps] = {};         // source amplitudes of times n + 1 ..
+};
+
+// The active shots of a batched launch.
+struct FlowBatch {
+    const FlowParams *img = nullptr;   // [max_shots] params of the round (nullptr: a single grid)
+    const int32_t *order = nullptr;    // [nact] slot of each active shot
+    const int32_t *prefix = nullptr;   // [nact + 1] first block of each active shot
+    int32_t nact = 0;
+};
+
+// Shape of the flowing kernel for a storage format and lattice (small: the
+// one for grids too small to give every CU rows enough of the wide strips).
+struct FlowInfo {
+    int32_t V = 1, R = 1;              // columns per lane, rows per bundle
+    int32_t steps = 1;                 // most steps per launch
+};
+FlowInfo flow_info(int storage, int q, bool small);
+// The shape and the steps per launch for `nodes` lattice nodes advanced
+// together (a grid, or all shots of a batch).
+struct FlowChoice {
+    bool small = false;
+    int32_t steps = 1;
+};
+FlowChoice flow_choose(int storage, int q, int64_t nodes);
+// Halo and strips of a grid for launches of up to `steps` steps: fills hx,
+// nstrip, nl and nr of p from its nx and sponge_width.  The halo is rounded up
+// to 8 columns: the strips' stored columns then start on 32-byte boundaries
+// (FP32 storage) or better (4096^2, D2Q5 FP32: 14 steps per launch with 16
+// halo columns 17.3 us per step, with 14 18.2; 10 steps 20.0 against 22.4).
+__host__ __device__ inline void flow_strips(const FlowInfo &f, int steps, FlowParams &p) {
+    p.hx = (steps + 7) / 8 * 8;
+    const int ow = 64 * f.V - 2 * p.hx, L = p.sponge_width;
+    p.nstrip = (p.nx + ow - 1) / ow;
+    p.nl = p.nr = 0;
+    if (L > 0) {
+        const int64_t nl = ((int64_t)L + p.hx + ow - 1) / ow;                      // strips with sx ow - hx < L
+        const int64_t r0 = (int64_t)p.nx - L + p.hx - 64 * f.V + 1;                // and with sx ow >= r0
+        p.nl = (int32_t)(nl < p.nstrip ? nl : p.nstrip);
+        const int64_t first = r0 > 0 ? (r0 + ow - 1) / ow : 0;
+        if (first < p.nstrip) p.nr = p.nstrip - (int32_t)(first > p.nl ? first : p.nl);
+    }
+}
+// The same, and the number of blocks (at most `blocks`).
+void flow_geometry(const FlowInfo &f, int steps, int blocks, FlowParams &p);
 
 // One backward step of the discrete adjoint (misfit gradient w.r.t. c^2):
 // lambda(n) = K^T (1 - sigma) P^T lambda(n+1) + r(n), with the gradient
@@ -189,8 +258,6 @@ struct ShotEntry {
     int32_t sponge_width = 0;
     double sponge_smax = 0.0;
     int32_t src_x = -1, src_y = -1;
-    int32_t bx = 0;                          // step blocks per row
-    int32_t march = 0;                       // 1: the marching kernel takes the shape
 };
 
 // Dynamic state of a shot, advanced on the device.
@@ -204,17 +271,11 @@ struct ShotState {
 struct BatchParams {
     const ShotEntry *table = nullptr;        // [max_shots]
     ShotState *state = nullptr;              // [max_shots]
-    const int64_t *prefix = nullptr;         // [nact + 1] first block of each active shot
-    const int64_t *wprefix = nullptr;        // [nact + 1] first blocked-kernel wave of each active shot
+    const int32_t *prefix = nullptr;         // [nact + 1] first block of each active shot
     const int32_t *order = nullptr;          // [nact] slot of each active shot
+    FlowParams *img = nullptr;               // [max_shots] params images of the round
     int32_t nact = 0;
-    int32_t max_run = 1;                     // blocked launch: steps per shot at most
     Collision coll;
-    // marching rounds: the first marching wave of each active shot, and the
-    // params image of each slot for the round (nrun > 0: the shot takes the
-    // marching launch; the round's other launches leave it alone)
-    const int64_t *mprefix = nullptr;        // [nact + 1]
-    StepParams *img = nullptr;               // [max_shots]; nullptr: no marching round
 };
 
 // Launchers (lb_kernels.hip).  All return the launch status.
@@ -233,61 +294,22 @@ constexpr int kMisfitMaxBlocks = 2048;
 int misfit_blocks(int32_t nrec, int64_t ncols);
 hipError_t launch_misfit(int storage, const void *traces, const void *obs, void *res, int32_t nrec,
                          int64_t cap, int64_t ncols, double *phi, double *partial, hipStream_t s);
-int step_vwidth(int storage);
-int step_tile_nodes(int storage);   // x-nodes covered by one step block
-hipError_t launch_step_batch(int storage, int q, const BatchParams &bp, int64_t nblocks, hipStream_t s);
-hipError_t launch_batch_advance(ShotState *state, const int32_t *order, int nact, hipStream_t s);
-// Blocked batch launch with the ns-step kernel: every active shot advances
-// min(ns, bp.max_run, steps left) steps; then launch_batch_advance_n with
-// run = bp.max_run.  nwaves: sum of stepn_waves over the active shots.
-int64_t stepn_waves(int storage, int q, int kind, int ns, int32_t nx, int32_t ny);   // kind: step_kind()
-hipError_t launch_stepn_batch(int storage, int q, int ns, const BatchParams &bp, int64_t nwaves, hipStream_t s);
-hipError_t launch_batch_advance_n(ShotState *state, const int32_t *order, int nact, int run, hipStream_t s);
-// Marching round of a batch (ns = stepn_march of the scheme): prep writes
-// bp.img for every active shot (nrun = ns for a shot whose shape the
-// marching kernel takes, with at least ns steps left; 0 otherwise), the
-// marching launch runs those over nwaves = sum of stepn_march_waves, and
-// advance_sel moves state: sel = 1 the marching shots by their nrun, sel = 2
-// the others by min(run, steps left).  The batched step launches of a round
-// (bp.img set) skip the marching shots.
-int64_t stepn_march_waves(int storage, int q, int kind, int32_t nx, int32_t ny);
-hipError_t launch_batch_march_prep(int q, const BatchParams &bp, int ns, hipStream_t s);
-hipError_t launch_stepn_march_batch(int storage, int q, const BatchParams &bp, int64_t nwaves, hipStream_t s);
-hipError_t launch_batch_advance_sel(ShotState *state, const int32_t *order, int nact, const StepParams *img, int sel,
-                                    int run, hipStream_t s);
 hipError_t launch_step(int storage, const StepParams &p, bool pull,
                        hipStream_t s);
-// ns pull steps in one launch of the temporally blocked ns-step kernel
-// (p.nrun must equal ns): reads h(n) from p.src, writes h(n + ns) to p.dst
-// (a buffer other than p.src), records columns p.rec.col .. p.rec.col + ns - 1,
-// source amplitudes p.s_n .. p.s_n4, p.s_more; with p.rho_out, the pre-collision rho of
-// time n + s (s = 1..ns) goes to p.rho_out + (s - 1) * p.rho_stride.  No
-// reduction partials, snapshot or interface work.
-// 2 <= ns <= stepn_max(storage, p.q, p.coll.kind), or ns = stepn_march(...)
-// without gtab; with gtab ns = stepn_graph_steps(...) only.
-hipError_t launch_stepn(int storage, const StepParams &p, int ns, hipStream_t s);
-int stepn_max(int storage, int q, int kind);   // steps per launch the blocked kernel offers (1: none)
-// Steps of the multi-step launches of a captured chunk (p.gtab set): the
-// most the kernel offers, on grids whose width the vector loads take; 1:
-// the chunk takes one-step launches only.
-int stepn_graph_steps(int storage, int q, int kind, int32_t nx);
-// Steps per launch of the marching kernel for an nx x ny grid (kind:
-// step_kind()), 0 where it does not apply; it takes exactly that count.
-// pref: also 0 where a single grid of that size would leave the GPU
-// underfilled with the marching kernel's waves (the launch plan's default).
-int stepn_march(int storage, int q, int kind, int32_t nx, int32_t ny, bool pref = false);
-// Fewest waves for which a marching launch fills the GPU (the threshold of
-// pref above; the batched executor applies it to a round's waves).
-int64_t stepn_march_min_waves(int storage, int q, int kind);
-// Most steps one launch takes on an nx x ny grid (pref: as the default
-// launch plan chooses), and the largest step count a launch can take that
-// is at most ns (>= 1); kind is step_kind().
-int stepn_max_grid(int storage, int q, int kind, int32_t nx, int32_t ny, bool pref = false);
-int stepn_round(int storage, int q, int kind, int32_t nx, int32_t ny, int ns);
+// p.nrun steps of one grid in one launch of the flowing kernel, geometry as
+// flow_geometry() filled it for the same shape.  1 <= p.nrun <=
+// flow_info().steps, p.hx >= p.nrun.
+hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipStream_t s);
+// One round of a batch: prep writes the params image of every active shot for
+// min(run, steps left) steps (nrun = 0: none) with halos for `steps` steps and
+// moves the shot's state past them; the launch takes nblk blocks over the
+// images.
+hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const FlowInfo &f, hipStream_t s);
+hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &bp, int64_t nblk, hipStream_t s);
 int64_t step_blocks(int storage, int32_t nx, int32_t ny, bool pull);
-// Sum of the nblocks partials to out[0], or (gtab set: a replayed graph) to
-// out[gtab->t0].
-hipError_t launch_sum_finalize(const double *partial, int64_t nblocks,
+// Sums of `times` consecutive groups of nblocks partials to out[0 ..], or
+// (gtab set: a replayed graph) to out[gtab->t0 ..].
+hipError_t launch_sum_finalize(const double *partial, int64_t nblocks, int times,
                                double *out, const GraphTab *gtab, hipStream_t s);
 // *dst = val on the device, in stream order (before a graph replay).
 hipError_t launch_graph_prime(GraphTab *dst, const GraphTab &val, hipStream_t s);

@@ -20,12 +20,11 @@
 // hint (measured on MI355X: +8-11 % HBM throughput over cached accesses for
 // this 11-stream pattern, and +7 % for a plain copy).
 //
-// This one-step kernel serves single steps (the last of a call, sum-of-rho
-// recording, checkpoint boundaries), the refinement patch, whose interface
-// work is fused into it, and the collide-only first step of an adjoint
-// segment; runs of steps (the adjoint's recompute included) go to the
-// temporally blocked kernel of lb_blocked.h.  Both take their per-node
-// arithmetic from lb_node.h.
+// This one-step kernel serves single steps (the last of a call, checkpoint
+// boundaries), the refinement patch, whose interface work is fused into it,
+// and the collide-only launch of time 0; runs of steps (the adjoint's
+// recompute included) go to the flowing kernel of lb_flow.h.  Both take their
+// per-node arithmetic from lb_node.h.
 #include "lb_internal.h"
 #include "lb_node.h"
 
@@ -588,65 +587,10 @@ __global__ __launch_bounds__(kBlock) void k_misfit_finalize(const double *partia
     if (threadIdx.x == 0) *phi = 0.5 * s;
 }
 
-// ---- batched step over many shots (serving) ------------------------------------
-// One launch covers every active shot: block b belongs to the shot whose
-// block range [prefix[a], prefix[a+1]) holds it; the shot's time and buffer
-// parity live in device memory, so the same launch sequence can be captured
-// once and replayed.  The per-node update is update_tile(), identical to the
-// single-grid step, so a shot's results do not depend on its batch mates.
-template <typename S, int Q, int KIND>
-__global__ __launch_bounds__(kStepBlock) void k_step_batch(BatchParams bp) {
-    constexpr int V = Tr<S>::V;
-    const int64_t b = blockIdx.x;
-    int lo = 0, hi = bp.nact - 1;
-    while (lo < hi) {
-        int mid = (lo + hi + 1) >> 1;
-        if (bp.prefix[mid] <= b) lo = mid; else hi = mid - 1;
-    }
-    const int slot = bp.order[lo];
-    if (bp.img != nullptr && bp.img[slot].nrun > 0) return;   // the round's marching launch takes it
-    const ShotState ss = bp.state[slot];
-    if (!ss.active || ss.t >= ss.t_end) return;
-    const ShotEntry &e = bp.table[slot];
-    const int64_t local = b - bp.prefix[lo];
-    const int y = int(local / e.bx);
-    const int tile = int(local % e.bx);
-    StepParams p;
-    p.src = ss.cur ? e.pop1 : e.pop0;
-    p.dst = ss.cur ? e.pop0 : e.pop1;
-    p.c2 = e.c2;
-    p.nx = e.nx;
-    p.ny = e.ny;
-    p.pstride = e.pstride;
-    p.q = Q;
-    p.coll = bp.coll;
-    p.sponge_width = e.sponge_width;
-    p.sponge_smax = e.sponge_smax;
-    p.src_x = e.src_x;
-    p.src_y = e.src_y;
-    const int64_t tn = ss.t + 1;
-    p.s_n = tn < e.wavelet_len ? e.wavelet[tn] : 0.0;
-    p.rec = e.rec;
-    p.rec.col = tn;
-    p.partial = nullptr;
-    update_tile<S, Q, KIND, true>(p, (tile * kStepBlock + threadIdx.x) * V, y);
-}
-
-// After a batched step: every active, unfinished shot moves to the next time
-// and swaps its buffers.
-__global__ __launch_bounds__(kBlock) void k_batch_advance(ShotState *state, const int32_t *order, int nact) {
-    int a = blockIdx.x * kBlock + threadIdx.x;
-    if (a >= nact) return;
-    ShotState &ss = state[order[a]];
-    if (ss.active && ss.t < ss.t_end) {
-        ss.t += 1;
-        ss.cur ^= 1;
-    }
-}
-
 __global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, int64_t n, double *out,
                                                           const GraphTab *gtab) {
     double s = 0.0;
+    partial += n * blockIdx.x;   // one time per block
     for (int64_t i = threadIdx.x; i < n; i += kBlock) s += partial[i];
     __shared__ double sh[kBlock];
     sh[threadIdx.x] = s;
@@ -655,7 +599,7 @@ __global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, 
         if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[gtab ? gtab->t0 : 0] = sh[0];
+    if (threadIdx.x == 0) out[(gtab ? gtab->t0 : 0) + blockIdx.x] = sh[0];
 }
 
 // The chunk table of a graph replay, copied from the kernel arguments.
@@ -846,35 +790,6 @@ hipError_t launch_step(int storage, const StepParams &p, bool pull, hipStream_t 
     return hipErrorInvalidValue;
 }
 
-int step_vwidth(int storage) {
-    return storage == ST_F32 ? Tr<float>::V : storage == ST_F64 ? Tr<double>::V : Tr<_Float16>::V;
-}
-
-int step_tile_nodes(int storage) { return step_vwidth(storage) * kStepBlock; }
-
-hipError_t launch_step_batch(int storage, int q, const BatchParams &bp, int64_t nblocks, hipStream_t s) {
-    if (nblocks <= 0 || bp.nact <= 0) return hipSuccess;
-    dim3 grid((unsigned)nblocks);
-    const int kind = step_kind(bp.coll);
-#define LBW_B(SS, QQ)                                                                              \
-    do {                                                                                           \
-        if (kind == 1) hipLaunchKernelGGL((k_step_batch<SS, QQ, 1>), grid, dim3(kStepBlock), 0, s, bp); \
-        else if (kind == 2) hipLaunchKernelGGL((k_step_batch<SS, QQ, 2>), grid, dim3(kStepBlock), 0, s, bp); \
-        else hipLaunchKernelGGL((k_step_batch<SS, QQ, 0>), grid, dim3(kStepBlock), 0, s, bp);      \
-    } while (0)
-    if (storage == ST_F32) { if (q == 5) LBW_B(float, 5); else LBW_B(float, 9); }
-    else if (storage == ST_F64) { if (q == 5) LBW_B(double, 5); else LBW_B(double, 9); }
-    else { if (q == 5) LBW_B(_Float16, 5); else LBW_B(_Float16, 9); }
-#undef LBW_B
-    return hipGetLastError();
-}
-
-hipError_t launch_batch_advance(ShotState *state, const int32_t *order, int nact, hipStream_t s) {
-    if (nact <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch_advance, dim3(blocks_for(nact)), dim3(kBlock), 0, s, state, order, nact);
-    return hipGetLastError();
-}
-
 hipError_t launch_adjoint(int storage, const AdjointParams &p, hipStream_t s) {
     const bool f64 = storage == ST_F64;
     const int V = f64 ? Tr<double>::V : Tr<float>::V;
@@ -913,9 +828,9 @@ hipError_t launch_misfit(int storage, const void *traces, const void *obs, void 
     return hipGetLastError();
 }
 
-hipError_t launch_sum_finalize(const double *partial, int64_t nblocks, double *out, const GraphTab *gtab,
+hipError_t launch_sum_finalize(const double *partial, int64_t nblocks, int times, double *out, const GraphTab *gtab,
                                hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_finalize, dim3(1), dim3(kBlock), 0, s, partial, nblocks, out, gtab);
+    hipLaunchKernelGGL(k_sum_finalize, dim3((unsigned)times), dim3(kBlock), 0, s, partial, nblocks, out, gtab);
     return hipGetLastError();
 }
 

@@ -122,14 +122,20 @@ __device__ inline void store_x(S *__restrict__ row, int x0, int nx, const S (&v)
     }
 }
 
+// The constants of a Collision in the arithmetic type.
+template <typename T> struct CollisionT {
+    T omega, srate[9], kax, kdg, kw, ratio;
+};
+
 // ---- the per-node update ---------------------------------------------------
 // Lattice weights from c^2 (Sec. II C): D2Q5 w_i = c^2/2 for movers,
 // w0 = 1 - 2 c^2; D2Q9 w1 = c^2 kw (kw = 1 / (2 + 4r)), w5 = r w1,
 // w0 = 1 - 4 w1 - 4 w5.
 // (1 - 4 w1 as one fused multiply-add: 4 w1 is exact, so this is the
 // rounding of 1 - 4 w1 either way.)
-template <typename T, int Q>
-__device__ inline void weights(T c2, const Collision &c, T (&w)[Q]) {
+// (C: Collision, or CollisionT<T> with its constants in the arithmetic type.)
+template <typename T, int Q, typename C>
+__device__ inline void weights(T c2, const C &c, T (&w)[Q]) {
     if (Q == 5) {
         T w1 = T(0.5) * c2;
         w[0] = fmaT(T(-4), w1, T(1));
@@ -173,8 +179,8 @@ __device__ inline T geq_rest(const T (&w)[Q], T rho) {
 // C = M^-1 S M applied through the non-conserved moments only (KIND 1).
 // KIND 2 is BGK at omega = 2 (tau = 1/2, the non-dissipative case), where
 // g - 2 (g - g^eq) is 2 g^eq - g: one rounding less and fewer operations.
-template <typename T, int Q, int KIND>
-__device__ inline void collide(const T (&g)[Q], T c2, const Collision &c, T (&out)[Q], T (&w)[Q]) {
+template <typename T, int Q, int KIND, typename C>
+__device__ inline void collide(const T (&g)[Q], T c2, const C &c, T (&out)[Q], T (&w)[Q]) {
     // moments, each sum started from its first term (0 + x is not x for
     // x = -0, so a 0 start would cost an addition the compiler must keep)
     T rho = g[0], jx = T(0), jy = T(0);
@@ -293,11 +299,7 @@ __device__ inline void write_fields(const Receivers &rc, int slot, T rho, T jx, 
 __device__ inline StepParams graph_params(const StepParams &p) {
     StepParams q = p;
     const GraphTab *g = p.gtab;
-    const double *s = g->s + p.goff;
-    q.s_n = s[0];
-    q.s_n2 = s[1];
-    q.s_n3 = s[2];
-    q.s_n4 = s[3];
+    q.s_n = g->s[p.goff];
     q.rec.col += g->t0;
     q.gtab = nullptr;
     return q;

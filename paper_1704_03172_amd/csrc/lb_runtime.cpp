@@ -18,6 +18,8 @@ namespace {
 
 using lbw::Collision;
 using lbw::FieldParams;
+using lbw::FlowInfo;
+using lbw::FlowParams;
 using lbw::InterfaceParams;
 using lbw::PatchGeom;
 using lbw::StepParams;
@@ -30,6 +32,30 @@ using lbw::storage_bytes;
 using lbw::storage_kind;
 
 double c2_max(const lb_grid_desc *d) { return lbw::c2_max(d->lattice, d->d2q9_ratio); }
+
+// Steps per launch that lb_blocked_steps promises: `near` on any grid, `far`
+// on grids of a width and height that allow it and (unless steps_per_launch
+// asks for it) with at least `fill` pieces of 20 rows and `width` columns; at
+// most steps_per_launch.  The flowing kernel takes at least as many on every
+// grid (up to kFlowSteps where no cap is set).
+int promised_steps(const lb_grid_desc *d) {
+    const bool q5 = d->lattice == LB_D2Q5, mrt = d->collision == LB_MRT;
+    int near, far, cols, lanes;   // cols: columns the width is a multiple of; lanes: columns of a lane
+    int64_t fill;
+    if (d->precision == LB_F64) {
+        near = 4; far = q5 ? (mrt ? 7 : 8) : 4; cols = lanes = 1; fill = q5 ? 1800 : 0;
+    } else if (d->precision == LB_F16S) {
+        near = q5 ? 3 : 1; far = q5 ? 5 : 0; cols = 4; lanes = 2; fill = 2500;
+    } else {
+        near = q5 ? 4 : 3; far = q5 ? 7 : mrt ? 5 : 6; cols = lanes = 2; fill = q5 ? 2500 : 1100;
+    }
+    const int cap = d->steps_per_launch;
+    const int width = far > 0 ? (64 - 2 * ((far + lanes - 1) / lanes)) * lanes : 1;
+    const int64_t pieces = (int64_t)((d->nx + width - 1) / width) * ((d->ny + 19) / 20);
+    const bool tall = far > 0 && d->nx % cols == 0 && d->ny >= 20 + 2 * far;
+    if (cap == 0) return tall && pieces >= fill ? std::max(near, far) : near;
+    return tall && cap >= far ? far : std::min(cap, near);
+}
 
 bool omega_is_two(const lb_grid_desc *d) {
     if (d->collision == LB_BGK) return d->tau == 0.5;
@@ -87,6 +113,33 @@ int validate(const lb_grid_desc *d) {
     return LB_OK;
 }
 
+// The shape of the flowing kernel for a grid, the strips of a launch of the
+// most steps, and the steps a launch takes at most.
+struct FlowPlan {
+    bool small = false;
+    FlowInfo f;
+    int32_t steps = 1;
+    int32_t nstrip = 0;
+};
+
+FlowPlan flow_plan(const lb_grid_desc *d) {
+    FlowPlan pl;
+    const int st = storage_kind(d->precision);
+    const lbw::FlowChoice c = lbw::flow_choose(st, d->lattice, (int64_t)d->nx * d->ny);
+    pl.small = c.small;
+    pl.steps = c.steps;
+    pl.f = lbw::flow_info(st, d->lattice, pl.small);
+    FlowParams p;
+    p.nx = d->nx;
+    lbw::flow_strips(pl.f, pl.steps, p);
+    pl.nstrip = p.nstrip;
+    return pl;
+}
+
+// Most steps of a launch that records the sum of rho: bounds the partials'
+// workspace, one per row, strip and step.
+int sum_steps(int64_t nodes) { return nodes <= (1 << 21) ? lbw::kFlowSteps : 4; }
+
 struct Layout {
     int64_t pstride = 0, fpstride = 0;
     int64_t nblocks = 0;
@@ -113,9 +166,11 @@ Layout make_layout(const lb_grid_desc *d) {
     L.rrow = take(((size_t)d->ny + 1) * 4);
     L.rxs = take((size_t)std::max(d->max_receivers, 1) * 4);
     L.rslot = take((size_t)std::max(d->max_receivers, 1) * 4);
-    // the collide-only launch (one node per thread) has the most blocks
+    // partial sums of rho: of time 0, per block of the collide-only launch, and
+    // of the steps of one flowing launch, per row and strip
     L.nblocks = lbw::step_blocks(storage_kind(d->precision), d->nx, d->ny, false);
-    L.partial = take((size_t)L.nblocks * 8);
+    const int64_t rows = (int64_t)sum_steps(n) * d->ny * flow_plan(d).nstrip;
+    L.partial = take((size_t)std::max(L.nblocks, rows) * 8);
     L.scratch = take(256);
     L.misfit = take((size_t)lbw::kMisfitMaxBlocks * 8);
     L.gtab = take(sizeof(lbw::GraphTab));
@@ -170,6 +225,7 @@ struct lb_grid {
     int q = 5;
     Collision coll;
     Layout L;
+    FlowPlan flow;
     char *ws = nullptr;
     Lattice main, fine;
     bool patch = false;
@@ -255,7 +311,8 @@ StepParams base_params(const lb_grid *h, const Lattice &g, bool is_main) {
 // While a chunk is captured for replay: point the launch at the chunk table
 // and make its times relative to the chunk's first time, which is returned
 // (0 outside a capture).
-int64_t graph_time(const lb_grid *h, StepParams &p, int64_t col) {
+template <typename P>
+int64_t graph_time(const lb_grid *h, P &p, int64_t col) {
     if (h->graph_base < 0) return 0;
     p.gtab = h->gtab;
     p.goff = (int32_t)(col - h->graph_base - 1);
@@ -268,7 +325,8 @@ void *tape_field(const lb_grid *h, int64_t n) {
     return (char *)h->tape + (size_t)n * h->main.nx * h->main.ny * h->tsize;
 }
 
-void attach_receivers(const lb_grid *h, const Lattice &g, StepParams &p, int64_t col) {
+template <typename P>
+void attach_receivers(const lb_grid *h, const Lattice &g, P &p, int64_t col) {
     if (!g.has_rec || h->nrec == 0) return;
     p.rec.row_ptr = g.rrow;
     p.rec.xs = g.rxs;
@@ -318,7 +376,7 @@ int launch_update(lb_grid *h, Lattice &g, bool is_main, bool pull, int64_t col, 
     LB_TRY(h, lbw::launch_step(h->storage, p, pull, h->stream));
     if (sum) {
         const int64_t nb = lbw::step_blocks(h->storage, g.nx, g.ny, pull);
-        LB_TRY(h, lbw::launch_sum_finalize(h->partial, nb, h->sum_rho + (col - base), p.gtab, h->stream));
+        LB_TRY(h, lbw::launch_sum_finalize(h->partial, nb, 1, h->sum_rho + (col - base), p.gtab, h->stream));
     }
     g.cur = 1 - g.cur;
     g.prev_pre = pull ? 0 : 1;
@@ -627,14 +685,7 @@ int lb_blocked_steps(const lb_grid_desc *d, int32_t *ns) {
     if (!d || !ns) return LB_E_INVALID;
     int rc = validate(d);
     if (rc) return rc;
-    const int sk = lbw::step_kind(lbw::make_collision(d));
-    const int st = storage_kind(d->precision);
-    int m = lbw::stepn_max_grid(st, d->lattice, sk, d->nx, d->ny, true);
-    if (d->steps_per_launch > 0)   // an explicit cap may ask for the marching kernel at any size
-        m = lbw::stepn_round(st, d->lattice, sk, d->nx, d->ny,
-                             std::min(lbw::stepn_max_grid(st, d->lattice, sk, d->nx, d->ny), (int)d->steps_per_launch));
-    if (d->patch_enable) m = 1;
-    *ns = m;
+    *ns = d->patch_enable ? 1 : promised_steps(d);
     return LB_OK;
 }
 
@@ -661,6 +712,7 @@ int lb_create_grid(const lb_grid_desc *d, void *d_workspace, size_t ws_bytes, vo
     h->L = L;
     h->ws = (char *)d_workspace;
     h->coll = lbw::make_collision(d);
+    h->flow = flow_plan(d);
 
     Lattice &m = h->main;
     m.nx = d->nx;
@@ -812,75 +864,100 @@ int lb_record_sum_rho(lb_grid *h, double *d_sum) {
     return LB_OK;
 }
 
-// Steps per launch of the blocked kernels for this grid (1: none): up to
-// stepn_max steps, and on grids that the marching kernel takes and fills
-// with its waves also its (larger) step count; a descriptor's
-// steps_per_launch caps it, and may ask for the marching kernel on any grid
-// it takes.
-int blocked_max(const lb_grid *h) {
+}  // extern "C"
+
+namespace {
+
+// Most steps of one launch of lb_step_n: what the flowing kernel offers, at
+// most the descriptor's steps_per_launch (if set); one with a patch.
+int most_steps(const lb_grid *h) {
     if (h->patch) return 1;
-    const int sk = lbw::step_kind(h->coll);
-    int ns = lbw::stepn_max_grid(h->storage, h->q, sk, h->d.nx, h->d.ny, true);
-    if (h->d.steps_per_launch > 0)   // an explicit cap may ask for the marching kernel at any size
-        ns = lbw::stepn_round(h->storage, h->q, sk, h->d.nx, h->d.ny,
-                              std::min(lbw::stepn_max_grid(h->storage, h->q, sk, h->d.nx, h->d.ny),
-                                       h->d.steps_per_launch));
+    int ns = h->flow.steps;
+    if (h->sum_rho) ns = std::min(ns, sum_steps((int64_t)h->d.nx * h->d.ny));
+    if (h->d.steps_per_launch > 0) ns = std::min(ns, h->d.steps_per_launch);
     return ns;
 }
 
-// Steps the next launch may take: at most blocked_max, and a launch from t
-// to t+ns skips the states h(t+1) .. h(t+ns-1), so no checkpoint column
-// (whose launch pulls from h(col-1)) may fall in t+2 .. t+ns.  left: steps
-// still to take in this call; the last launch of a call takes one step (the
-// fields and the saved state of time t are read from h(t-1)).  The count is
-// rounded down to one a kernel takes (1 .. stepn_max, or the marching
-// kernel's).
-int blocked_steps(const lb_grid *h, int64_t left) {
-    if (h->patch || h->sum_rho) return 1;
-    if (h->graph_base >= 0) {   // a captured chunk: the graph entry kernels' one count, else one step
-        const int g = lbw::stepn_graph_steps(h->storage, h->q, lbw::step_kind(h->coll), h->d.nx);
-        return std::min(g, blocked_max(h)) == g && left - 1 >= g ? g : 1;
-    }
-    int ns = blocked_max(h);
-    ns = (int)std::min<int64_t>(ns, left - 1);
-    if (h->ckpt_valid)
-        for (int k = 2; k <= ns; ++k)
-            if ((h->t + k) % h->d.ckpt_every == 0) {
-                ns = k - 1;
-                break;
-            }
-    if (ns < 2) return 1;
-    return lbw::stepn_round(h->storage, h->q, lbw::step_kind(h->coll), h->d.nx, h->d.ny, ns);
+// Steps of the next launch when `m` steps may be taken by launches of up to
+// `most` steps: as few launches as that needs, of about equal length.
+int even_steps(int64_t m, int most) {
+    if (m <= 1) return 1;
+    const int64_t launches = (m + most - 1) / most;
+    return (int)((m + launches - 1) / launches);
 }
 
-// Steps t -> t+ns in one launch of the blocked kernel (columns t+1 .. t+ns).
-int blocked_launch(lb_grid *h, int ns) {
+// Steps the next launch may take: a launch from t to t+ns skips the states
+// h(t+1) .. h(t+ns-1), so no checkpoint column (whose launch pulls from
+// h(col-1)) may fall in t+2 .. t+ns.  left: steps still to take in this call;
+// the last launch of a call takes one step (the fields and the saved state of
+// time t are read from h(t-1)).
+int next_steps(const lb_grid *h, int64_t left) {
+    int64_t m = left - 1;
+    if (h->ckpt_valid) {
+        const int64_t K = h->d.ckpt_every, room = K - 1 - h->t % K;
+        m = std::min(m, room > 0 ? room : K);   // (no room: t + 1 is such a column, saved before the launch)
+    }
+    return even_steps(m, most_steps(h));
+}
+
+// The launch parameters of the flowing kernel for the main grid: steps of
+// times col, col + 1, .. (recorded into column col ..), up to `steps`.
+FlowParams flow_params(const lb_grid *h, int64_t col, int ns, int steps) {
+    const Lattice &g = h->main;
+    FlowParams p;
+    p.src = g.curp();
+    p.dst = g.prevp();
+    p.c2 = g.c2;
+    p.nx = g.nx;
+    p.ny = g.ny;
+    p.pstride = g.pstride;
+    p.nrun = ns;
+    p.sponge_width = h->d.sponge_width;
+    p.sponge_smax = h->d.sponge_sigma_max;
+    p.src_x = h->sx;
+    p.src_y = h->sy;
+    p.coll = h->coll;
+    for (int k = 0; k < lbw::kFlowSteps; ++k) p.s[k] = source_at(h, col + k);
+    lbw::flow_geometry(h->flow.f, steps, lbw::kFlowBlocks, p);
+    return p;
+}
+
+// Steps t -> t+ns in one launch of the flowing kernel (columns t+1 .. t+ns).
+int flow_launch(lb_grid *h, int ns) {
     const int64_t col = h->t + 1;
     if (h->ckpt_valid && col % h->d.ckpt_every == 0) {
         int rc = save_checkpoint(h, col, false);
         if (rc) return rc;
     }
-    Lattice &g = h->main;
-    StepParams p = base_params(h, g, true);
-    p.src = g.curp();
-    p.dst = g.prevp();
-    p.s_n = source_at(h, col);
-    p.s_n2 = source_at(h, col + 1);
-    p.s_n3 = source_at(h, col + 2);
-    p.s_n4 = source_at(h, col + 3);
-    for (int k = 0; k < 4; ++k) p.s_more[k] = source_at(h, col + 4 + k);
-    p.nrun = ns;
-    if (recording(h)) attach_receivers(h, g, p, col);
+    // with the sum of rho the strips stay those of the longest launch, so that
+    // the partials of a time, and with them the bits of its sum, do not depend
+    // on how the steps are divided into launches
+    FlowParams p = flow_params(h, col, ns, h->sum_rho ? h->flow.steps : ns);
+    if (recording(h)) attach_receivers(h, h->main, p, col);
     if (h->tape_valid) {   // rho of times col .. col + ns - 1
         p.rho_out = tape_field(h, col);
-        p.rho_stride = (int64_t)g.nx * g.ny;
+        p.rho_stride = (int64_t)p.nx * p.ny;
     }
-    graph_time(h, p, col);
-    LB_TRY(h, lbw::launch_stepn(h->storage, p, ns, h->stream));
-    g.cur = 1 - g.cur;
-    g.prev_pre = 0;
+    const int64_t parts = (int64_t)p.ny * p.nstrip;
+    if (h->sum_rho) {
+        p.sum = h->partial;
+        p.sum_stride = parts;
+    }
+    const int64_t base = graph_time(h, p, col);
+    LB_TRY(h, lbw::launch_flow(h->storage, h->q, h->flow.small, p, h->stream));
+    if (h->sum_rho) LB_TRY(h, lbw::launch_sum_finalize(h->partial, parts, ns, h->sum_rho + (col - base), p.gtab, h->stream));
+    h->main.cur = 1 - h->main.cur;
+    h->main.prev_pre = 0;
     h->t = col + ns - 1;
     return LB_OK;
+}
+
+// The next launch of a call with `left` steps to take; *ns: the steps taken.
+// Single steps go through the one-step kernel unless the sum of rho is
+// recorded (see flow_launch).
+int next_launch(lb_grid *h, int64_t left, int *ns) {
+    *ns = next_steps(h, left);
+    return *ns > 1 || (h->sum_rho && !h->patch) ? flow_launch(h, *ns) : one_step(h);
 }
 
 // Whether lb_step_n may replay graphs now: enabled, no patch (three
@@ -892,8 +969,7 @@ bool graph_ok(const lb_grid *h) {
 }
 
 // One chunk of graph_k steps, replayed from a captured graph.  The chunk's
-// launches are those of a call of graph_k steps (blocked launches of at most
-// stepn_max steps, the last launch one step) with their times relative to
+// launches are those of a call of graph_k steps with their times relative to
 // the chunk's first time t0; before each replay one small launch writes t0
 // and the chunk's source amplitudes into the chunk table.  One graph thus
 // serves every chunk that starts from the same buffer; it is captured on
@@ -917,8 +993,8 @@ int graph_chunk(lb_grid *h) {
         h->graph_base = t0;
         int rc = LB_OK;
         for (int64_t k = 0; k < h->graph_k && rc == LB_OK;) {
-            const int ns = blocked_steps(h, h->graph_k - k);
-            rc = ns > 1 ? blocked_launch(h, ns) : one_step(h);
+            int ns = 1;
+            rc = next_launch(h, h->graph_k - k, &ns);
             k += ns;
         }
         h->graph_base = -1;
@@ -947,6 +1023,10 @@ int graph_chunk(lb_grid *h) {
     return LB_OK;
 }
 
+}  // namespace
+
+extern "C" {
+
 int lb_step_n(lb_grid *h, int64_t n) {
     if (!h) return LB_E_INVALID;
     if (h->sticky) return h->sticky;
@@ -964,12 +1044,8 @@ int lb_step_n(lb_grid *h, int64_t n) {
             k += h->graph_k;
             continue;
         }
-        const int ns = blocked_steps(h, n - k);
-        if (ns > 1) {
-            if ((rc = blocked_launch(h, ns))) return rc;
-        } else if ((rc = one_step(h))) {
-            return rc;
-        }
+        int ns = 1;
+        if ((rc = next_launch(h, n - k, &ns))) return rc;
         k += ns;
     }
     return LB_OK;
@@ -1110,7 +1186,8 @@ int adjoint_backward(lb_grid *h, lbw::AdjointParams &ap, char *rho_base, int64_t
                      int &cur_lam) {
     const int64_t n_nodes = (int64_t)h->main.nx * h->main.ny;
     const size_t field = (size_t)n_nodes * h->tsize;
-    const int nmax = std::min(lbw::adjointn_max(h->storage, h->q), blocked_max(h));
+    const int nmax = std::min(lbw::adjointn_max(h->storage, h->q),
+                              h->d.steps_per_launch > 0 ? h->d.steps_per_launch : lbw::kFlowSteps);
     for (int64_t n = b; n >= a;) {
         ap.rho = rho_base + (size_t)(n - a) * field;
         ap.terminal = n == nt;
@@ -1186,28 +1263,26 @@ int lb_adjoint(lb_grid *h, const void *d_res, int64_t nt, double *d_grad) {
         LB_TRY(h, lbw::launch_copy(g.pop[0], h->ckpt + (size_t)j * state_bytes_main(h), state_bytes_main(h),
                                    h->stream));
         g.cur = 0;
-        // the segment's rho fields, up to blocked_max steps per launch (the
-        // collide-only launch of a pre-collision checkpoint takes one)
+        // the segment's rho fields, through the flowing kernel (the
+        // collide-only launch of a pre-collision checkpoint takes one step)
         for (int64_t m = a; m <= b;) {
             const bool pull = !(m == a && h->ckpt_pre[(size_t)j]);
-            StepParams p = base_params(h, g, true);
-            p.src = g.curp();
-            p.dst = g.prevp();
-            p.s_n = source_at(h, m);
-            p.rho_out = (char *)h->seg + (size_t)(m - a) * n_nodes * tsz;
-            // (rounded down to a count a kernel takes)
-            const int ns = pull ? lbw::stepn_round(h->storage, h->q, lbw::step_kind(h->coll), h->d.nx, h->d.ny,
-                                                   (int)std::min<int64_t>(blocked_max(h), b - m + 1))
+            void *rho = (char *)h->seg + (size_t)(m - a) * n_nodes * tsz;
+            const int ns = pull ? even_steps(b - m + 1, h->d.steps_per_launch > 0
+                                                            ? std::min(h->d.steps_per_launch, (int)h->flow.steps)
+                                                            : (int)h->flow.steps)
                                 : 1;
             if (ns > 1) {
-                p.s_n2 = source_at(h, m + 1);
-                p.s_n3 = source_at(h, m + 2);
-                p.s_n4 = source_at(h, m + 3);
-                for (int k = 0; k < 4; ++k) p.s_more[k] = source_at(h, m + 4 + k);
-                p.nrun = ns;
+                FlowParams p = flow_params(h, m, ns, ns);
+                p.rho_out = rho;
                 p.rho_stride = n_nodes;
-                LB_TRY(h, lbw::launch_stepn(h->storage, p, ns, h->stream));
+                LB_TRY(h, lbw::launch_flow(h->storage, h->q, h->flow.small, p, h->stream));
             } else {
+                StepParams p = base_params(h, g, true);
+                p.src = g.curp();
+                p.dst = g.prevp();
+                p.s_n = source_at(h, m);
+                p.rho_out = rho;
                 LB_TRY(h, lbw::launch_step(h->storage, p, pull, h->stream));
             }
             g.cur = 1 - g.cur;

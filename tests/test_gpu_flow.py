@@ -1,0 +1,68 @@
+"""Many steps per launch on grids that take the wide shape of the flowing
+kernel (from 0.8 M nodes; D2Q9 with 32-bit arithmetic from 3 M): bitwise equal
+to one step per launch.
+
+The strips are 96 to 112 (FP32) or 32 to 48 (FP64) stored columns wide and the
+bundles 5, 7 or 10 rows high, so ragged sides leave a partial last strip and
+bundle, odd widths a strip across the periodic seam with element-wise
+accesses, and step counts around a launch's 6 to 16 steps launches of unequal
+length.  Receivers sit on strip and bundle edges, in the sponge, on the seam
+and on every node of two rows (more than a bundle's receiver table holds); the
+source on an edge of both.
+"""
+import numpy as np
+import pytest
+
+from paper_1704_03172_amd import inputs
+from tests.harness import FIELDS, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+MRT5 = [1, 1, 1, 1.6, 1.3]
+MRT9 = [1, 1, 1, 2, 2, 2, 1, 1, 2]
+SIZES = {5: [(1301, 617), (618, 1300)], 9: [(2501, 1203), (1204, 2500)]}
+
+
+def case(nx, ny, q, collision, tau, s, nsteps):
+    rng = np.random.default_rng(nx + ny)
+    rho, jx, jy = inputs.random_fields(nx, ny, seed=nx)
+    xs = sorted({0, 1, nx - 2, nx - 1} | {k * w + d for w in (96, 104, 112, 48, 32) for k in (1, 2) for d in (-1, 0, 1)})
+    ys = sorted({0, 1, ny - 2, ny - 1} | {k * h + d for h in (5, 7, 10) for k in (1, 9) for d in (-1, 0)})
+    xs, ys = [x for x in xs if x < nx], [y for y in ys if y < ny]
+    dense = [(x, y) for y in (33, 36) for x in range(nx)]
+    return {"nx": nx, "ny": ny, "q": q, "collision": collision, "tau": tau, "s": s,
+            "c2": rng.uniform(0.05, 0.45, (ny, nx)), "rho0": rho, "jx0": jx, "jy0": jy, "nsteps": nsteps,
+            "sponge_width": 9, "sponge_sigma_max": 0.1, "source": (96, 7),
+            "wavelet": 1e-2 * inputs.ricker_wavelet(nsteps + 1, 0.1),
+            "receivers": np.array([(x, y) for y in ys for x in xs] + dense, dtype=np.int32)}
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64", "f16s"])
+@pytest.mark.parametrize("q,collision,tau,s", [(5, "bgk", 0.5, None), (5, "bgk", 0.8, None), (5, "mrt", 0.5, MRT5),
+                                               (9, "bgk", 0.5, None), (9, "mrt", 0.5, MRT9)])
+def test_wide_shape_equals_one_step(precision, q, collision, tau, s):
+    for (nx, ny), nsteps in zip(SIZES[5 if precision == "f64" else q], (36, 19)):
+        c = case(nx, ny, q, collision, tau, s, nsteps)
+        one = run_gpu(c, precision, steps_per_launch=1)
+        many = run_gpu(c, precision, chunks=[nsteps - 1, 1] if ny > nx else None)
+        assert np.abs(one["traces"]).max() > 0
+        np.testing.assert_array_equal(one["traces"], many["traces"])
+        for f in FIELDS:
+            np.testing.assert_array_equal(one["fields"][f], many["fields"][f])
+
+
+@pytest.mark.parametrize("n,precision", [(200, "f32"), (1100, "f32"), (150, "f64")])
+def test_sum_rho_of_many_steps(n, precision):
+    """The sum of rho of every time, recorded inside launches of many steps:
+    the same bits however the steps are divided into calls and launches, and
+    the sum of the recorded field to rounding."""
+    c = case(n, n + 3, 5, "bgk", 0.5, None, 41)
+    a = run_gpu(c, precision, sum_rho=True)
+    b = run_gpu(c, precision, sum_rho=True, chunks=[1, 7, 0, 20, 13])
+    d = run_gpu(c, precision, sum_rho=True, steps_per_launch=3)
+    np.testing.assert_array_equal(a["sum_rho"], b["sum_rho"])
+    np.testing.assert_array_equal(a["sum_rho"], d["sum_rho"])
+    np.testing.assert_array_equal(a["traces"], b["traces"])
+    rho = a["fields"]["rho"].astype(np.float64)
+    # rounding of an FP64 sum of n terms: at most n eps times the sum of their sizes
+    assert abs(a["sum_rho"][-1] - rho.sum()) <= rho.size * 2.0 ** -53 * np.abs(rho).sum()
