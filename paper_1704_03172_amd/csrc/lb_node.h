@@ -34,7 +34,7 @@ __host__ __device__ constexpr int cyv(int i) {
 
 // Rows of the moment matrix of Appendix A (non-conserved rows only are
 // used: D2Q5 k = 3 (e), 4 (pxx); D2Q9 k = 3 (e), 4 (pxx), 5 (eps),
-// 6 (qx), 7 (qy), 8 (pxy)).
+// 6 (qx), 7 (qy), 8 (pxy)); mrt_apply() has them factored.
 template <int Q>
 __host__ __device__ constexpr int mrow(int k, int i) {
     if (Q == 5) {
@@ -174,6 +174,44 @@ __device__ inline T geq_rest(const T (&w)[Q], T rho) {
     else return w[0] * rho;
 }
 
+// acc = C d with C = M^-1 S M through the non-conserved moments only (C is
+// symmetric): the rows of mrow() through the sums and differences of opposite
+// populations, 45 operations for D2Q9 where the rows taken one by one cost 130
+// (FP64 MRT on 701 x 899: 8.6 us per step before, 7.6 after).
+template <typename T, int Q, typename C>
+__device__ inline void mrt_apply(const T (&d)[Q], const C &c, T (&acc)[Q]) {
+    if constexpr (Q == 5) {
+        const T x = d[1] + d[3], y = d[2] + d[4];
+        const T re = T(c.srate[3]) * fmaT(T(-4), d[0], x + y), rp = T(c.srate[4]) * (x - y);
+        acc[0] = T(-4) * re;
+        acc[1] = acc[3] = re + rp;
+        acc[2] = acc[4] = re - rp;
+    } else {
+        const T s1 = d[1] + d[3], s2 = d[2] + d[4], s5 = d[5] + d[7], s6 = d[6] + d[8];
+        const T a1 = d[1] - d[3], a2 = d[2] - d[4], a5 = d[5] - d[7], a6 = d[6] - d[8];
+        const T sx = s1 + s2, sd = s5 + s6;
+        const T re = T(c.srate[3]) * fmaT(T(2), sd, fmaT(T(-4), d[0], -sx));
+        const T rp = T(c.srate[4]) * (s1 - s2);
+        const T rs = T(c.srate[5]) * fmaT(T(-2), sx, fmaT(T(4), d[0], sd));
+        const T rx = T(c.srate[6]) * fmaT(T(-2), a1, a5 - a6);
+        const T ry = T(c.srate[7]) * fmaT(T(-2), a2, a5 + a6);
+        const T rxy = T(c.srate[8]) * (s5 - s6);
+        // axis movers: -re - 2 rs +- rp -+ 2 rx (or ry); diagonal ones:
+        // 2 re + rs +- (rx +- ry) +- rxy
+        const T ba = fmaT(T(-2), rs, -re), bd = fmaT(T(2), re, rs);
+        const T bx = ba + rp, by = ba - rp, b5 = bd + rxy, b6 = bd - rxy, p = rx + ry, m = rx - ry;
+        acc[0] = T(4) * (rs - re);
+        acc[1] = fmaT(T(-2), rx, bx);
+        acc[2] = fmaT(T(-2), ry, by);
+        acc[3] = fmaT(T(2), rx, bx);
+        acc[4] = fmaT(T(2), ry, by);
+        acc[5] = b5 + p;
+        acc[6] = b6 - m;
+        acc[7] = b5 - p;
+        acc[8] = b6 + m;
+    }
+}
+
 // Collision of one node: out = g - C (g - g^eq) with the linear equilibrium
 // g^eq_i = w_i rho + (w_i / c^2)(c_i . J); BGK C = omega I (KIND 0), MRT
 // C = M^-1 S M applied through the non-conserved moments only (KIND 1).
@@ -240,27 +278,10 @@ __device__ inline void collide(const T (&g)[Q], T c2, const C &c, T (&out)[Q], T
 #pragma unroll
         for (int i = 0; i < Q; ++i) out[i] = fmaT(-om, d[i], g[i]);
     } else {
-        T r[9];
+        T acc[Q];
+        mrt_apply<T, Q>(d, c, acc);
 #pragma unroll
-        for (int k = 3; k < Q; ++k) {
-            T m = T(0);
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                int a = mrow<Q>(k, i);
-                if (a != 0) m += T(a) * d[i];
-            }
-            r[k] = T(c.srate[k]) * m;
-        }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            T acc = T(0);
-#pragma unroll
-            for (int k = 3; k < Q; ++k) {
-                int a = mrow<Q>(k, i);
-                if (a != 0) acc += T(a) * r[k];
-            }
-            out[i] = g[i] - acc;
-        }
+        for (int i = 0; i < Q; ++i) out[i] = g[i] - acc[i];
     }
 }
 
