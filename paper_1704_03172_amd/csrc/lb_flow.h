@@ -134,7 +134,28 @@ __device__ inline double lane_of(double v, int k) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-template <typename S, int Q, int KIND, int V, int R, int W, int E>
+// Sum over the lanes, in lane 63: DPP row rotations by 8, 4, 2, 1 (every lane
+// of a row of 16 then holds that row's sum), then row_bcast:15 into rows 1 and
+// 3 and row_bcast:31 into rows 2 and 3.
+template <int CTRL, int ROWS>
+__device__ inline double dpp_add(double a) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, a);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, false);
+    return a + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ inline double wave_total(double a) {
+    a = dpp_add<0x128, 0xF>(a);
+    a = dpp_add<0x124, 0xF>(a);
+    a = dpp_add<0x122, 0xF>(a);
+    a = dpp_add<0x121, 0xF>(a);
+    a = dpp_add<0x142, 0xA>(a);
+    return dpp_add<0x143, 0xC>(a);
+}
+
+// OUT: the launch writes rho or its sums (a kernel of its own: the code costs
+// the others scalar registers, 2 % of a 4096^2 shot).
+template <typename S, int Q, int KIND, int V, int R, int W, int E, bool OUT>
 __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int blk) {
     using T = typename Tr<S>::T;
     typedef typename LaneVec<V, T>::type ct;
@@ -155,6 +176,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
         fin[threadIdx.x] = 0;
     }
     __syncthreads();
+    const bool frho = OUT && p->rho_out != nullptr, fsum = OUT && p->sum != nullptr;
     const int wp = w > 0 ? w - 1 : W - 1, wc = w < W - 1 ? w + 1 : 0;
     const int L = p->sponge_width;
     CollisionT<T> coll;
@@ -288,7 +310,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                 if (p->rec.nslots > 0x80000) nrec = 64 * V + 1;   // slots too large for the table
             }
             mpre = mrec;
-            if (p->rho_out != nullptr || p->sum != nullptr) mpre |= (uint32_t)__ballot(owned);
+            if (frho || fsum) mpre |= (uint32_t)__ballot(owned);
             // the ring slot is free once the bundles that read its rows are done
             for (int m = 0; m <= mlast; ++m) {
                 const int qq = q - W - E + m;
@@ -338,6 +360,9 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
             const uint32_t bpre = mpre >> sh, bpost = (msrc | mspo) >> sh;
             T fyl = T(1);
             if (mspo) fyl = *sb;
+            // where slot 0's row of rho and of its sums goes
+            T *const rho_s = frho ? reinterpret_cast<T *>(p->rho_out) + (int64_t)(s - 1) * p->rho_stride + (int64_t)(Y - s) * nx : nullptr;
+            double *const sum_s = fsum ? p->sum + (int64_t)(s - 1) * p->sum_stride + (int64_t)(Y - s) * p->nstrip + sx : nullptr;
             ct cn = cb[(R - 1) * 64];
             auto row = [&](auto rc, const T (&U)[Q][V], const T (&C)[Q][V], const T (&D)[Q][V]) __attribute__((always_inline)) {
                 constexpr int r = decltype(rc)::value;
@@ -348,10 +373,9 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                 T g[Q][V];
                 pull_row2<T, Q, V>(U, C, D, g);
                 if (__builtin_expect((bpre >> r) & 1, 0)) {
-                    const KernFlow z = rare(p);
                     const int gy = Y + r - s, xl = xa + lane * V, c0 = lane * V;
                     const bool own0 = c0 >= hx && c0 < hx + ow && xl < nx;
-                    if (z->rho_out != nullptr || z->sum != nullptr) {   // summed as the one-step kernel sums it
+                    if (OUT && (frho | fsum)) {   // summed as the one-step kernel sums it
                         T rv[V];
 #pragma unroll
                         for (int j = 0; j < V; ++j) {
@@ -359,29 +383,30 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
 #pragma unroll
                             for (int i = 0; i < Q; ++i) rv[j] += g[i][j];
                         }
-                        if (z->rho_out != nullptr && own0) {
-                            T *rr = reinterpret_cast<T *>(z->rho_out) + (int64_t)(s - 1) * z->rho_stride + (int64_t)gy * nx;
+                        if (frho && own0) {
+                            T *rr = rho_s + (int64_t)r * nx;
                             if (xl + V <= nx) {
                                 ct t;
 #pragma unroll
                                 for (int j = 0; j < V; ++j) t[j] = rv[j];
-                                *(GlobalPtr<ct>)at_lane<ct>(rr, xl) = t;
+                                st_nt(t, at_lane<ct>(rr, xl));
                             } else {
 #pragma unroll
                                 for (int j = 0; j < V - 1; ++j)
-                                    if (xl + j < nx) rr[xl + j] = rv[j];
+                                    if (xl + j < nx) st_nt(rv[j], rr + xl + j);
                             }
                         }
-                        if (z->sum != nullptr) {   // one partial per row and strip
+                        if (fsum) {   // one partial per row and strip
                             double a = 0.0;
 #pragma unroll
                             for (int j = 0; j < V; ++j)
                                 if (own0 && xl + j < nx) a += double(rv[j]);
-                            for (int off = 32; off > 0; off >>= 1) a += __shfl_down(a, off, 64);
-                            if (lane == 0) z->sum[(int64_t)(s - 1) * z->sum_stride + (int64_t)gy * z->nstrip + sx] = a;
+                            a = wave_total(a);
+                            if (lane == 63) st_nt(a, sum_s + r * p->nstrip);
                         }
                     }
                     if ((mrec >> (sh + r)) & 1) {
+                        const KernFlow z = rare(p);
                         Receivers rx;
                         rx.row_ptr = z->rec.row_ptr;
                         rx.xs = z->rec.xs;
@@ -540,7 +565,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
 // Single grid (fb.img == nullptr: the parameters are the kernel arguments) or
 // every active shot of a batch (block k belongs to the shot a with prefix[a]
 // <= k < prefix[a + 1] and takes its params image of the round).
-template <typename S, int Q, int KIND, bool SMALL>
+template <typename S, int Q, int KIND, bool SMALL, bool OUT>
 __global__ __launch_bounds__((FlowShape<S, Q, SMALL>::W * 64))
 __attribute__((amdgpu_waves_per_eu(FlowShape<S, Q, SMALL>::EU, FlowShape<S, Q, SMALL>::EU)))
 void k_flow(FlowParams, FlowBatch fb) {
@@ -557,17 +582,17 @@ void k_flow(FlowParams, FlowBatch fb) {
         p = (KernFlow)(fb.img + __builtin_amdgcn_readfirstlane(fb.order[lo]));
         if (p->nrun < 1) return;
     }
-    flow_body<S, Q, KIND, F::V, F::R, F::W, F::E>(p, blk);
+    flow_body<S, Q, KIND, F::V, F::R, F::W, F::E, OUT>(p, blk);
 }
 
-template <typename S, int Q, bool SMALL>
+template <typename S, int Q, bool SMALL, bool OUT>
 hipError_t flow_launch(const FlowParams &p, const FlowBatch &fb, int64_t nblk, int kind, hipStream_t s) {
     using F = FlowShape<S, Q, SMALL>;
     if (nblk < 1 || nblk > (1 << 30)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblk), block(F::W * 64);
-    if (kind == 1) hipLaunchKernelGGL((k_flow<S, Q, 1, SMALL>), grid, block, 0, s, p, fb);
-    else if (kind == 2) hipLaunchKernelGGL((k_flow<S, Q, 2, SMALL>), grid, block, 0, s, p, fb);
-    else hipLaunchKernelGGL((k_flow<S, Q, 0, SMALL>), grid, block, 0, s, p, fb);
+    if (kind == 1) hipLaunchKernelGGL((k_flow<S, Q, 1, SMALL, OUT>), grid, block, 0, s, p, fb);
+    else if (kind == 2) hipLaunchKernelGGL((k_flow<S, Q, 2, SMALL, OUT>), grid, block, 0, s, p, fb);
+    else hipLaunchKernelGGL((k_flow<S, Q, 0, SMALL, OUT>), grid, block, 0, s, p, fb);
     return hipGetLastError();
 }
 
@@ -590,8 +615,11 @@ FlowInfo flow_info() {
 #define LBW_FLOW_UNIT(SS, QQ, NAME)                                                                                 \
     hipError_t launch_flow_##NAME(bool small, const FlowParams &p, const FlowBatch &fb, int64_t nblk, int kind,      \
                                   hipStream_t s) {                                                                  \
-        return small ? flow_launch<SS, QQ, true>(p, fb, nblk, kind, s)                                              \
-                     : flow_launch<SS, QQ, false>(p, fb, nblk, kind, s);                                            \
+        const bool out = p.rho_out != nullptr || p.sum != nullptr;                                                  \
+        if (out) return small ? flow_launch<SS, QQ, true, true>(p, fb, nblk, kind, s)                               \
+                              : flow_launch<SS, QQ, false, true>(p, fb, nblk, kind, s);                             \
+        return small ? flow_launch<SS, QQ, true, false>(p, fb, nblk, kind, s)                                       \
+                     : flow_launch<SS, QQ, false, false>(p, fb, nblk, kind, s);                                     \
     }                                                                                                               \
     FlowInfo flow_info_##NAME(bool small) { return small ? flow_info<SS, QQ, true>() : flow_info<SS, QQ, false>(); }
 
