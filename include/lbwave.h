@@ -128,6 +128,9 @@ typedef struct lb_grid lb_grid;
  *                  checkpoints (no ckpt_every needed).  Steps per launch as
  *                  without the tape (the multi-step kernels also write
  *                  rho).  Not with a patch.  0: off.
+ *                  LB_F32 D2Q5 grids with rho_tape or ckpt_every evaluate
+ *                  the collision in another order than those without: the
+ *                  same values to FP32 rounding, not the same bits.
  */
 typedef struct {
     int32_t nx, ny;

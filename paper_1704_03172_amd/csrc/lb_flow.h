@@ -180,8 +180,8 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
     const int wp = w > 0 ? w - 1 : W - 1, wc = w < W - 1 ? w + 1 : 0;
     const int L = p->sponge_width;
     CollisionT<T> coll;
-    if constexpr (KIND == 0) coll.omega = uniform(T(p->coll.omega));
-    if constexpr (KIND == 1)
+    if constexpr (KIND % 3 == 0) coll.omega = uniform(T(p->coll.omega));
+    if constexpr (KIND % 3 == 1)
         for (int k = 3; k < Q; ++k) coll.srate[k] = uniform(T(p->coll.srate[k]));
     if constexpr (Q == 9) {
         coll.kax = uniform(T(p->coll.kax));
@@ -590,10 +590,10 @@ hipError_t flow_launch(const FlowParams &p, const FlowBatch &fb, int64_t nblk, i
     using F = FlowShape<S, Q, SMALL>;
     if (nblk < 1 || nblk > (1 << 30)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblk), block(F::W * 64);
-    if (kind == 1) hipLaunchKernelGGL((k_flow<S, Q, 1, SMALL, OUT>), grid, block, 0, s, p, fb);
-    else if (kind == 2) hipLaunchKernelGGL((k_flow<S, Q, 2, SMALL, OUT>), grid, block, 0, s, p, fb);
-    else hipLaunchKernelGGL((k_flow<S, Q, 0, SMALL, OUT>), grid, block, 0, s, p, fb);
-    return hipGetLastError();
+    return for_kind<S, Q>(kind, [&](auto kc) {
+        hipLaunchKernelGGL((k_flow<S, Q, decltype(kc)::value, SMALL, OUT>), grid, block, 0, s, p, fb);
+        return hipGetLastError();
+    });
 }
 
 template <typename S, int Q, bool SMALL>

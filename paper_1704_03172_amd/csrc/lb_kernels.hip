@@ -728,6 +728,13 @@ inline unsigned blocks_for(int64_t n) { return unsigned((n + kBlock - 1) / kBloc
 template <typename S>
 int vwidth(bool pull) { return pull ? Tr<S>::V : 1; }
 
+// f(lattice, kind), both as integral constants.
+template <typename S, typename F>
+hipError_t step_by_lattice(int q, int kind, F &&f) {
+    if (q == 5) return for_kind<S, 5>(kind, [&](auto kc) { return f(std::integral_constant<int, 5>(), kc); });
+    return for_kind<S, 9>(kind, [&](auto kc) { return f(std::integral_constant<int, 9>(), kc); });
+}
+
 template <typename S>
 hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
     const int V = vwidth<S>(pull);
@@ -742,35 +749,26 @@ hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
             grid.y += (unsigned)rows;
         } else {   // a launch of its own first
             dim3 pg((unsigned)ring_tile_blocks<kBlock>(p0.iface.g));
-            if (kind == 1) hipLaunchKernelGGL((k_prolong_pair<S, 1>), pg, dim3(kBlock), 0, s, p0.iface);
-            else if (kind == 2) hipLaunchKernelGGL((k_prolong_pair<S, 2>), pg, dim3(kBlock), 0, s, p0.iface);
-            else hipLaunchKernelGGL((k_prolong_pair<S, 0>), pg, dim3(kBlock), 0, s, p0.iface);
+            const hipError_t e = for_kind<S, 5>(kind, [&](auto kc) {
+                hipLaunchKernelGGL((k_prolong_pair<S, decltype(kc)::value>), pg, dim3(kBlock), 0, s, p0.iface);
+                return hipGetLastError();
+            });
+            if (e != hipSuccess) return e;
         }
     }
     if (p.gtab) {   // a launch of a captured chunk: its own entry kernel
         if (!pull || p.prolong_on || p.restrict_on || p.snap || p.ring_buf) return hipErrorInvalidValue;
-#define LBW_GRAPH(QQ, KK) hipLaunchKernelGGL((k_step_graph<S, QQ, KK>), grid, dim3(kStepBlock), 0, s, p)
-        if (p.q == 5) {
-            if (kind == 0) LBW_GRAPH(5, 0); else if (kind == 2) LBW_GRAPH(5, 2); else LBW_GRAPH(5, 1);
-        } else {
-            if (kind == 0) LBW_GRAPH(9, 0); else if (kind == 2) LBW_GRAPH(9, 2); else LBW_GRAPH(9, 1);
-        }
-#undef LBW_GRAPH
+        return step_by_lattice<S>(p.q, kind, [&](auto qc, auto kc) {
+            hipLaunchKernelGGL((k_step_graph<S, decltype(qc)::value, decltype(kc)::value>), grid, dim3(kStepBlock), 0, s, p);
+            return hipGetLastError();
+        });
+    }
+    return step_by_lattice<S>(p.q, kind, [&](auto qc, auto kc) {
+        constexpr int Q = decltype(qc)::value, KIND = decltype(kc)::value;
+        if (pull) hipLaunchKernelGGL((k_step<S, Q, KIND, true>), grid, dim3(kStepBlock), 0, s, p);
+        else hipLaunchKernelGGL((k_step<S, Q, KIND, false>), grid, dim3(kStepBlock), 0, s, p);
         return hipGetLastError();
-    }
-#define LBW_LAUNCH(QQ, KK, PP) \
-    hipLaunchKernelGGL((k_step<S, QQ, KK, PP>), grid, dim3(kStepBlock), 0, s, p)
-    if (p.q == 5) {
-        if (kind == 0) { if (pull) LBW_LAUNCH(5, 0, true); else LBW_LAUNCH(5, 0, false); }
-        else if (kind == 2) { if (pull) LBW_LAUNCH(5, 2, true); else LBW_LAUNCH(5, 2, false); }
-        else { if (pull) LBW_LAUNCH(5, 1, true); else LBW_LAUNCH(5, 1, false); }
-    } else {
-        if (kind == 0) { if (pull) LBW_LAUNCH(9, 0, true); else LBW_LAUNCH(9, 0, false); }
-        else if (kind == 2) { if (pull) LBW_LAUNCH(9, 2, true); else LBW_LAUNCH(9, 2, false); }
-        else { if (pull) LBW_LAUNCH(9, 1, true); else LBW_LAUNCH(9, 1, false); }
-    }
-#undef LBW_LAUNCH
-    return hipGetLastError();
+    });
 }
 
 }  // namespace
@@ -894,29 +892,21 @@ hipError_t launch_field(int storage, const FieldParams &p, hipStream_t s) {
 }
 
 #define LBW_IFACE_KIND(KERNEL, SS)                                                                 \
-    do {                                                                                           \
-        if (kind == 1) hipLaunchKernelGGL((KERNEL<SS, 1>), grid, dim3(kBlock), 0, s, p);           \
-        else if (kind == 2) hipLaunchKernelGGL((KERNEL<SS, 2>), grid, dim3(kBlock), 0, s, p);      \
-        else hipLaunchKernelGGL((KERNEL<SS, 0>), grid, dim3(kBlock), 0, s, p);                     \
-    } while (0)
-#define LBW_IFACE(KERNEL, N)                                                                       \
-    dim3 grid(blocks_for(N));                                                                      \
-    const int kind = step_kind(p.coll);                                                            \
+    return for_kind<SS, 5>(step_kind(p.coll), [&](auto kc) {                                       \
+        hipLaunchKernelGGL((KERNEL<SS, decltype(kc)::value>), grid, dim3(kBlock), 0, s, p);        \
+        return hipGetLastError();                                                                  \
+    })
+#define LBW_IFACE(KERNEL, GRID)                                                                    \
+    const dim3 grid(GRID);                                                                         \
     if (storage == ST_F32) LBW_IFACE_KIND(KERNEL, float);                                          \
-    else if (storage == ST_F64) LBW_IFACE_KIND(KERNEL, double);                                    \
-    else LBW_IFACE_KIND(KERNEL, _Float16);                                                         \
-    return hipGetLastError();
+    if (storage == ST_F64) LBW_IFACE_KIND(KERNEL, double);                                         \
+    LBW_IFACE_KIND(KERNEL, _Float16);
 
-hipError_t launch_prolong(int storage, const InterfaceParams &p, hipStream_t s) { LBW_IFACE(k_prolong, p.g.nring) }
+hipError_t launch_prolong(int storage, const InterfaceParams &p, hipStream_t s) { LBW_IFACE(k_prolong, blocks_for(p.g.nring)) }
 
 hipError_t launch_prolong_pair(int storage, const InterfaceParams &p, hipStream_t s) {
-    dim3 grid((unsigned)ring_tile_blocks<kBlock>(p.g));   // one side's nodes per block
-    const int kind = step_kind(p.coll);
-    if (storage == ST_F32) LBW_IFACE_KIND(k_prolong_pair, float);
-    else if (storage == ST_F64) LBW_IFACE_KIND(k_prolong_pair, double);
-    else LBW_IFACE_KIND(k_prolong_pair, _Float16);
-    return hipGetLastError();
+    LBW_IFACE(k_prolong_pair, (unsigned)ring_tile_blocks<kBlock>(p.g))   // one side's nodes per block
 }
-hipError_t launch_restrict(int storage, const InterfaceParams &p, hipStream_t s) { LBW_IFACE(k_restrict, p.g.ninner) }
+hipError_t launch_restrict(int storage, const InterfaceParams &p, hipStream_t s) { LBW_IFACE(k_restrict, blocks_for(p.g.ninner)) }
 
 }  // namespace lbw

@@ -66,3 +66,28 @@ def test_sum_rho_of_many_steps(n, precision):
     rho = a["fields"]["rho"].astype(np.float64)
     # rounding of an FP64 sum of n terms: at most n eps times the sum of their sizes
     assert abs(a["sum_rho"][-1] - rho.sum()) <= rho.size * 2.0 ** -53 * np.abs(rho).sum()
+
+
+@pytest.mark.parametrize("n", [131, 1300])
+@pytest.mark.parametrize("collision,tau,s", [("bgk", 0.5, None), ("bgk", 0.8, None), ("mrt", 0.5, MRT5)])
+def test_two_forms_of_the_collision(n, collision, tau, s):
+    """An FP32 grid that records for a gradient writes each mover's
+    equilibrium out, others use the sums of opposite movers: both are the FP64
+    run to rounding, at one step per launch and at many (the same bits)."""
+    from paper_1704_03172_amd import lbwave
+    c = case(n, 617, 5, collision, tau, s, 25)
+    got = {}
+    for precision, tape, launch in [("f64", 0, 0), ("f32", 0, 1), ("f32", 0, 0), ("f32", 1, 1), ("f32", 1, 0)]:
+        g = lbwave.Grid(n, 617, collision=collision, precision=precision, tau=tau, s=s, sponge_width=9, sponge_sigma_max=0.1,
+                        trace_capacity=26, max_receivers=len(c["receivers"]), rho_tape=tape, steps_per_launch=launch)
+        g.set_medium(c["c2"])
+        g.set_state(c["rho0"], c["jx0"], c["jy0"])
+        g.set_source(c["source"][0], c["source"][1], c["wavelet"])
+        g.record(c["receivers"])
+        g.step(25)
+        got[precision, tape, launch] = np.stack([g.field(f).cpu().numpy().astype(np.float64) for f in FIELDS])
+    exact = got["f64", 0, 0]
+    for tape in (0, 1):
+        np.testing.assert_array_equal(got["f32", tape, 1], got["f32", tape, 0])
+        # a step rounds a population at most 8 times, a field sums 5 of them
+        assert np.abs(got["f32", tape, 0] - exact).max() <= 25 * 8 * 5 * 2.0 ** -24 * np.abs(exact).max()
