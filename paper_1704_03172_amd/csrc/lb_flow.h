@@ -134,6 +134,30 @@ __device__ inline double lane_of(double v, int k) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// Block k's share of the strips' bundles of rows starts at share_start(k) and
+// ends at share_start(k + 1): equal weights, where a bundle of the strips that
+// lie in the sponge of a side edge counts more (kFlowSponge against
+// kFlowPlain).  nbs: bundles of a strip.
+__device__ inline int share_start(KernFlow p, int nbs, int k) {
+    const int64_t wl = (int64_t)p->nl * nbs, wm = (int64_t)(p->nstrip - p->nl - p->nr) * nbs, wr = (int64_t)p->nr * nbs;
+    const int64_t all = (wl + wr) * kFlowSponge + wm * kFlowPlain, t = all * k / p->nblk;
+    if (t < wl * kFlowSponge) return (int)(t / kFlowSponge);
+    if (t < wl * kFlowSponge + wm * kFlowPlain) return (int)(wl + (t - wl * kFlowSponge) / kFlowPlain);
+    return (int)(wl + wm + (t - wl * kFlowSponge - wm * kFlowPlain) / kFlowSponge);
+}
+
+// Bundles that carry the share [b0, b1): each run of rows within a strip has
+// 2 ns more rows at its head.
+__device__ inline int share_bundles(int R, int ny, int ns, int nbs, int b0, int b1) {
+    int total = 0;
+    for (int b = b0; b < b1;) {
+        const int j0 = b % nbs, j1 = min(nbs, j0 + (b1 - b));
+        total += (min(j1 * R, ny) - j0 * R + 2 * ns + R - 1) / R;
+        b += j1 - j0;
+    }
+    return total;
+}
+
 // Sum over the lanes, in lane 63: DPP row rotations by 8, 4, 2, 1 (every lane
 // of a row of 16 then holds that row's sum), then row_bcast:15 into rows 1 and
 // 3 and row_bcast:31 into rows 2 and 3.
@@ -190,26 +214,9 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
         coll.ratio = uniform(T(p->coll.ratio));
     }
 
-    // this block's share of the strips' bundles of rows, [b0, b1): equal
-    // weights, where a bundle of the strips that lie in the sponge of a side
-    // edge counts more (kFlowSponge against kFlowPlain)
     const int nbs = (ny + R - 1) / R;
-    auto at = [&](int k) {
-        const int64_t wl = (int64_t)p->nl * nbs, wm = (int64_t)(p->nstrip - p->nl - p->nr) * nbs, wr = (int64_t)p->nr * nbs;
-        const int64_t all = (wl + wr) * kFlowSponge + wm * kFlowPlain, t = all * k / p->nblk;
-        if (t < wl * kFlowSponge) return (int)(t / kFlowSponge);
-        if (t < wl * kFlowSponge + wm * kFlowPlain) return (int)(wl + (t - wl * kFlowSponge) / kFlowPlain);
-        return (int)(wl + wm + (t - wl * kFlowSponge - wm * kFlowPlain) / kFlowSponge);
-    };
-    const int b0 = at(blk), b1 = at(blk + 1);
-    // bundles of the block: each run of rows within a strip has 2 ns more rows
-    // at its head
-    int total = 0;
-    for (int b = b0; b < b1;) {
-        const int j0 = b % nbs, j1 = min(nbs, j0 + (b1 - b));
-        total += (min(j1 * R, ny) - j0 * R + 2 * ns + R - 1) / R;
-        b += j1 - j0;
-    }
+    const int b0 = share_start(p, nbs, blk), b1 = share_start(p, nbs, blk + 1);
+    const int total = share_bundles(R, ny, ns, nbs, b0, b1);
     const int mlast = (R + ns - 1) / R;   // bundles q .. q + mlast read the c^2 rows of bundle q
     int b = b0, base = 0, it = 0, ring = w * R;
     for (int q = w; q < total; q += W, ++it) {

@@ -1,7 +1,8 @@
-// lb_flow.hip -- host side of the flowing kernel (lb_flow.h; instantiated per
-// storage format and lattice in lb_flow_*.hip): shapes, geometry, argument
+// lb_flow.hip -- host side of the flowing kernels (lb_flow.h, instantiated per
+// storage format and lattice in lb_flow_{f32,f64,f16}_*.hip, and backwards
+// lb_flow_adjoint.h, lb_flow_adjoint_*.hip): shapes, geometry, argument
 // checks and dispatch, and the batched executor's per-shot params and advance.
-#include "lb_flow.h"
+#include "lb_flow_adjoint.h"
 
 #include <algorithm>
 
@@ -51,6 +52,14 @@ hipError_t dispatch(int storage, int q, bool small, const FlowParams &p, const F
     return q == 5 ? launch_flow_f16_q5(small, p, fb, nblk, kind, s) : launch_flow_f16_q9(small, p, fb, nblk, kind, s);
 }
 
+// What the kernels take for granted: halos of whole lanes, wide enough, and
+// every column and bundle in some strip and block.
+bool flow_fits(const FlowInfo &f, const FlowParams &p) {
+    return p.nx >= 1 && p.ny >= 1 && p.nrun >= 1 && p.nrun <= f.steps && p.hx >= p.nrun && p.hx % f.V == 0 &&
+           2 * p.hx < 64 * f.V && p.nblk >= 1 && p.nl >= 0 && p.nr >= 0 && p.nl + p.nr <= p.nstrip &&
+           (int64_t)p.nstrip * (64 * f.V - 2 * p.hx) >= p.nx;
+}
+
 }  // namespace
 
 FlowInfo flow_info(int storage, int q, bool small) {
@@ -93,14 +102,34 @@ void flow_geometry(const FlowInfo &f, int steps, int blocks, FlowParams &p) {
 }
 
 hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipStream_t s) {
-    if ((q != 5 && q != 9) || p.nx < 1 || p.ny < 1) return hipErrorInvalidValue;
-    const FlowInfo f = flow_info(storage, q, small);
-    // what the kernel takes for granted: halos of whole lanes, wide enough,
-    // and every column and bundle in some strip and block
-    if (p.nrun < 1 || p.nrun > f.steps || p.hx < p.nrun || p.hx % f.V != 0 || 2 * p.hx >= 64 * f.V || p.nblk < 1 ||
-        p.nl < 0 || p.nr < 0 || p.nl + p.nr > p.nstrip || (int64_t)p.nstrip * (64 * f.V - 2 * p.hx) < p.nx)
-        return hipErrorInvalidValue;
+    if ((q != 5 && q != 9) || !flow_fits(flow_info(storage, q, small), p)) return hipErrorInvalidValue;
     return dispatch(storage, q, small, p, FlowBatch(), p.nblk, p.coll, s);
+}
+
+FlowInfo flow_adjoint_info(int storage, int q, bool small) {
+    if (storage == ST_F64) return q == 5 ? flow_adjoint_info_f64_q5(small) : flow_adjoint_info_f64_q9(small);
+    return q == 5 ? flow_adjoint_info_f32_q5(small) : flow_adjoint_info_f32_q9(small);
+}
+
+// Measured as above, with a tape (us per backward step at 8 / 16 steps per
+// launch, the best shape): FP32 D2Q5 128^2 4.39 / 4.24, 256^2 3.44 / 3.16,
+// 512^2 3.27 / 3.73, 1024^2 5.43 / 6.78 (small shape; the wide one 7.07 / 6.72),
+// 2048^2 13.3 / 12.4; FP64 D2Q5 256^2 3.73 / 3.43, 1024^2 7.00 / 7.69, 2048^2
+// 23.7 / 22.7; FP32 D2Q9 (8 / 12 steps) 1024^2 8.38 / 10.8, 2048^2 23.7 / 27.2;
+// FP64 D2Q9 (6 / 8) 1024^2 12.2 / 12.1, 2048^2 42.4 / 36.3.
+FlowChoice flow_adjoint_choose(int storage, int q, int64_t nodes) {
+    FlowChoice c;
+    c.small = storage != ST_F64 && nodes < 2000000;
+    c.steps = q == 5 && (nodes <= 100000 || nodes >= 2000000) ? 16 : 8;
+    return c;
+}
+
+hipError_t launch_flow_adjoint(int storage, int q, bool small, const AdjointFlowParams &p, hipStream_t s) {
+    if ((q != 5 && q != 9) || p.f.nrun < 2 || p.f.rec.col < p.f.nrun - 1 || p.rho_back <= 0 ||
+        p.f.nx < 2 || !flow_fits(flow_adjoint_info(storage, q, small), p.f))
+        return hipErrorInvalidValue;
+    if (storage == ST_F64) return q == 5 ? launch_flow_adjoint_f64_q5(small, p, s) : launch_flow_adjoint_f64_q9(small, p, s);
+    return q == 5 ? launch_flow_adjoint_f32_q5(small, p, s) : launch_flow_adjoint_f32_q9(small, p, s);
 }
 
 hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const FlowInfo &f, hipStream_t s) {

@@ -251,12 +251,20 @@ struct AdjointParams {
     Receivers rec;                     // tables + residual array in `traces`
     int32_t terminal = 0;              // 1: n = N (no step, lambda(N+1) = 0)
     int32_t initial = 0;               // 1: n = 0, add the initial-state term
-    // launch_adjointn (steps n = rec.col, n - 1, .., n - ns + 1): the rho of
-    // time n - k at rho - k * rho_back elements, S(n - k) in s_back[k], and
-    // the stage (k + 1) whose time is 0 (0: none)
-    int64_t rho_back = 0;
-    double s_back[4] = {0, 0, 0, 0};
-    int32_t initial_stage = 0;
+};
+
+// One launch of the backward flowing kernel (lb_flow_adjoint.hip): the nrun
+// backward steps of times n, n - 1, .., n - nrun + 1, none of them the
+// terminal one.  f: src lambda(n + 1), dst lambda(n - nrun + 1), s[k] = S(n - k),
+// rec the receivers with the residuals as traces and col = n; rho_out,
+// rho_stride, sum, sum_stride and gtab are not used.
+struct AdjointFlowParams {
+    FlowParams f;
+    const void *rho = nullptr;         // forward pre-collision rho(n) [ny][nx]; that of time
+    int64_t rho_back = 0;              // n - k at rho - k * rho_back elements
+    double *grad = nullptr;            // [ny][nx]
+    double dw[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    int32_t initial_stage = 0;         // k + 1 where time n - k is 0 (0: none)
 };
 
 // Field extraction: one field of the state at the current time.
@@ -306,12 +314,11 @@ struct BatchParams {
 
 // Launchers (lb_kernels.hip).  All return the launch status.
 hipError_t launch_adjoint(int storage, const AdjointParams &p, hipStream_t s);
-// ns backward steps (n = p.rec.col down to n - ns + 1, ns - 1 <= n < N) in
-// one launch: lambda(n+1) from p.lam_next, lambda(n-ns+1) to p.lam, rho and
-// S of each time as in AdjointParams; the gradient gets the terms of n, then
-// of n - 1, ... (the order of one-step launches).  2 <= ns <= adjointn_max.
-hipError_t launch_adjointn(int storage, const AdjointParams &p, int ns, hipStream_t s);
-int adjointn_max(int storage, int q);
+// The shape and the steps per launch of the backward flowing kernel; its
+// launch: 2 <= f.nrun <= flow_adjoint_info().steps.
+FlowInfo flow_adjoint_info(int storage, int q, bool small);
+FlowChoice flow_adjoint_choose(int storage, int q, int64_t nodes);
+hipError_t launch_flow_adjoint(int storage, int q, bool small, const AdjointFlowParams &p, hipStream_t s);
 // Trace misfit: res = traces - obs over columns 0 .. ncols-1 of nrec rows of
 // cap columns, and phi = 1/2 sum res^2 (FP64) through misfit_blocks(nrec,
 // ncols) block partials in `partial` (at most kMisfitMaxBlocks doubles), then

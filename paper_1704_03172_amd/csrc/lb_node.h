@@ -425,34 +425,17 @@ __device__ inline void post_node(const StepParams &p, const T (&g)[Q], T c2, int
     for (int i = 0; i < Q; ++i) out[i] = gs[i];
 }
 
-// One node of the backward step of time n (the discrete adjoint; see
-// k_adjoint): mu is lambda(n+1) pulled back to the node (before the sponge),
-// dedge the node's distance to the nearest edge, [rb, re) its row's
-// receiver entries (empty: none), col = n for the residuals, s_n = S(n),
-// initial: n = 0.  Writes lambda(n) and returns the node's gradient term of
-// time n (FP64).  Shared by the one-step and the two-step adjoint kernels,
-// so both give the same bits.
-template <typename T, int Q, int KIND>
-__device__ inline double adjoint_node(const AdjointParams &p, const T (&mu)[Q], T c2, T rho, int x, int y, int dedge,
-                                      int rb, int re, int64_t col, double s_n, bool initial, T (&lam)[Q],
-                                      bool sponge = true) {
-    const T *res = reinterpret_cast<const T *>(p.rec.traces);
-    T m[Q], nu[Q], w[Q];
-    // (1 - sigma) P^T lambda: outside the sponge the factor is 1 and
-    // mu * 1 = mu, so only nodes inside it multiply (sponge false: the
-    // caller has applied the factor to mu already)
-    if (sponge && dedge < p.sponge_width) {
-        asm volatile("");
-        const T sf = sponge_at<T>(dedge, p.sponge_width, p.sponge_smax);
+// The backward step of a node at time n (the discrete adjoint; see k_adjoint),
+// shared by the one-step and the many-step kernel, so that both give the same
+// bits: mu = lambda(n+1) pulled back to the node, m = (1 - sigma) mu, nu = C^T m
+// (C is symmetric), then lambda(n) without the residuals.  Kinds as in
+// collide(); the form of kind 2 has the values of kind 0 (products by 2 are
+// exact).
+template <typename T, int Q, int KIND, typename C>
+__device__ inline void adjoint_relax(const T (&m)[Q], const C &coll, T (&nu)[Q]) {
+    if constexpr (KIND != 1) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) m[i] = mu[i] * sf;
-    } else {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) m[i] = mu[i];
-    }
-    if (KIND == 0) {
-#pragma unroll
-        for (int i = 0; i < Q; ++i) nu[i] = T(p.coll.omega) * m[i];
+        for (int i = 0; i < Q; ++i) nu[i] = KIND == 2 ? T(2) * m[i] : T(coll.omega) * m[i];
     } else {
         T r[9];
 #pragma unroll
@@ -463,7 +446,7 @@ __device__ inline double adjoint_node(const AdjointParams &p, const T (&mu)[Q], 
                 const int c = mrow<Q>(k, i);
                 if (c != 0) a += T(c) * m[i];
             }
-            r[k] = T(p.coll.srate[k]) * a;
+            r[k] = T(coll.srate[k]) * a;
         }
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
@@ -476,34 +459,87 @@ __device__ inline double adjoint_node(const AdjointParams &p, const T (&mu)[Q], 
             nu[i] = a;
         }
     }
-    double gacc = 0.0;
-    {
-        double dn = 0.0, dm = 0.0;
+}
+
+template <typename T, int Q, int KIND, typename C>
+__device__ inline void adjoint_lambda(const T (&m)[Q], const T (&nu)[Q], T c2, const C &coll, T (&lam)[Q]) {
+    T s0, sx = T(0), sy = T(0);
+    if constexpr (Q == 5 && KIND == 2) {
+        s0 = fmaT(T(-4), c2, T(2)) * m[0];
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            dn += p.dw[i] * double(nu[i]);
-            dm += p.dw[i] * double(m[i]);
+        for (int i = 1; i < Q; ++i) s0 += c2 * m[i];
+        sx = m[1] - m[3];
+        sy = m[2] - m[4];
+        lam[0] = s0 - m[0];
+#pragma unroll
+        for (int i = 1; i < Q; ++i) lam[i] = (s0 - m[i]) + cdot<T>(cxv<Q>(i), cyv<Q>(i), sx, sy);
+        return;
+    }
+    T w[Q];
+    weights<T, Q>(c2, coll, w);
+    s0 = w[0] * nu[0];
+    bool hx = false, hy = false;
+#pragma unroll
+    for (int i = 1; i < Q; ++i) {
+        s0 += w[i] * nu[i];
+        const T kn = (Q == 5 ? T(0.5) : (i <= 4 ? T(coll.kax) : T(coll.kdg))) * nu[i];
+        if (cxv<Q>(i) != 0) {
+            const T v = cxv<Q>(i) > 0 ? kn : -kn;
+            sx = hx ? sx + v : v;
+            hx = true;
         }
-        gacc += double(rho) * dn;
-        if (y == p.src_y) {   // uniform over a row: only the source row tests x
-            asm volatile("");
-            if (x == p.src_x) gacc += s_n * dm;
+        if (cyv<Q>(i) != 0) {
+            const T v = cyv<Q>(i) > 0 ? kn : -kn;
+            sy = hy ? sy + v : v;
+            hy = true;
         }
     }
-    weights<T, Q>(c2, p.coll, w);
-    T s0 = T(0), sxv = T(0), syv = T(0);
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-        s0 += w[i] * nu[i];
-        const T kj = Q == 5 ? T(0.5) : (i <= 4 ? T(p.coll.kax) : T(p.coll.kdg));
-        if (i > 0) {
-            sxv += kj * T(cxv<Q>(i)) * nu[i];
-            syv += kj * T(cyv<Q>(i)) * nu[i];
-        }
+        T l = m[i] - nu[i] + s0;
+        if (cxv<Q>(i) != 0) l += cxv<Q>(i) > 0 ? sx : -sx;
+        if (cyv<Q>(i) != 0) l += cyv<Q>(i) > 0 ? sy : -sy;
+        lam[i] = l;
     }
+}
+
+// dw . v in FP64, the derivatives dw of the weights by c^2 being alike for the
+// axis and for the diagonal movers.
+template <typename T, int Q, typename P>
+__device__ inline double dw_dot(const P &dw, const T (&v)[Q]) {
+    double d = fmaT(double(dw[1]), (double(v[1]) + double(v[3])) + (double(v[2]) + double(v[4])), double(dw[0]) * double(v[0]));
+    if constexpr (Q == 9)
+        d = fmaT(double(dw[5]), (double(v[5]) + double(v[7])) + (double(v[6]) + double(v[8])), d);
+    return d;
+}
+
+// One node of the one-step kernel: dedge is the node's distance to the nearest
+// edge, [rb, re) its row's receiver entries (empty: none), col = n for the
+// residuals, s_n = S(n), initial: n = 0.  Writes lambda(n) and returns the
+// node's gradient term of time n (FP64).
+template <typename T, int Q, int KIND>
+__device__ inline double adjoint_node(const AdjointParams &p, const T (&mu)[Q], T c2, T rho, int x, int y, int dedge,
+                                      int rb, int re, int64_t col, double s_n, bool initial, T (&lam)[Q]) {
+    const T *res = reinterpret_cast<const T *>(p.rec.traces);
+    T m[Q], nu[Q];
+    // (1 - sigma) P^T lambda: outside the sponge the factor is 1 and
+    // mu * 1 = mu, so only nodes inside it multiply
+    if (dedge < p.sponge_width) {
+        asm volatile("");
+        const T sf = sponge_at<T>(dedge, p.sponge_width, p.sponge_smax);
 #pragma unroll
-    for (int i = 0; i < Q; ++i)
-        lam[i] = m[i] - nu[i] + s0 + T(cxv<Q>(i)) * sxv + T(cyv<Q>(i)) * syv;
+        for (int i = 0; i < Q; ++i) m[i] = mu[i] * sf;
+    } else {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) m[i] = mu[i];
+    }
+    adjoint_relax<T, Q, KIND>(m, p.coll, nu);
+    double gacc = double(rho) * dw_dot<T, Q>(p.dw, nu);
+    if (y == p.src_y) {   // uniform over a row: only the source row tests x
+        asm volatile("");
+        if (x == p.src_x) gacc += s_n * dw_dot<T, Q>(p.dw, m);
+    }
+    adjoint_lambda<T, Q, KIND>(m, nu, c2, p.coll, lam);
     if (rb < re) {
         int lo = rb, hi = re;
         while (lo < hi) {
@@ -517,12 +553,7 @@ __device__ inline double adjoint_node(const AdjointParams &p, const T (&mu)[Q], 
             gacc += double(rr) * double(rho);
         }
     }
-    if (initial) {
-        double dl = 0.0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) dl += p.dw[i] * double(lam[i]);
-        gacc += double(rho) * dl;
-    }
+    if (initial) gacc += double(rho) * dw_dot<T, Q>(p.dw, lam);
     return gacc;
 }
 

@@ -133,6 +133,33 @@ __device__ inline void pull_row2(const T (&U)[Q][V], const T (&C)[Q][V], const T
     }
 }
 
+// mu_i(x) = lambda_i(n+1)(x + c_i): the transpose of the pull, from the row
+// below for c_y = +1 (D), above for c_y = -1 (U), and the lane to the right
+// (x + 1) or left (x - 1) along x.
+template <typename T, int Q, int V>
+__device__ inline void pull_back_row(const T (&U)[Q][V], const T (&C)[Q][V], const T (&D)[Q][V], T (&g)[Q][V]) {
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        T r[V];
+#pragma unroll
+        for (int j = 0; j < V; ++j) r[j] = cyv<Q>(i) > 0 ? D[i][j] : cyv<Q>(i) < 0 ? U[i][j] : C[i][j];
+        if (cxv<Q>(i) > 0) {          // from x + 1
+            const T rr = from_upper(r[0]);
+#pragma unroll
+            for (int j = 0; j < V - 1; ++j) g[i][j] = r[j + 1];
+            g[i][V - 1] = rr;
+        } else if (cxv<Q>(i) < 0) {   // from x - 1
+            const T l = from_lower(r[V - 1]);
+#pragma unroll
+            for (int j = V - 1; j > 0; --j) g[i][j] = r[j - 1];
+            g[i][0] = l;
+        } else {
+#pragma unroll
+            for (int j = 0; j < V; ++j) g[i][j] = r[j];
+        }
+    }
+}
+
 // Blocks are dealt to the 8 XCDs round-robin (block b on XCD b mod 8);
 // renumbered, each XCD takes a contiguous range of strips and segments, whose
 // shared halo rows then meet in that XCD's L2.
@@ -151,16 +178,6 @@ __device__ inline void static_for_impl(F &&f, std::integer_sequence<int, I...>) 
 template <int B, int E, typename F>
 __device__ inline void static_for(F &&f) {
     static_for_impl<B>(f, std::make_integer_sequence<int, E - B>{});
-}
-
-// One of four arrays chosen at compile time (separate arrays per stage stay
-// in registers; one array of all stages would be too large to promote).
-template <int I, typename A>
-__device__ inline A &pick4(A &a0, A &a1, A &a2, A &a3) {
-    if constexpr (I == 0) return a0;
-    else if constexpr (I == 1) return a1;
-    else if constexpr (I == 2) return a2;
-    else return a3;
 }
 
 }  // namespace

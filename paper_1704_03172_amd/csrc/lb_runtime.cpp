@@ -1178,31 +1178,52 @@ int lb_trace_misfit(const void *d_traces, const void *d_obs, void *d_res, int32_
 }
 
 // Backward steps n = b, b - 1, .., a of the adjoint, the forward rho of time
-// n at rho_base + (n - a) fields; up to adjointn_max steps per launch (capped
-// as the forward launches are, so steps_per_launch = 1 gives one step per
-// launch) where they lie in [a, b] and not at the terminal time nt.
-// cur_lam: the lambda buffer holding lambda(b + 1), updated.
+// n at rho_base + (n - a) fields; many steps per launch (capped as the forward
+// launches are, so steps_per_launch = 1 gives one step per launch) where they
+// lie in [a, b] and not at the terminal time nt.  cur_lam: the lambda buffer
+// holding lambda(b + 1), updated.
 int adjoint_backward(lb_grid *h, lbw::AdjointParams &ap, char *rho_base, int64_t a, int64_t b, int64_t nt,
                      int &cur_lam) {
     const int64_t n_nodes = (int64_t)h->main.nx * h->main.ny;
     const size_t field = (size_t)n_nodes * h->tsize;
-    const int nmax = std::min(lbw::adjointn_max(h->storage, h->q),
-                              h->d.steps_per_launch > 0 ? h->d.steps_per_launch : lbw::kFlowSteps);
+    const lbw::FlowChoice fc = lbw::flow_adjoint_choose(h->storage, h->q, n_nodes);
+    const int nmax = h->d.steps_per_launch > 0 ? std::min(h->d.steps_per_launch, (int)fc.steps) : (int)fc.steps;
     for (int64_t n = b; n >= a;) {
-        ap.rho = rho_base + (size_t)(n - a) * field;
-        ap.terminal = n == nt;
-        ap.initial = n == 0;
-        ap.lam_next = h->lam[cur_lam];
-        ap.lam = h->lam[1 - cur_lam];
-        ap.s_n = source_at(h, n);
-        ap.rec.col = n;
-        const int ns = n == nt ? 1 : (int)std::min<int64_t>(nmax, n - a + 1);
+        const int ns = n == nt || h->main.nx < 2 ? 1 : even_steps(n - a + 1, nmax);
+        const void *lam_next = h->lam[cur_lam], *rho = rho_base + (size_t)(n - a) * field;
+        void *lam = h->lam[1 - cur_lam];
         if (ns >= 2) {
-            ap.rho_back = n_nodes;
-            for (int k = 0; k < 4; ++k) ap.s_back[k] = k < ns ? source_at(h, n - k) : 0.0;
-            ap.initial_stage = n < ns ? (int32_t)n + 1 : 0;   // the stage of time 0
-            LB_TRY(h, lbw::launch_adjointn(h->storage, ap, ns, h->stream));
+            lbw::AdjointFlowParams p;
+            p.f.src = lam_next;
+            p.f.dst = lam;
+            p.f.c2 = ap.c2;
+            p.f.nx = ap.nx;
+            p.f.ny = ap.ny;
+            p.f.pstride = ap.pstride;
+            p.f.nrun = ns;
+            p.f.sponge_width = ap.sponge_width;
+            p.f.sponge_smax = ap.sponge_smax;
+            p.f.src_x = ap.src_x;
+            p.f.src_y = ap.src_y;
+            p.f.coll = ap.coll;
+            p.f.rec = ap.rec;
+            p.f.rec.col = n;
+            for (int k = 0; k < ns; ++k) p.f.s[k] = source_at(h, n - k);
+            lbw::flow_geometry(lbw::flow_adjoint_info(h->storage, h->q, fc.small), ns, lbw::kFlowBlocks, p.f);
+            p.rho = rho;
+            p.rho_back = n_nodes;
+            p.grad = ap.grad;
+            for (int k = 0; k < 9; ++k) p.dw[k] = ap.dw[k];
+            p.initial_stage = n < ns ? (int32_t)n + 1 : 0;   // the step of time 0
+            LB_TRY(h, lbw::launch_flow_adjoint(h->storage, h->q, fc.small, p, h->stream));
         } else {
+            ap.rho = rho;
+            ap.terminal = n == nt;
+            ap.initial = n == 0;
+            ap.lam_next = lam_next;
+            ap.lam = lam;
+            ap.s_n = source_at(h, n);
+            ap.rec.col = n;
             LB_TRY(h, lbw::launch_adjoint(h->storage, ap, h->stream));
         }
         n -= ns;

@@ -91,3 +91,35 @@ def test_two_forms_of_the_collision(n, collision, tau, s):
         np.testing.assert_array_equal(got["f32", tape, 1], got["f32", tape, 0])
         # a step rounds a population at most 8 times, a field sums 5 of them
         assert np.abs(got["f32", tape, 0] - exact).max() <= 25 * 8 * 5 * 2.0 ** -24 * np.abs(exact).max()
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64", "f16s"])
+@pytest.mark.parametrize("q,collision,tau,s", [(5, "bgk", 0.5, None), (5, "bgk", 0.8, None), (5, "mrt", 0.5, MRT5),
+                                               (9, "bgk", 0.5, None), (9, "mrt", 0.5, MRT9)])
+def test_backward_steps_of_a_launch(precision, q, collision, tau, s):
+    """The gradient of many backward steps per launch has the bits of one step
+    per launch: both shapes, ragged sides (an odd width, so that the last
+    stored column shares a lane with the seam), receivers in dense rows and
+    twice on a node, from a tape and from checkpoints."""
+    import torch
+    from paper_1704_03172_amd import lbwave
+    for nx, ny, nt in [(131, 217, 41), (1453, 1391, 23)]:
+        c = case(nx, ny, q, collision, tau, s, nt)
+        rec = np.concatenate([c["receivers"], c["receivers"][:5], [(nx - 1, ny - 1), (0, ny // 2)]]).astype(np.int32)
+        got = []
+        for launch, extra in [(1, {"rho_tape": 1}), (0, {"rho_tape": 1}), (0, {"ckpt_every": 9, "ckpt_capacity": 6})]:
+            g = lbwave.Grid(nx, ny, lattice=q, collision=collision, precision=precision, tau=tau, s=s, sponge_width=9,
+                            sponge_sigma_max=0.1, trace_capacity=nt + 1, max_receivers=len(rec), steps_per_launch=launch,
+                            **extra)
+            g.set_medium(c["c2"])
+            g.set_state(c["rho0"], c["jx0"], c["jy0"])
+            g.set_source(c["source"][0], c["source"][1], c["wavelet"])
+            g.record(rec)
+            g.step(nt)
+            gen = torch.Generator(device="cuda").manual_seed(nx)
+            res = torch.randn((len(rec), nt + 1), generator=gen, device="cuda",
+                              dtype=torch.float64 if precision == "f64" else torch.float32)
+            got.append(g.adjoint(res, nt).cpu().numpy())
+        assert np.isfinite(got[0]).all() and np.abs(got[0]).max() > 0
+        np.testing.assert_array_equal(got[0], got[1])
+        np.testing.assert_array_equal(got[0], got[2])
