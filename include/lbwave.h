@@ -109,8 +109,9 @@ typedef struct lb_grid lb_grid;
  *   ckpt_capacity  checkpoint slots; a run of N steps needs N / K + 1.
  *   steps_per_launch  0 (default): lb_step_n advances several time steps
  *                  per kernel launch (temporal blocking), up to 16, wherever
- *                  it can (no patch, no checkpoint falling inside a launch;
- *                  the last launch of each call takes one step), which
+ *                  it can (no checkpoint falling inside a launch; the last
+ *                  launch of each call takes one step; with a patch the
+ *                  coarse grid away from it, up to 8), which
  *                  divides the HBM traffic per step accordingly; the results
  *                  equal those of one step per launch bit for bit.  The
  *                  count depends on the grid: 16 for D2Q5 on large grids

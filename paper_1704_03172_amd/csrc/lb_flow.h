@@ -39,6 +39,7 @@
 // (13.5), 1024^2 3.2 (6.5), 256^2 1.8 (5.9).
 #pragma once
 
+#include "lb_iface.h"
 #include "lb_internal.h"
 #include "lb_rows.h"
 
@@ -95,6 +96,7 @@ constexpr bool flow_steps_ok(int ns, int R, int W, int E) {
 }
 
 typedef const __attribute__((address_space(4))) FlowParams *KernFlow;
+typedef const __attribute__((address_space(4))) FlowPatchParams *KernPatch;
 typedef const __attribute__((address_space(4))) int32_t *ConstInt;
 
 // A pointer whose value the compiler cannot follow: fields read through it are
@@ -177,20 +179,24 @@ __device__ inline double wave_total(double a) {
     return dpp_add<0x143, 0xC>(a);
 }
 
-// OUT: the launch writes rho or its sums (a kernel of its own: the code costs
-// the others scalar registers, 2 % of a 4096^2 shot).
-template <typename S, int Q, int KIND, int V, int R, int W, int E, bool OUT>
+// MODE 1: the launch writes rho or its sums; 2: the fine steps of a patch (p is
+// the f of a FlowPatchParams).  Kernels of their own: the code costs the
+// others scalar registers, 2 % of a 4096^2 shot.
+template <typename S, int Q, int KIND, int V, int R, int W, int E, int MODE>
 __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int blk) {
     using T = typename Tr<S>::T;
     typedef typename LaneVec<V, T>::type ct;
     typedef typename LaneVec<V, S>::type vt;
     constexpr int RING = (W + E) * R;   // rows of the c^2 ring
     static_assert(R >= 3 && R <= 16 && V * 64 <= 256, "row masks and the receiver table");
+    constexpr bool OUT = MODE == 1, PATCH = MODE == 2;
+    static_assert(!PATCH || (V == 1 && Q == 5), "one ring node per lane and row");
     __shared__ ct c2s[(RING + R) * 64];           // c^2 of the bundles' rows (the first R repeated at the end)
     __shared__ ct edge[2][W][Q][64];              // last two rows of each wave's bundle, one step back
     __shared__ uint32_t rtab[W][64 * V];              // receivers of each wave's bundle
     __shared__ T sfys[RING + R];                  // sponge factor of each ring row by its distance to the top or bottom
     __shared__ int pub[W], con[W], fin[W];
+    __shared__ T ringsd[PATCH ? W : 1][PATCH ? 20 * R : 1];
     const int nx = p->nx, ny = p->ny, ns = p->nrun, hx = p->hx, ow = 64 * V - 2 * hx;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -237,6 +243,14 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
         // bit k, row Y - ns + k: what to do with its pre-collision state (rho,
         // its sum, receivers), the source, the sponge
         uint32_t mpre = 0, mrec = 0, msrc = 0, mspo = 0;
+        // PATCH: rows of the coarse inner ring and their coarse c^2; rows with
+        // nodes of the outer ring, those that are its top or bottom row, and
+        // its states at that row after either step (the sides' are in LDS).
+        // All are read with the rows themselves: read where they are used they
+        // were a chain of a microsecond per row (a 1033 x 521 patch 15.5 us,
+        // 8.1 without any interface)
+        uint32_t mres = 0, mring = 0, mtb = 0;
+        T ringtb[2][PATCH ? 5 : 1], ringc[PATCH ? R : 1];
         int nrec = 0;
         {
             const int xl = xa + lane * V;
@@ -275,6 +289,35 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                     for (int j = 0; j < V; ++j) fx[j] = sponge_at<T>(min(xw[j], nx - 1 - xw[j]), L, smax);
                     sfy = sponge_at<T>(dyl, L, smax);
                 }
+            }
+            if constexpr (PATCH) {
+                const KernPatch pp = (KernPatch)p;
+                const int cy = pp->iface.g.Y0 + (row_l >> 1);
+                mres = (uint32_t)__ballot(owned && !(row_l & 1) && cy >= pp->iface.g.ya && cy <= pp->iface.g.yb);
+                // only nodes of the grid itself count: what lies beyond the
+                // ring does not reach the nodes within
+                const bool side = xa <= 0 || xa + 64 > nx - 1;
+                mtb = (uint32_t)__ballot(mine && (row_l == 0 || row_l == ny - 1));
+                mring = side ? ~0u : mtb;
+                const GlobalPtr<const T> rb = (GlobalPtr<const T>)pp->ring, cc = (GlobalPtr<const T>)pp->iface.dst_c2;
+                const int rn = pp->ring_n;
+                if (mtb) {
+                    const int k = (Y <= 2 ? 0 : nx) + min(max(xl, 0), nx - 1);
+#pragma unroll
+                    for (int i = 0; i < 10; ++i) ringtb[i / 5][i % 5] = rb[i * rn + k];
+                }
+                if (side) {   // [step][side][population][slot]
+                    for (int e = lane; e < 20 * R; e += 64) {
+                        const int st = e / (10 * R), sd = e / (5 * R) % 2, i = e / R % 5, y = Y + e % R - st - 1;
+                        ringsd[w][e] = y >= 1 && y <= ny - 2 ? rb[(st * 5 + i) * rn + 2 * nx + sd * (ny - 2) + y - 1] : T(0);
+                    }
+                }
+                const int cx = min(max(pp->iface.g.X0 + (xl >> 1), 0), pp->iface.dst_nx - 1);
+                static_for<0, R>([&](auto rc) __attribute__((always_inline)) {
+                    constexpr int r = decltype(rc)::value;
+                    const int y = min(max(pp->iface.g.Y0 + ((Y + r - 2) >> 1), 0), pp->iface.dst_ny - 1);
+                    ringc[r] = (mres >> r) & 1 ? cc[(int64_t)y * pp->iface.dst_nx + cx] : T(0);
+                });
             }
             if (p->rec.row_ptr != nullptr) {
                 // receivers among the rows and columns this bundle stores go
@@ -316,7 +359,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                 }
                 if (p->rec.nslots > 0x80000) nrec = 64 * V + 1;   // slots too large for the table
             }
-            mpre = mrec;
+            mpre = mrec | mres;
             if (frho || fsum) mpre |= (uint32_t)__ballot(owned);
             // the ring slot is free once the bundles that read its rows are done
             for (int m = 0; m <= mlast; ++m) {
@@ -364,7 +407,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
             const ct *cb = c2s + rs * 64 + lane;
             const T *sb = sfys + rs + min(lane, R - 1);
             const int sh = ns - s;
-            const uint32_t bpre = mpre >> sh, bpost = (msrc | mspo) >> sh;
+            const uint32_t bpre = PATCH && s < ns ? 0 : mpre >> sh, bpost = (msrc | mspo | mring) >> sh;
             T fyl = T(1);
             if (mspo) fyl = *sb;
             // where slot 0's row of rho and of its sums goes
@@ -410,6 +453,28 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                                 if (own0 && xl + j < nx) a += double(rv[j]);
                             a = wave_total(a);
                             if (lane == 63) st_nt(a, sum_s + r * p->nstrip);
+                        }
+                    }
+                    if constexpr (PATCH) {
+                        if ((mres >> (sh + r)) & 1) {
+                            // fine nodes that coincide with a coarse node of
+                            // the inner ring replace its state
+                            const auto &ip = ((KernPatch)rare(p))->iface;
+                            const int cy = ip.g.Y0 + (gy >> 1);
+#pragma unroll
+                            for (int j = 0; j < V; ++j) {
+                                const int x = xl + j, cx = ip.g.X0 + (x >> 1);
+                                if (own0 && x < nx && !(x & 1) && cx >= ip.g.xa && cx <= ip.g.xb &&
+                                    (cx == ip.g.xa || cx == ip.g.xb || cy == ip.g.ya || cy == ip.g.yb)) {
+                                    T gj[5], out[5];
+#pragma unroll
+                                    for (int i = 0; i < 5; ++i) gj[i] = g[i][j];
+                                    rescale_collide<S, KIND>(ip, gj, cx, cy, ringc[r], out);
+                                    S *d = reinterpret_cast<S *>(ip.dst) + (int64_t)cy * ip.dst_nx + cx;
+#pragma unroll
+                                    for (int i = 0; i < 5; ++i) *(GlobalPtr<S>)(d + i * ip.dst_pstride) = to_store<S>(out[i]);
+                                }
+                            }
                         }
                     }
                     if ((mrec >> (sh + r)) & 1) {
@@ -496,6 +561,18 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                         const T sf = min(fx[j], fy);
 #pragma unroll
                         for (int i = 0; i < Q; ++i) pj[j][i] = pj[j][i] * sf;
+                    }
+                    if constexpr (PATCH) {   // the outer ring's states come from the coarse grid
+                        const int x = xa + lane;
+                        if ((mtb >> (sh + r)) & 1) {
+#pragma unroll
+                            for (int i = 0; i < 5; ++i) pj[0][i] = s == 1 ? ringtb[0][i] : ringtb[1][i];
+                        } else if ((mring >> (sh + r)) & 1) {
+                            if (x == 0 || x == nx - 1) {
+#pragma unroll
+                                for (int i = 0; i < 5; ++i) pj[0][i] = ringsd[w][((s - 1) * 10 + (x == 0 ? 0 : 5) + i) * R + r];
+                            }
+                        }
                     }
                 }
                 // rounded to the storage format, as a stored state would be
@@ -589,7 +666,32 @@ void k_flow(FlowParams, FlowBatch fb) {
         p = (KernFlow)(fb.img + __builtin_amdgcn_readfirstlane(fb.order[lo]));
         if (p->nrun < 1) return;
     }
-    flow_body<S, Q, KIND, F::V, F::R, F::W, F::E, OUT>(p, blk);
+    flow_body<S, Q, KIND, F::V, F::R, F::W, F::E, OUT ? 1 : 0>(p, blk);
+}
+
+// The two fine steps of a coarse step of a refined grid, 10.9 us for a
+// 1033 x 521 patch (10.1 and 10.6 as two one-step launches).  Two steps are a
+// latency more than a throughput: blocks of 8 waves, two per CU (FP64: one,
+// with twice the registers), so that a share is one bundle per wave.
+template <typename S> struct PatchShape {
+    static constexpr int V = 1, R = 4, W = 8, EU = sizeof(S) == 8 ? 2 : 4, E = 0;
+};
+
+template <typename S, int KIND>
+__global__ __launch_bounds__(PatchShape<S>::W * 64)
+__attribute__((amdgpu_waves_per_eu(PatchShape<S>::EU, PatchShape<S>::EU)))
+void k_flow_patch(FlowPatchParams) {
+    using F = PatchShape<S>;
+    flow_body<S, 5, KIND, F::V, F::R, F::W, F::E, 2>((KernFlow)__builtin_amdgcn_kernarg_segment_ptr(), xcd_block());
+}
+
+template <typename S>
+hipError_t flow_patch_launch(const FlowPatchParams &p, hipStream_t s) {
+    return for_kind<S, 5>(step_kind(p.f.coll), [&](auto kc) {
+        hipLaunchKernelGGL((k_flow_patch<S, decltype(kc)::value>), dim3((unsigned)p.f.nblk),
+                           dim3(PatchShape<S>::W * 64), 0, s, p);
+        return hipGetLastError();
+    });
 }
 
 template <typename S, int Q, bool SMALL, bool OUT>
@@ -629,6 +731,12 @@ FlowInfo flow_info() {
                      : flow_launch<SS, QQ, false, false>(p, fb, nblk, kind, s);                                     \
     }                                                                                                               \
     FlowInfo flow_info_##NAME(bool small) { return small ? flow_info<SS, QQ, true>() : flow_info<SS, QQ, false>(); }
+
+#define LBW_FLOW_PATCH_UNIT(SS, NAME) \
+    hipError_t launch_flow_patch_##NAME(const FlowPatchParams &p, hipStream_t s) { return flow_patch_launch<SS>(p, s); }
+hipError_t launch_flow_patch_f32(const FlowPatchParams &p, hipStream_t s);
+hipError_t launch_flow_patch_f64(const FlowPatchParams &p, hipStream_t s);
+hipError_t launch_flow_patch_f16(const FlowPatchParams &p, hipStream_t s);
 
 #define LBW_FLOW_DECL(NAME)                                                                                         \
     hipError_t launch_flow_##NAME(bool small, const FlowParams &p, const FlowBatch &fb, int64_t nblk, int kind,      \

@@ -106,6 +106,40 @@ hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipS
     return dispatch(storage, q, small, p, FlowBatch(), p.nblk, p.coll, s);
 }
 
+namespace {
+template <typename S>
+FlowInfo patch_info() {
+    static_assert(flow_steps_ok(2, PatchShape<S>::R, PatchShape<S>::W, PatchShape<S>::E));
+    FlowInfo f;
+    f.V = PatchShape<S>::V;
+    f.R = PatchShape<S>::R;
+    f.steps = 2;
+    return f;
+}
+FlowInfo patch_info(int storage) {
+    return storage == ST_F64 ? patch_info<double>() : storage == ST_F32 ? patch_info<float>() : patch_info<_Float16>();
+}
+}  // namespace
+
+// Halos of exactly two columns (the odd rows of a fine grid start anywhere) and
+// as many blocks as run at once.
+void flow_patch_geometry(int storage, FlowParams &p) {
+    const FlowInfo f = patch_info(storage);
+    p.hx = 2;
+    const int ow = 64 * f.V - 2 * p.hx;
+    p.nstrip = (p.nx + ow - 1) / ow;
+    p.nl = p.nr = 0;
+    const int64_t bundles = (int64_t)p.nstrip * ((p.ny + f.R - 1) / f.R);
+    p.nblk = (int32_t)std::max<int64_t>(1, std::min<int64_t>((storage == ST_F64 ? 1 : 2) * kFlowBlocks, bundles));
+}
+
+hipError_t launch_flow_patch(int storage, const FlowPatchParams &p, hipStream_t s) {
+    if (p.ring == nullptr || p.f.nrun != 2 || p.f.nx < 16 || p.f.ny < 16 || !flow_fits(patch_info(storage), p.f)) return hipErrorInvalidValue;
+    if (storage == ST_F32) return launch_flow_patch_f32(p, s);
+    if (storage == ST_F64) return launch_flow_patch_f64(p, s);
+    return launch_flow_patch_f16(p, s);
+}
+
 FlowInfo flow_adjoint_info(int storage, int q, bool small) {
     if (storage == ST_F64) return q == 5 ? flow_adjoint_info_f64_q5(small) : flow_adjoint_info_f64_q9(small);
     return q == 5 ? flow_adjoint_info_f32_q5(small) : flow_adjoint_info_f32_q9(small);

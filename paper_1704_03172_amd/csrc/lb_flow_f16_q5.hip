@@ -4,4 +4,5 @@
 
 namespace lbw {
 LBW_FLOW_UNIT(_Float16, 5, f16_q5)
+LBW_FLOW_PATCH_UNIT(_Float16, f16)
 }  // namespace lbw

@@ -4,4 +4,5 @@
 
 namespace lbw {
 LBW_FLOW_UNIT(float, 5, f32_q5)
+LBW_FLOW_PATCH_UNIT(float, f32)
 }  // namespace lbw

@@ -4,4 +4,5 @@
 
 namespace lbw {
 LBW_FLOW_UNIT(double, 5, f64_q5)
+LBW_FLOW_PATCH_UNIT(double, f64)
 }  // namespace lbw

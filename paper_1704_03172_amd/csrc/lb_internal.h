@@ -150,6 +150,9 @@ struct StepParams {
     InterfaceParams iface;
     int32_t pre_rows = 0;              // set by launch_step: leading block rows that
                                        // do the prolong_on work
+    int32_t x0 = 0, x1 = 0;            // region updated, [x0, x1) x [y0, y1) (x1 = 0: the whole
+    int32_t y0 = 0, y1 = 0;            // grid), of a destination with a population stride of its
+    int64_t dst_pstride = 0;           // own; the region's neighbours are read from src
     const GraphTab *gtab = nullptr;    // graph replay: rec.col is relative to gtab->t0 and
     int32_t goff = 0;                  // the source amplitude is gtab->s[goff]
 };
@@ -186,6 +189,22 @@ struct FlowParams {
     const GraphTab *gtab = nullptr;
     double s[kFlowSteps] = {};         // source amplitudes of times n + 1 ..
 };
+
+// The fine steps of one coarse step of a refined grid in one launch of the
+// flowing kernel: f is the fine grid's (f.nrun = 2, receivers recorded at the
+// last step only, into column f.rec.col + nrun - 1); after each step the outer
+// ring takes its states from ring ([nrun][5][ring_n]); the last step writes
+// the coarse inner ring from its pre-collision state (iface, as for
+// launch_restrict).
+struct FlowPatchParams {
+    FlowParams f;
+    const void *ring = nullptr;
+    int32_t ring_n = 0;
+    InterfaceParams iface;
+};
+hipError_t launch_flow_patch(int storage, const FlowPatchParams &p, hipStream_t s);
+// Its strips and blocks.
+void flow_patch_geometry(int storage, FlowParams &p);
 
 // The active shots of a batched launch.
 struct FlowBatch {

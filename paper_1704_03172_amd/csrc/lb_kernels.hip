@@ -25,6 +25,7 @@
 // and the collide-only launch of time 0; runs of steps (the adjoint's
 // recompute included) go to the flowing kernel of lb_flow.h.  Both take their
 // per-node arithmetic from lb_node.h.
+#include "lb_iface.h"
 #include "lb_internal.h"
 #include "lb_node.h"
 
@@ -51,62 +52,6 @@ __device__ inline void pre_at(const GridRef &r, int x, int y, T (&g)[5]) {
 // Snapshot layout (written by the coarse step, see update_tile): top row
 // (y = Y0, x = X0-1 .. X0+W+1), bottom row (y = Y0+H), left column (x = X0,
 // y = Y0-1 .. Y0+H+1), right column (x = X0+W).
-
-// R_f(g) = g^eq(rho(g), J(g)) + f (g - g^eq) with the weights of the
-// receiving node's c^2 (eq. coarse-fine dist connect), then the collision
-// (and sponge) of the receiving grid; written as the post-collision state at
-// node (x, y) of dst.
-template <typename S, int KIND>
-__device__ inline void rescale_collide(const InterfaceParams &p, typename Tr<S>::T (&gh)[5], int x, int y,
-                                       typename Tr<S>::T (&out)[5]) {
-    using T = typename Tr<S>::T;
-    const int64_t k = (int64_t)y * p.dst_nx + x;
-    const T c2 = reinterpret_cast<const T *>(p.dst_c2)[k];
-    T rho = T(0), jx = T(0), jy = T(0);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        rho += gh[i];
-        jx += T(cxv<5>(i)) * gh[i];
-        jy += T(cyv<5>(i)) * gh[i];
-    }
-    T w[5];
-    weights<T, 5>(c2, p.coll, w);
-    T gr[5];
-    const T f = T(p.f);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) {
-        T geq = w[i] * rho + (i == 0 ? T(0) : T(0.5) * (T(cxv<5>(i)) * jx + T(cyv<5>(i)) * jy));
-        gr[i] = geq + f * (gh[i] - geq);
-    }
-    collide<T, 5, KIND>(gr, c2, p.coll, out, w);
-    const T sf = sponge_factor<T>(x, y, p.dst_nx, p.dst_ny, p.sponge_width, p.sponge_smax);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) out[i] *= sf;
-}
-
-template <typename S, int KIND>
-__device__ inline void rescale_collide_store_impl(const InterfaceParams &p, typename Tr<S>::T (&gh)[5], int x, int y) {
-    using T = typename Tr<S>::T;
-    const int64_t k = (int64_t)y * p.dst_nx + x;
-    if (p.field) {   // R_f keeps rho and J: the node's fields are those of gh
-        T rho = T(0), jx = T(0), jy = T(0);
-#pragma unroll
-        for (int i = 0; i < 5; ++i) {
-            rho += gh[i];
-            jx += T(cxv<5>(i)) * gh[i];
-            jy += T(cyv<5>(i)) * gh[i];
-        }
-        const T c2 = reinterpret_cast<const T *>(p.dst_c2)[k];
-        T v = p.field == 1u ? c2 * rho : p.field == 2u ? rho : p.field == 4u ? jx : jy;
-        reinterpret_cast<T *>(p.field_out)[k] = v;
-        return;
-    }
-    T out[5];
-    rescale_collide<S, KIND>(p, gh, x, y, out);
-    S *dst = reinterpret_cast<S *>(p.dst);
-#pragma unroll
-    for (int i = 0; i < 5; ++i) dst[i * p.dst_pstride + k] = to_store<S>(out[i]);
-}
 
 // Interpolation stencil of fine outer-ring node (i, j): coincident nodes
 // copy the coarse node (weight 1 on entry 1, the other entries repeat it with
@@ -296,9 +241,9 @@ template <typename S, int Q, int KIND, bool PULL>
 __device__ inline double update_tile(const StepParams &p, int x0, int y) {
     using T = typename Tr<S>::T;
     constexpr int V = PULL ? Tr<S>::V : 1;
-    const int nx = p.nx, ny = p.ny;
+    const int nx = p.nx, ny = p.ny, x1 = p.x1;
     double local = 0.0;
-    if (x0 >= nx) return local;
+    if (x0 >= x1) return local;
 
     const S *src = reinterpret_cast<const S *>(p.src);
     T g[Q][V];
@@ -334,7 +279,7 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             const int x = x0 + j;
-            if (x >= nx) break;
+            if (x >= x1) break;
             if ((y == Y0 || y == Y0 + H) && x >= X0 - 1 && x <= X0 + W + 1) {
                 const int t = (y == Y0 ? 0 : nh) + (x - (X0 - 1));
 #pragma unroll
@@ -363,8 +308,8 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
         const int x = x0 + j;
-        if (rb < re && x < nx) record_node<T, Q>(p.rec, rb, re, x, gj, c2v[j]);
-        if ((p.partial || p.rho_out) && x < nx) {
+        if (rb < re && x < x1) record_node<T, Q>(p.rec, rb, re, x, gj, c2v[j]);
+        if ((p.partial || p.rho_out) && x < x1) {
             T rho = T(0);
 #pragma unroll
             for (int i = 0; i < Q; ++i) rho += gj[i];
@@ -399,7 +344,7 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
     S *dst = reinterpret_cast<S *>(p.dst);
 #pragma unroll
     for (int i = 0; i < Q; ++i)
-        store_x<S, V>(dst + i * p.pstride + (int64_t)y * nx, x0, nx, outv[i]);
+        store_x<S, V>(dst + i * p.dst_pstride + (int64_t)y * nx, x0, x1, outv[i]);
     return local;
 }
 
@@ -416,8 +361,8 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepParams
             return;
         }
     }
-    const int y = blockIdx.y - p.pre_rows;
-    const int x0 = (blockIdx.x * kStepBlock + threadIdx.x) * V;
+    const int y = blockIdx.y - p.pre_rows + p.y0;
+    const int x0 = p.x0 + (blockIdx.x * kStepBlock + threadIdx.x) * V;
     double local = update_tile<S, Q, KIND, PULL>(p, x0, y);
 
     if (p.partial) {   // uniform branch: per-block sum of rho in FP64
@@ -738,13 +683,21 @@ hipError_t step_by_lattice(int q, int kind, F &&f) {
 template <typename S>
 hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
     const int V = vwidth<S>(pull);
-    dim3 grid((unsigned)(((int64_t)p0.nx + (int64_t)V * kStepBlock - 1) / ((int64_t)V * kStepBlock)), (unsigned)p0.ny);
     const int kind = step_kind(p0.coll);
     StepParams p = p0;
     p.pre_rows = 0;
+    if (p.x1 <= 0) {   // the whole grid
+        p.x0 = p.y0 = 0;
+        p.x1 = p.nx;
+        p.y1 = p.ny;
+        p.dst_pstride = p.pstride;
+    }
+    if (p.x0 < 0 || p.y0 < 0 || p.x0 >= p.x1 || p.y0 >= p.y1 || p.x1 > p.nx || p.y1 > p.ny) return hipErrorInvalidValue;
+    dim3 grid((unsigned)(((int64_t)p.x1 - p.x0 + (int64_t)V * kStepBlock - 1) / ((int64_t)V * kStepBlock)),
+              (unsigned)(p.y1 - p.y0));
     if (p0.prolong_on) {
         const int rows = (int)((ring_tile_blocks<kStepBlock>(p0.iface.g) + grid.x - 1) / grid.x);
-        if (!kIsF64<S> && (int64_t)p0.ny + rows <= 65535) {
+        if (!kIsF64<S> && (int64_t)grid.y + rows <= 65535) {
             p.pre_rows = rows;
             grid.y += (unsigned)rows;
         } else {   // a launch of its own first

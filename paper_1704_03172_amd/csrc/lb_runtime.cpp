@@ -140,8 +140,47 @@ FlowPlan flow_plan(const lb_grid_desc *d) {
 // workspace, one per row, strip and step.
 int sum_steps(int64_t nodes) { return nodes <= (1 << 21) ? lbw::kFlowSteps : 4; }
 
+constexpr int kPairSide = 16;               // smallest fine side for both fine steps in one launch
+constexpr int kWindowSteps = 8;            // most coarse steps taken together
+constexpr int kWindowShare = 3;            // smallest ratio of grid to window nodes
+
+// Coarse steps of a refined grid taken together (see window_steps): the coarse
+// nodes [x0, x1) x [y0, y1) are those that the patch can reach in `steps` steps
+// (the inner ring and `steps` nodes around it) and those that its outer ring is
+// made from.  Region k = 1 .. steps - 1 of the stepwise updates reaches
+// steps - k rows and, to stay aligned, 4 (steps - k) columns further on each
+// side.  steps = 0: no room for the regions on the grid, or a window that is
+// itself much of the grid.  Measured with a patch of n/4 x n/8 (us per coarse
+// step, tau = 1/2; one step per launch / both fine steps together / the window
+// at 4, 8 and 16 steps): FP32 256^2 23.8 / 18.2 / -, 16.7, -; 1024^2 29.7 / - /
+// 20.1, 18.7, 18.8; 2048^2 56.6 / - / 29.4, 24.6, 24.1; FP64 1024^2 38.3 / - /
+// 26.9, 23.7, 24.5; 2048^2 97.4 / - / 53.3, 44.0, 42.1.
+struct WindowPlan {
+    int steps = 0;
+    int32_t x0 = 0, x1 = 0, y0 = 0, y1 = 0;
+    int32_t rows = 0;              // of the largest region
+};
+WindowPlan window_plan(const lb_grid_desc *d) {
+    WindowPlan w;
+    if (!d->patch_enable || d->steps_per_launch == 1) return w;
+    const PatchGeom g = patch_geom(d);
+    const int K = d->steps_per_launch > 0 ? std::min(d->steps_per_launch, kWindowSteps) : kWindowSteps;
+    w.x0 = std::min(g.xa - K, g.X0 - 3) & ~3;
+    w.x1 = (std::max(g.xb + K, g.X0 + g.W + 3) + 1 + 3) & ~3;
+    w.y0 = std::min(g.ya - K, g.Y0 - 3);
+    w.y1 = std::max(g.yb + K, g.Y0 + g.H + 3) + 1;
+    w.rows = w.y1 - w.y0 + 2 * (K - 1);
+    const int ex = 4 * K, ey = K;   // region 1, and its neighbours
+    if (w.x0 - ex < 0 || w.x1 + ex > d->nx || w.y0 - ey < 0 || w.y1 + ey > d->ny) return w;
+    if (kWindowShare * (int64_t)(w.x1 - w.x0) * (w.y1 - w.y0) > (int64_t)d->nx * d->ny) return w;
+    if (g.nxf < kPairSide || g.nyf < kPairSide) return w;
+    w.steps = K;
+    return w;
+}
+
 struct Layout {
-    int64_t pstride = 0, fpstride = 0;
+    int64_t pstride = 0, fpstride = 0, wpstride = 0;
+    size_t win = 0;
     int64_t nblocks = 0;
     size_t pop[2] = {0, 0}, c2 = 0, rrow = 0, rxs = 0, rslot = 0;
     size_t frow = 0, fxs = 0, fslot = 0, partial = 0, scratch = 0, misfit = 0;
@@ -186,6 +225,9 @@ Layout make_layout(const lb_grid_desc *d) {
         L.fslot = take((size_t)std::max(d->max_receivers, 1) * 4);
         L.snap = take(2 * 5 * (size_t)g.nsnap * ts);   // ping-pong by coarse time parity
         L.ring = take(2 * 5 * (size_t)g.nring * ts);   // fine outer ring at T+1, T+2
+        const WindowPlan w = window_plan(d);
+        L.wpstride = (int64_t)w.rows * d->nx;
+        if (w.steps > 0) L.win = take(5 * (size_t)L.wpstride * ss);
     }
     if (d->ckpt_every > 0) {
         L.ckpt = take((size_t)d->ckpt_capacity * d->lattice * L.pstride * ss);
@@ -243,6 +285,8 @@ struct lb_grid {
     uint32_t what = 0;
     double *sum_rho = nullptr;
     int sticky = LB_OK;
+    WindowPlan window;             // refined grids: coarse steps taken together
+    char *win = nullptr;           // [5][window.rows][nx] coarse states of a region
     // adjoint support
     char *ckpt = nullptr;          // [ckpt_capacity] population states
     void *seg = nullptr;           // [ckpt_every][ny][nx] recomputed rho
@@ -338,6 +382,16 @@ void attach_receivers(const lb_grid *h, const Lattice &g, P &p, int64_t col) {
     p.rec.col = col;
 }
 
+// Have a coarse launch keep g(col) on the ring line: the snapshot of time col.
+void keep_snapshot(const lb_grid *h, StepParams &p, int64_t col) {
+    p.snap = snap_buffer(h, col);
+    p.snap_x0 = h->geom.X0;
+    p.snap_y0 = h->geom.Y0;
+    p.snap_w = h->geom.W;
+    p.snap_h = h->geom.H;
+    p.snap_n = h->geom.nsnap;
+}
+
 // Launch one update of lattice g: pull-stream + collide (or collide only
 // when `pull` is false, for the state at time 0).  Records column `col`.
 // A fine launch takes its outer ring from ring_buf and, with `restr`, also
@@ -354,14 +408,7 @@ int launch_update(lb_grid *h, Lattice &g, bool is_main, bool pull, int64_t col, 
     if (sum) p.partial = h->partial;
     if (is_main && h->tape_valid) p.rho_out = tape_field(h, col);
     const int64_t base = graph_time(h, p, col);
-    if (is_main && h->patch) {   // keep g(col) on the ring line: snapshot of time col
-        p.snap = snap_buffer(h, col);
-        p.snap_x0 = h->geom.X0;
-        p.snap_y0 = h->geom.Y0;
-        p.snap_w = h->geom.W;
-        p.snap_h = h->geom.H;
-        p.snap_n = h->geom.nsnap;
-    }
+    if (is_main && h->patch) keep_snapshot(h, p, col);
     if (ring_buf) {
         p.ring_buf = ring_buf;
         p.ring_n = h->geom.nring;
@@ -474,7 +521,48 @@ int initial_collision(lb_grid *h) {
     return LB_OK;
 }
 
-int one_step(lb_grid *h) {
+int even_steps(int64_t m, int most);
+FlowParams flow_params(const lb_grid *h, int64_t col, int ns, int steps);
+
+lbw::GridRef coarse_ref(const lb_grid *h, const void *pop, int64_t pstride) {
+    lbw::GridRef r;
+    r.pop = pop;
+    r.pre = 0;
+    r.c2 = h->main.c2;
+    r.nx = h->main.nx;
+    r.ny = h->main.ny;
+    r.pstride = pstride;
+    return r;
+}
+
+// Both fine steps of the coarse step to time col in one launch of the flowing
+// kernel, with the restriction rp.  The other fine buffer then holds the state
+// of two fine steps before, so a call's last coarse step takes one by one
+// (the fine fields are read from the state of one step before).
+int fine_pair(lb_grid *h, int64_t col, const InterfaceParams &rp) {
+    Lattice &g = h->fine;
+    lbw::FlowPatchParams p;
+    p.f.src = g.curp();
+    p.f.dst = g.prevp();
+    p.f.c2 = g.c2;
+    p.f.nx = g.nx;
+    p.f.ny = g.ny;
+    p.f.pstride = g.pstride;
+    p.f.nrun = 2;
+    p.f.coll = h->coll;
+    if (recording(h)) attach_receivers(h, g, p.f, col - 1);   // the second step's column is col
+    lbw::flow_patch_geometry(h->storage, p.f);
+    p.ring = h->ring;
+    p.ring_n = h->geom.nring;
+    p.iface = rp;
+    LB_TRY(h, lbw::launch_flow_patch(h->storage, p, h->stream));
+    g.cur = 1 - g.cur;
+    g.prev_pre = 0;
+    return LB_OK;
+}
+
+// One step; pair: the two fine steps of a refined grid in one launch.
+int one_step(lb_grid *h, bool pair = false) {
     int rc;
     const bool rec = recording(h), sum = h->sum_rho != nullptr;
     const int64_t col = h->t + 1;
@@ -484,25 +572,71 @@ int one_step(lb_grid *h) {
         h->t = col;
         return LB_OK;
     }
-    // Coarse step T -> T+2 in fine time units (Sec. IV schedule), 3 launches:
-    // the coarse step, which also keeps the ring-line snapshot of T+2 for the
-    // next step and computes the fine outer-ring states of T+1 and T+2 (from
-    // h(T), whose pull is g(T+2), and the snapshot of T: both only read by
-    // this launch); then two fine steps, the second of which also restricts
-    // to the coarse inner ring of T+2.
-    lbw::GridRef coarse_src;
-    coarse_src.pop = h->main.curp();
-    coarse_src.pre = 0;
-    coarse_src.c2 = h->main.c2;
-    coarse_src.nx = h->main.nx;
-    coarse_src.ny = h->main.ny;
-    coarse_src.pstride = h->main.pstride;
-    const InterfaceParams pp = prolong_params(h, coarse_src, h->t);
+    // Coarse step T -> T+2 in fine time units (Sec. IV schedule), 2 or 3
+    // launches: the coarse step, which also keeps the ring-line snapshot of
+    // T+2 for the next step and computes the fine outer-ring states of T+1 and
+    // T+2 (from h(T), whose pull is g(T+2), and the snapshot of T: both only
+    // read by this launch); then two fine steps, the second of which also
+    // restricts to the coarse inner ring of T+2.
+    const InterfaceParams pp = prolong_params(h, coarse_ref(h, h->main.curp(), h->main.pstride), h->t);
     if ((rc = launch_update(h, h->main, true, true, col, rec, false, nullptr, nullptr, &pp))) return rc;
-    if ((rc = launch_update(h, h->fine, false, true, col, false, false, ring_half(h, 0)))) return rc;  // T+1
     const InterfaceParams rp = restrict_params(h);
-    if ((rc = launch_update(h, h->fine, false, true, col, rec, false, ring_half(h, 1), &rp))) return rc;  // T+2
+    if (pair && h->fine.nx >= kPairSide && h->fine.ny >= kPairSide) {
+        if ((rc = fine_pair(h, col, rp))) return rc;
+    } else {
+        if ((rc = launch_update(h, h->fine, false, true, col, false, false, ring_half(h, 0)))) return rc;  // T+1
+        if ((rc = launch_update(h, h->fine, false, true, col, rec, false, ring_half(h, 1), &rp))) return rc;  // T+2
+    }
     h->t = col;
+    return LB_OK;
+}
+
+// K coarse steps of a refined grid: the whole coarse grid in one launch of the
+// flowing kernel as if there were no patch, then step by step only the window
+// around the patch, whose last states replace the flowing kernel's where the
+// patch was felt.  The steps of the window alternate between a buffer of their
+// own and the buffer that held the state before (the flowing kernel has read
+// it); the last one goes to the flowing kernel's result.  Receivers in the
+// window are written by both, last by the window's steps.
+int window_steps(lb_grid *h, int K) {
+    const WindowPlan &w = h->window;
+    Lattice &g = h->main;
+    FlowParams f = flow_params(h, h->t + 1, K, K);
+    if (recording(h)) attach_receivers(h, g, f, h->t + 1);
+    LB_TRY(h, lbw::launch_flow(h->storage, h->q, h->flow.small, f, h->stream));
+    // the window's buffer as if it began with row 0 of the grid
+    char *win = h->win - (int64_t)(w.y0 - (w.steps - 1)) * g.nx * (int64_t)h->ssize;
+    const void *src = g.curp();
+    int64_t src_pstride = g.pstride;
+    for (int k = 1; k <= K; ++k) {
+        const int64_t col = h->t + 1;
+        const bool to_win = k < K && (k & 1);
+        StepParams p = base_params(h, g, true);
+        p.src = src;
+        p.pstride = src_pstride;
+        p.dst = k == K ? g.prevp() : to_win ? (void *)win : g.curp();
+        p.dst_pstride = to_win ? h->L.wpstride : g.pstride;
+        p.x0 = w.x0 - 4 * (K - k);
+        p.x1 = w.x1 + 4 * (K - k);
+        p.y0 = w.y0 - (K - k);
+        p.y1 = w.y1 + (K - k);
+        p.s_n = source_at(h, col);
+        if (recording(h)) attach_receivers(h, g, p, col);
+        keep_snapshot(h, p, col);
+        p.prolong_on = 1;
+        p.iface = prolong_params(h, coarse_ref(h, src, src_pstride), h->t);
+        LB_TRY(h, lbw::launch_step(h->storage, p, true, h->stream));
+        InterfaceParams rp = restrict_params(h);
+        rp.dst = p.dst;
+        rp.dst_pstride = p.dst_pstride;
+        const int rc = fine_pair(h, col, rp);
+        if (rc) return rc;
+        src = p.dst;
+        src_pstride = p.dst_pstride;
+        h->t = col;
+    }
+    g.cur = 1 - g.cur;
+    g.prev_pre = 0;
     return LB_OK;
 }
 
@@ -743,6 +877,8 @@ int lb_create_grid(const lb_grid_desc *d, void *d_workspace, size_t ws_bytes, vo
         f.rslot = (int32_t *)(h->ws + L.fslot);
         h->snap = h->ws + L.snap;
         h->ring = h->ws + L.ring;
+        h->window = window_plan(d);
+        h->win = h->ws + L.win;
     }
     if (d->ckpt_every > 0) {
         h->ckpt = h->ws + L.ckpt;
@@ -869,7 +1005,8 @@ int lb_record_sum_rho(lb_grid *h, double *d_sum) {
 namespace {
 
 // Most steps of one launch of lb_step_n: what the flowing kernel offers, at
-// most the descriptor's steps_per_launch (if set); one with a patch.
+// most the descriptor's steps_per_launch (if set); one with a patch (which
+// next_launch takes several at a time by its own rule).
 int most_steps(const lb_grid *h) {
     if (h->patch) return 1;
     int ns = h->flow.steps;
@@ -954,8 +1091,13 @@ int flow_launch(lb_grid *h, int ns) {
 
 // The next launch of a call with `left` steps to take; *ns: the steps taken.
 // Single steps go through the one-step kernel unless the sum of rho is
-// recorded (see flow_launch).
+// recorded (see flow_launch).  With a patch a call's last step goes one launch
+// at a time: the fields and the saved states are read from the states before.
 int next_launch(lb_grid *h, int64_t left, int *ns) {
+    if (h->patch && left > 1 && h->d.steps_per_launch != 1) {
+        *ns = left > 2 && h->window.steps > 1 ? even_steps(left - 1, h->window.steps) : 1;
+        return *ns > 1 ? window_steps(h, *ns) : one_step(h, true);
+    }
     *ns = next_steps(h, left);
     return *ns > 1 || (h->sum_rho && !h->patch) ? flow_launch(h, *ns) : one_step(h);
 }

@@ -123,3 +123,40 @@ def test_backward_steps_of_a_launch(precision, q, collision, tau, s):
         assert np.isfinite(got[0]).all() and np.abs(got[0]).max() > 0
         np.testing.assert_array_equal(got[0], got[1])
         np.testing.assert_array_equal(got[0], got[2])
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64", "f16s"])
+@pytest.mark.parametrize("collision,tau,s", [("bgk", 0.5, None), ("mrt", 0.5, [1, 1, 1, 2, 2])])
+def test_refined_steps_taken_together(precision, collision, tau, s):
+    """A refined grid whose coarse steps are taken several at a time (large
+    grids) or whose fine steps two at a time (any) has the bits of one step per
+    launch: odd sides, a patch against the sponge and the source within the
+    window, receivers on it, around it and in the patch, short calls."""
+    from paper_1704_03172_amd import lbwave
+    for nx, ny, patch, nsteps in [(777, 531, (300, 211, 101, 53), 29), (777, 531, (44, 37, 30, 131), 20),
+                                  (121, 96, (40, 30, 21, 17), 14)]:
+        c = case(nx, ny, 5, collision, tau, s, nsteps)
+        px, py, pw, ph = patch
+        rng = np.random.default_rng(nx + px)
+        fine = rng.uniform(0.05, 0.45, (2 * (ph + 4) + 1, 2 * (pw + 4) + 1))
+        rec = np.array([(x, y) for y in sorted({1, py - 9, py - 3, py, py + 3, py + ph // 2, py + ph, py + ph + 6, ny - 1})
+                        for x in sorted({0, px - 9, px - 2, px - 1, px, px + 1, px + 2, px + 3, px + pw // 2, px + pw - 1,
+                                         px + pw, px + pw + 11, nx - 1})], dtype=np.int32)
+        got = []
+        for launch, calls in [(1, [nsteps]), (0, [nsteps]), (0, [1, 9, 2, nsteps - 12]), (3, [nsteps])]:
+            g = lbwave.Grid(nx, ny, collision=collision, precision=precision, tau=tau, s=s, sponge_width=12,
+                            sponge_sigma_max=0.1, patch=patch, trace_capacity=nsteps + 1, max_receivers=len(rec),
+                            steps_per_launch=launch)
+            g.set_medium(c["c2"])
+            g.set_medium(fine, fine=True)
+            g.set_state(c["rho0"], c["jx0"], c["jy0"])
+            g.set_state(0.01 * fine, fine=True)
+            g.set_source(px - 6, py + 7, c["wavelet"])
+            g.record(rec, fields=FIELDS)
+            for k in calls:
+                g.step(k)
+            got.append([g.traces.cpu().numpy()] + [g.field(f, fine=b).cpu().numpy() for f in FIELDS for b in (False, True)])
+        assert all(np.isfinite(a).all() and np.abs(a).max() > 0 for a in got[0])
+        for other in got[1:]:
+            for a, b in zip(got[0], other):
+                np.testing.assert_array_equal(a, b)
