@@ -237,6 +237,65 @@ __device__ inline void prolong_pair_tile(const InterfaceParams &p, int b) {
 template <typename S>
 constexpr bool kIsF64 = sizeof(S) == 8;
 
+// The receivers of a row, entries [rb, re), among the wave's columns: lane l of
+// the m active ones (the first m) holds columns x0 .. x0 + V - 1 with their
+// pre-collision state g; x1 ends the row.  The lanes look at m entries at a
+// time, and each writes the fields of its entry, taken from the lane that
+// holds the column.  (A search by each lane was a chain of loads: 8.5 us for a
+// step of 256^2 with 64 receivers in a row, 5.1 so.)
+template <typename T, int Q, int V>
+__device__ inline void record_wave(const Receivers &rc, int rb, int re, int x0, int x1, const T (&g)[Q][V], const T (&c2)[V]) {
+    const int lane = threadIdx.x & 63, m = __builtin_popcountll(__ballot(true));
+    const int xa = __builtin_amdgcn_readfirstlane(x0), xe = min(xa + m * V, x1);
+    // a short end of a row, or states that leave no registers (D2Q9 of half
+    // storage: 138 instead of 118)
+    if (V * Q > 64 || m < 16) {
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            T gj[Q];
+#pragma unroll
+            for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
+            if (x0 + j < x1) record_node<T, Q>(rc, rb, re, x0 + j, gj, c2[j]);
+        }
+        return;
+    }
+    int l = rb, u = re;   // the first entry with x >= xa is in [l, u]
+    while (u - l > m) {
+        const int st = (u - l + m - 1) / m, e = l + lane * st;
+        const int c = __builtin_popcountll(__ballot(e < u && rc.xs[min(e, u - 1)] < xa));
+        u = min(u, l + c * st);
+        l = c > 0 ? l + (c - 1) * st + 1 : l;
+    }
+    const int64_t plane = (int64_t)rc.nslots * rc.cap;
+    for (bool more = true; more && l < re; l += m) {
+        const int e = min(l + lane, re - 1), x = rc.xs[e], slot = rc.slot[e];
+        const bool hit = l + lane < re && x >= xa && x < xe;
+        more = __builtin_amdgcn_readlane(x, m - 1) < xe;
+        if (__ballot(hit) == 0) continue;
+        const int c = min(max(x - xa, 0), m * V - 1), from = c / V, jj = c % V;
+        T *tr = reinterpret_cast<T *>(rc.traces) + (int64_t)slot * rc.cap + rc.col;
+        for (int f = 0; f < 4; ++f) {
+            if (!((rc.what >> f) & 1)) continue;
+            T out = T(0);
+#pragma unroll
+            for (int j = 0; j < V; ++j) {
+                T rho = T(0), jx = T(0), jy = T(0);
+#pragma unroll
+                for (int i = 0; i < Q; ++i) {
+                    rho += g[i][j];
+                    jx += T(cxv<Q>(i)) * g[i][j];
+                    jy += T(cyv<Q>(i)) * g[i][j];
+                }
+                const T v = f == 0 ? c2[j] * rho : f == 1 ? rho : f == 2 ? jx : jy;
+                const T vs = __shfl(v, from);
+                if (jj == j) out = vs;
+            }
+            if (hit) *tr = out;
+            tr += plane;
+        }
+    }
+}
+
 template <typename S, int Q, int KIND, bool PULL>
 __device__ inline double update_tile(const StepParams &p, int x0, int y) {
     using T = typename Tr<S>::T;
@@ -300,6 +359,7 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
         rb = p.rec.row_ptr[y];
         re = p.rec.row_ptr[y + 1];
     }
+    if (rb < re) record_wave<T, Q, V>(p.rec, rb, re, x0, x1, g, c2v);
 
     S outv[Q][V];
 #pragma unroll
@@ -308,7 +368,6 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
         const int x = x0 + j;
-        if (rb < re && x < x1) record_node<T, Q>(p.rec, rb, re, x, gj, c2v[j]);
         if ((p.partial || p.rho_out) && x < x1) {
             T rho = T(0);
 #pragma unroll
