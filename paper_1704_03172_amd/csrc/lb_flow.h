@@ -252,6 +252,11 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
         uint32_t mres = 0, mring = 0, mtb = 0;
         T ringtb[2][PATCH ? 5 : 1], ringc[PATCH ? R : 1];
         int nrec = 0;
+        // OUT: rows that this run stores, and whether the lane stores some or
+        // all of its columns (the others find out where they need it)
+        uint32_t mown = 0;
+        auto stores = [&](int n) { return lane * V >= hx && lane * V < hx + ow && xa + lane * V + n <= nx; };
+        const bool some = OUT && stores(1), whole = OUT && stores(V), ragged = OUT && V > 1 && __ballot(some && !whole) != 0;
         {
             const int xl = xa + lane * V;
             int xw[V];
@@ -360,7 +365,10 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                 if (p->rec.nslots > 0x80000) nrec = 64 * V + 1;   // slots too large for the table
             }
             mpre = mrec | mres;
-            if (frho || fsum) mpre |= (uint32_t)__ballot(owned);
+            if constexpr (OUT) {
+                mown = (uint32_t)__ballot(owned);
+                mpre |= mown;
+            }
             // the ring slot is free once the bundles that read its rows are done
             for (int m = 0; m <= mlast; ++m) {
                 const int qq = q - W - E + m;
@@ -422,31 +430,32 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                 if constexpr (r > 0) cn = cb[(r - 1) * 64];
                 T g[Q][V];
                 pull_row2<T, Q, V>(U, C, D, g);
-                if (__builtin_expect((bpre >> r) & 1, 0)) {
-                    const int gy = Y + r - s, xl = xa + lane * V, c0 = lane * V;
-                    const bool own0 = c0 >= hx && c0 < hx + ow && xl < nx;
-                    if (OUT && (frho | fsum)) {   // summed as the one-step kernel sums it
+                if (__builtin_expect((bpre >> r) & 1, OUT)) {
+                    const int gy = Y + r - s, xl = xa + lane * V;
+                    const bool own0 = OUT ? some : stores(1);
+                    if (OUT) {   // rho with the bits that the one-step kernel gives it
                         T rv[V];
 #pragma unroll
                         for (int j = 0; j < V; ++j) {
-                            rv[j] = T(0);
+                            rv[j] = g[0][j];
 #pragma unroll
-                            for (int i = 0; i < Q; ++i) rv[j] += g[i][j];
+                            for (int i = 1; i < Q; ++i) rv[j] += g[i][j];
                         }
-                        if (frho && own0) {
+                        if (frho && ((mown >> (sh + r)) & 1)) {
                             T *rr = rho_s + (int64_t)r * nx;
-                            if (xl + V <= nx) {
+                            if (whole) {
                                 ct t;
 #pragma unroll
                                 for (int j = 0; j < V; ++j) t[j] = rv[j];
                                 st_nt(t, at_lane<ct>(rr, xl));
-                            } else {
+                            }
+                            if (ragged) {
 #pragma unroll
                                 for (int j = 0; j < V - 1; ++j)
-                                    if (xl + j < nx) st_nt(rv[j], rr + xl + j);
+                                    if (own0 && !whole && xl + j < nx) st_nt(rv[j], rr + xl + j);
                             }
                         }
-                        if (fsum) {   // one partial per row and strip
+                        if (fsum && ((mown >> (sh + r)) & 1)) {   // one partial per row and strip
                             double a = 0.0;
 #pragma unroll
                             for (int j = 0; j < V; ++j)
@@ -619,9 +628,9 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
         order();
         ring += W * R;
         if (ring >= RING) ring -= RING;
-        const int xl = xa + lane * V, c0 = lane * V;
-        if (c0 >= hx && c0 < hx + ow && xl < nx) {
-            const bool whole = xl + V <= nx;
+        const int xl = xa + lane * V;
+        if (stores(1)) {
+            const bool all = xl + V <= nx;
             static_for<0, R>([&](auto rc) __attribute__((always_inline)) {
                 constexpr int r = decltype(rc)::value;
                 const int gy = Y + r - ns;
@@ -629,7 +638,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                     S *d = reinterpret_cast<S *>(p->dst) + (int64_t)gy * nx;
 #pragma unroll
                     for (int i = 0; i < Q; ++i, d += p->pstride) {
-                        if (whole) {
+                        if (all) {
                             vt t;
 #pragma unroll
                             for (int j = 0; j < V; ++j) t[j] = S(h[r][i][j]);
