@@ -19,6 +19,7 @@ namespace {
 
 constexpr int kGraphRounds = 2;          // rounds of a captured graph
 constexpr size_t kStageBytes = 4 << 20;  // pinned staging of the uploads
+constexpr size_t kStageFlag = 256;       // its first bytes receive the c^2 check's flag
 constexpr int kTickEvents = 64;          // ticks whose completion can be tracked at once
 
 using lbw::align_up;
@@ -154,14 +155,45 @@ ShotLayout shot_layout(const lb_batch *b, const lb_shot_desc *s) {
 // pinned staging buffer at *off (advanced), so the copy runs without the
 // host waiting on it (a pageable source would make the call wait).
 int stage_copy(lb_batch *b, void *dst, const void *src, size_t bytes, size_t *off) {
-    if (bytes == 0) return LB_OK;
-    if (*off + bytes > kStageBytes) {   // full: let the uploads so far finish
-        BT_TRY(b, hipStreamSynchronize(b->up));
-        *off = 0;
+    for (size_t done = 0; done < bytes;) {   // in pieces if it is larger than the buffer
+        const size_t n = std::min(bytes - done, kStageBytes - kStageFlag);
+        if (*off + n > kStageBytes) {   // full: let the uploads so far finish
+            BT_TRY(b, hipStreamSynchronize(b->up));
+            *off = kStageFlag;
+        }
+        std::memcpy(b->stage + *off, (const char *)src + done, n);
+        BT_TRY(b, hipMemcpyAsync((char *)dst + done, b->stage + *off, n, hipMemcpyHostToDevice, b->up));
+        *off = align_up(*off + n);
+        done += n;
     }
-    std::memcpy(b->stage + *off, src, bytes);
-    BT_TRY(b, hipMemcpyAsync(dst, b->stage + *off, bytes, hipMemcpyHostToDevice, b->up));
-    *off = align_up(*off + bytes);
+    return LB_OK;
+}
+
+// Several parts to places that lie within `span` bytes from dst on, at offsets
+// from there: one copy for all (the bytes between them are not used), where a
+// copy each costs the host 5 us; part by part if they do not fit the staging
+// buffer together.
+struct Part {
+    size_t at;
+    const void *src;
+    size_t bytes;
+};
+int stage_parts(lb_batch *b, char *dst, size_t span, const Part *part, int n, size_t *off) {
+    if (kStageFlag + span > kStageBytes) {
+        for (int i = 0; i < n; ++i) {
+            const int rc = stage_copy(b, dst + part[i].at, part[i].src, part[i].bytes, off);
+            if (rc) return rc;
+        }
+        return LB_OK;
+    }
+    if (*off + span > kStageBytes) {
+        BT_TRY(b, hipStreamSynchronize(b->up));
+        *off = kStageFlag;
+    }
+    for (int i = 0; i < n; ++i)
+        if (part[i].bytes > 0) std::memcpy(b->stage + *off + part[i].at, part[i].src, part[i].bytes);
+    BT_TRY(b, hipMemcpyAsync(dst, b->stage + *off, span, hipMemcpyHostToDevice, b->up));
+    *off = align_up(*off + span);
     return LB_OK;
 }
 
@@ -214,8 +246,9 @@ int rebuild(lb_batch *b, size_t *off) {
     BT_TRY(b, hipStreamWaitEvent(b->up, b->ev_set[ns], 0));
     int rc;
     if (!b->order.empty()) {
-        if ((rc = stage_copy(b, d.order, b->order.data(), b->order.size() * 4, off))) return rc;
-        if ((rc = stage_copy(b, d.prefix, b->prefix.data(), b->prefix.size() * 4, off))) return rc;
+        const size_t at = (size_t)((char *)d.prefix - (char *)d.order), bytes = b->prefix.size() * 4;
+        const Part part[2] = {{0, b->order.data(), b->order.size() * 4}, {at, b->prefix.data(), bytes}};
+        if ((rc = stage_parts(b, (char *)d.order, at + bytes, part, 2, off))) return rc;
     }
     BT_TRY(b, hipEventRecord(b->ev_up, b->up));
     b->up_pending = true;
@@ -405,17 +438,16 @@ int lb_batch_add_shot(lb_batch *b, const lb_shot_desc *s, void *d_ws, size_t ws_
     // keep the GPU busy; the host waits only for this shot's uploads (the
     // range check of c^2)
     BT_TRY(b, hipStreamSynchronize(b->up));   // the staging buffer is free
-    size_t off = 0;
+    size_t off = kStageFlag;
     char *ws = (char *)d_ws;
     const int64_t n = (int64_t)s->nx * s->ny;
     if ((rc = lbw::upload_c2(b->up, b->scheme.precision, b->q, b->scheme.d2q9_ratio, ws + L.c2, c2, t, on_device,
-                             n, b->d_scratch))) {
+                             n, b->d_scratch, (int32_t *)b->stage))) {
         if (rc == LB_E_HIP) b->sticky = LB_E_HIP;
         return rc;
     }
     BT_TRY(b, lbw::launch_fill_zero(ws + L.pop0, (int64_t)(L.c2 - L.pop0), b->up));
     const int64_t nw = std::min<int64_t>(nt, s->nsteps + 1);
-    if (nw > 0 && (rc = stage_copy(b, ws + L.wavelet, wavelet, (size_t)nw * 8, &off))) return rc;
 
     // receiver tables: CSR over rows, x ascending
     struct R { int32_t x, y, slot; };
@@ -431,10 +463,14 @@ int lb_batch_add_shot(lb_batch *b, const lb_shot_desc *s, void *d_ws, size_t ws_
         xs[i] = v[i].x;
         sl[i] = v[i].slot;
     }
-    if (s->nrec > 0) {
-        if ((rc = stage_copy(b, ws + L.rrow, row.data(), row.size() * 4, &off))) return rc;
-        if ((rc = stage_copy(b, ws + L.rxs, xs.data(), xs.size() * 4, &off))) return rc;
-        if ((rc = stage_copy(b, ws + L.rslot, sl.data(), sl.size() * 4, &off))) return rc;
+    {   // the wavelet and the tables lie one after the other
+        const size_t tables = s->nrec > 0 ? 1 : 0;
+        const Part part[4] = {{0, wavelet, (size_t)nw * 8},
+                              {L.rrow - L.wavelet, row.data(), tables * row.size() * 4},
+                              {L.rxs - L.wavelet, xs.data(), xs.size() * 4},
+                              {L.rslot - L.wavelet, sl.data(), sl.size() * 4}};
+        const size_t span = tables ? L.rslot - L.wavelet + sl.size() * 4 : (size_t)nw * 8;
+        if (span > 0 && (rc = stage_parts(b, ws + L.wavelet, span, part, 4, &off))) return rc;
     }
 
     ShotEntry e;
@@ -511,7 +547,7 @@ int lb_batch_remove_shot(lb_batch *b, int32_t slot) {
     b->used[(size_t)slot] = 0;
     b->table[(size_t)slot] = ShotEntry();
     BT_TRY(b, hipStreamSynchronize(b->up));   // the staging buffer is free
-    size_t off = 0;
+    size_t off = kStageFlag;
     return rebuild(b, &off);
 }
 

@@ -42,6 +42,7 @@ int validate_scheme(const lb_grid_desc *d);
 // host arrays are checked and converted on the host, device arrays by a
 // kernel whose failure count lands in `scratch`.  Synchronises the stream.
 int upload_c2(hipStream_t s, int precision, int lattice, double ratio, void *dst, const void *c2,
-              lb_dtype t, int on_device, int64_t n, int32_t *scratch);
+              lb_dtype t, int on_device, int64_t n, int32_t *scratch,
+              int32_t *pinned = nullptr);
 
 }  // namespace lbw

@@ -1572,7 +1572,7 @@ int validate_scheme(const lb_grid_desc *d) {
 }
 
 int upload_c2(hipStream_t s, int precision, int lattice, double ratio, void *dst, const void *c2, lb_dtype t,
-              int on_device, int64_t n, int32_t *scratch) {
+              int on_device, int64_t n, int32_t *scratch, int32_t *pinned) {
     const double cmax = lbw::c2_max(lattice, ratio);
     const bool in64 = t == LB_F64;
     if (!on_device) {
@@ -1599,10 +1599,10 @@ int upload_c2(hipStream_t s, int precision, int lattice, double ratio, void *dst
     }
     if (launch_fill_zero(scratch, 256, s) != hipSuccess) return LB_E_HIP;
     if (launch_convert_c2(storage_kind(precision), c2, in64, dst, n, cmax, scratch, s) != hipSuccess) return LB_E_HIP;
-    int32_t bad = 0;
-    if (hipMemcpyAsync(&bad, scratch, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return LB_E_HIP;
+    int32_t local = 0, *bad = pinned ? pinned : &local;
+    if (hipMemcpyAsync(bad, scratch, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return LB_E_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return LB_E_HIP;
-    return bad ? LB_E_RANGE : LB_OK;
+    return *bad ? LB_E_RANGE : LB_OK;
 }
 
 }  // namespace lbw

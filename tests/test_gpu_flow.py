@@ -160,3 +160,30 @@ def test_refined_steps_taken_together(precision, collision, tau, s):
         for other in got[1:]:
             for a, b in zip(got[0], other):
                 np.testing.assert_array_equal(a, b)
+
+
+@pytest.mark.parametrize("nsteps,nrec", [(40, 0), (40, 5), (600_000, 3)])
+def test_batch_uploads_in_one_and_in_parts(nsteps, nrec):
+    """A shot's wavelet and tables go to the device in one copy, or part by
+    part when they are larger than the staging buffer (a wavelet of 600 000
+    times): its first 40 steps are a single grid's."""
+    from paper_1704_03172_amd import lbwave
+    c = case(130, 67, 5, "bgk", 0.5, None, 40)
+    wavelet = np.concatenate([c["wavelet"], np.zeros(nsteps - 40)])
+    rec = c["receivers"][7:7 + nrec]
+    g = lbwave.Grid(130, 67, sponge_width=9, sponge_sigma_max=0.1, trace_capacity=41, max_receivers=max(nrec, 1))
+    g.set_medium(c["c2"])
+    g.set_state(np.zeros((67, 130)))
+    g.set_source(96, 7, c["wavelet"])
+    if nrec:
+        g.record(rec)
+    g.step(40)
+    b = lbwave.Batch(2)
+    slot = b.add(lbwave.shot_desc(130, 67, (96, 7), nsteps, nrec, 9, 0.1), c["c2"], wavelet, rec)
+    b.tick(40)
+    traces = b.remove(slot).cpu().numpy()
+    b.close()
+    if nrec:
+        want = g.traces.cpu().numpy().reshape(nrec, 41)
+        assert np.abs(want).max() > 0
+        np.testing.assert_array_equal(traces[:, :41], want)
