@@ -115,11 +115,11 @@ typedef struct lb_grid lb_grid;
  *                  divides the HBM traffic per step accordingly; the results
  *                  equal those of one step per launch bit for bit.  The
  *                  count depends on the grid: 16 for D2Q5 on large grids
- *                  (FP32 and FP16 storage from 2 M nodes, 12 below; FP64
- *                  from 1.6 M nodes, 8 below) and on the smallest (up to
- *                  32768 nodes), 8 in between, 8 for D2Q9 (FP64 below 0.8 M
- *                  nodes: 6; FP32 up to 32768 nodes: 12); the steps of a
- *                  call are divided evenly over its launches.
+ *                  (FP32 from 2.7 M nodes, FP16 storage from 4.5 M, both 12
+ *                  below; FP64 from 1.6 M nodes, 8 below) and on the smallest
+ *                  (up to 32768 nodes), 8 below 0.8 M nodes, 8 for D2Q9
+ *                  (FP64 below 0.32 M nodes: 6; FP32 up to 32768 nodes: 12);
+ *                  the steps of a call are divided evenly over its launches.
  *                  1 .. 8: at most that many steps per launch.
  *   nbatch         independent shots sharing the grid shape (must be 1).
  *   rho_tape       1: lb_step_n also keeps the pre-collision rho of every
@@ -129,9 +129,10 @@ typedef struct lb_grid lb_grid;
  *                  checkpoints (no ckpt_every needed).  Steps per launch as
  *                  without the tape (the multi-step kernels also write
  *                  rho).  Not with a patch.  0: off.
- *                  LB_F32 D2Q5 grids with rho_tape or ckpt_every evaluate
- *                  the collision in another order than those without: the
- *                  same values to FP32 rounding, not the same bits.
+ *                  LB_F32 grids with rho_tape or ckpt_every evaluate the
+ *                  D2Q5 and the D2Q9 MRT collision in another order than
+ *                  those without: the same values to FP32 rounding, not the
+ *                  same bits.
  */
 typedef struct {
     int32_t nx, ny;

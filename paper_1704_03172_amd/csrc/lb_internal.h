@@ -37,35 +37,38 @@ struct Collision {
                                        // in the arithmetic type)
     double kw = 0.5;                   // D2Q9 weights: w1 = c^2 kw, kw = 1 / (2 + 4r)
     double ratio = 0.0;                // D2Q9 w5 / w1
-    int32_t momentum = 0;              // D2Q5: the equilibrium's momentum written out (step_kind)
+    int32_t written = 0;               // the collision's older form (step_kind)
 };
 
 // Collision kind the forward kernels are instantiated for: 0 BGK, 1 MRT,
 // 2 BGK with omega = 2 (tau = 1/2), whose collision is written as
-// 2 g^eq - g.  D2Q5 with `momentum`: 3 to 5, the same three with the
-// equilibrium of each mover written out, as half storage (which turns a last
-// bit into 2^-11 of a value at every step) and FP32 runs recorded for a
-// gradient (an FP64 result) have it: both keep the values that they have
-// always given.
+// 2 g^eq - g.  With `written` 3 more: the same collision with the equilibrium
+// of each mover and, for MRT, each moment written out, as half storage (which
+// turns a last bit into 2^-11 of a value at every step) and FP32 runs recorded
+// for a gradient (an FP64 result) have it: both keep the values that they have
+// always given.  D2Q9 BGK has one form only.
 // The adjoint keeps Collision::kind.
 inline int step_kind(const Collision &c) {
-    return (c.kind == 1 ? 1 : c.omega == 2.0 ? 2 : 0) + (c.momentum ? 3 : 0);
+    return (c.kind == 1 ? 1 : c.omega == 2.0 ? 2 : 0) + (c.written ? 3 : 0);
 }
 
 // f(std::integral_constant<int, KIND>) for the kind of a launch over storage S
 // and lattice Q.
 template <typename S, int Q, typename F>
 hipError_t for_kind(int kind, F &&f) {
-    if constexpr (Q == 5) {
+    constexpr bool half = sizeof(S) == 2, f32 = sizeof(S) == 4;
+    if constexpr (Q == 5 && (half || f32)) {
         if (kind == 3) return f(std::integral_constant<int, 3>());
-        if (kind == 4) return f(std::integral_constant<int, 4>());
         if (kind == 5) return f(std::integral_constant<int, 5>());
     }
-    if constexpr (Q != 5 || sizeof(S) != 2) {
+    if constexpr (half || f32)
+        if (kind == 4) return f(std::integral_constant<int, 4>());
+    if constexpr (Q != 5 || !half) {
         if (kind == 0) return f(std::integral_constant<int, 0>());
-        if (kind == 1) return f(std::integral_constant<int, 1>());
         if (kind == 2) return f(std::integral_constant<int, 2>());
     }
+    if constexpr (!half)
+        if (kind == 1) return f(std::integral_constant<int, 1>());
     return hipErrorInvalidValue;
 }
 

@@ -34,7 +34,7 @@ __host__ __device__ constexpr int cyv(int i) {
 
 // Rows of the moment matrix of Appendix A (non-conserved rows only are
 // used: D2Q5 k = 3 (e), 4 (pxx); D2Q9 k = 3 (e), 4 (pxx), 5 (eps),
-// 6 (qx), 7 (qy), 8 (pxy)); mrt_apply() has them factored.
+// 6 (qx), 7 (qy), 8 (pxy)); mrt_apply() has D2Q9's factored.
 template <int Q>
 __host__ __device__ constexpr int mrow(int k, int i) {
     if (Q == 5) {
@@ -174,42 +174,60 @@ __device__ inline T geq_rest(const T (&w)[Q], T rho) {
     else return w[0] * rho;
 }
 
-// acc = C d with C = M^-1 S M through the non-conserved moments only (C is
-// symmetric): the rows of mrow() through the sums and differences of opposite
-// populations, 45 operations for D2Q9 where the rows taken one by one cost 130
-// (FP64 MRT on 701 x 899: 8.6 us per step before, 7.6 after).
+// acc = C d with C = M^-1 S M (symmetric) through the non-conserved moments
+// only, row by row.
 template <typename T, int Q, typename C>
-__device__ inline void mrt_apply(const T (&d)[Q], const C &c, T (&acc)[Q]) {
-    if constexpr (Q == 5) {
-        const T x = d[1] + d[3], y = d[2] + d[4];
-        const T re = T(c.srate[3]) * fmaT(T(-4), d[0], x + y), rp = T(c.srate[4]) * (x - y);
-        acc[0] = T(-4) * re;
-        acc[1] = acc[3] = re + rp;
-        acc[2] = acc[4] = re - rp;
-    } else {
-        const T s1 = d[1] + d[3], s2 = d[2] + d[4], s5 = d[5] + d[7], s6 = d[6] + d[8];
-        const T a1 = d[1] - d[3], a2 = d[2] - d[4], a5 = d[5] - d[7], a6 = d[6] - d[8];
-        const T sx = s1 + s2, sd = s5 + s6;
-        const T re = T(c.srate[3]) * fmaT(T(2), sd, fmaT(T(-4), d[0], -sx));
-        const T rp = T(c.srate[4]) * (s1 - s2);
-        const T rs = T(c.srate[5]) * fmaT(T(-2), sx, fmaT(T(4), d[0], sd));
-        const T rx = T(c.srate[6]) * fmaT(T(-2), a1, a5 - a6);
-        const T ry = T(c.srate[7]) * fmaT(T(-2), a2, a5 + a6);
-        const T rxy = T(c.srate[8]) * (s5 - s6);
-        // axis movers: -re - 2 rs +- rp -+ 2 rx (or ry); diagonal ones:
-        // 2 re + rs +- (rx +- ry) +- rxy
-        const T ba = fmaT(T(-2), rs, -re), bd = fmaT(T(2), re, rs);
-        const T bx = ba + rp, by = ba - rp, b5 = bd + rxy, b6 = bd - rxy, p = rx + ry, m = rx - ry;
-        acc[0] = T(4) * (rs - re);
-        acc[1] = fmaT(T(-2), rx, bx);
-        acc[2] = fmaT(T(-2), ry, by);
-        acc[3] = fmaT(T(2), rx, bx);
-        acc[4] = fmaT(T(2), ry, by);
-        acc[5] = b5 + p;
-        acc[6] = b6 - m;
-        acc[7] = b5 - p;
-        acc[8] = b6 + m;
+__device__ inline void mrt_rows(const T (&d)[Q], const C &c, T (&acc)[Q]) {
+    T r[9];
+#pragma unroll
+    for (int k = 3; k < Q; ++k) {
+        T a = T(0);
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+            const int m = mrow<Q>(k, i);
+            if (m != 0) a += T(m) * d[i];
+        }
+        r[k] = T(c.srate[k]) * a;
     }
+#pragma unroll
+    for (int i = 0; i < Q; ++i) {
+        T a = T(0);
+#pragma unroll
+        for (int k = 3; k < Q; ++k) {
+            const int m = mrow<Q>(k, i);
+            if (m != 0) a += T(m) * r[k];
+        }
+        acc[i] = a;
+    }
+}
+
+// The same for D2Q9 through the sums and differences of opposite populations:
+// 45 operations instead of 130 (FP64 MRT on 701 x 899: 8.6 us per step before,
+// 7.6 after).
+template <typename T, typename C>
+__device__ inline void mrt_apply(const T (&d)[9], const C &c, T (&acc)[9]) {
+    const T s1 = d[1] + d[3], s2 = d[2] + d[4], s5 = d[5] + d[7], s6 = d[6] + d[8];
+    const T a1 = d[1] - d[3], a2 = d[2] - d[4], a5 = d[5] - d[7], a6 = d[6] - d[8];
+    const T sx = s1 + s2, sd = s5 + s6;
+    const T re = T(c.srate[3]) * fmaT(T(2), sd, fmaT(T(-4), d[0], -sx));
+    const T rp = T(c.srate[4]) * (s1 - s2);
+    const T rs = T(c.srate[5]) * fmaT(T(-2), sx, fmaT(T(4), d[0], sd));
+    const T rx = T(c.srate[6]) * fmaT(T(-2), a1, a5 - a6);
+    const T ry = T(c.srate[7]) * fmaT(T(-2), a2, a5 + a6);
+    const T rxy = T(c.srate[8]) * (s5 - s6);
+    // axis movers: -re - 2 rs +- rp -+ 2 rx (or ry); diagonal ones:
+    // 2 re + rs +- (rx +- ry) +- rxy
+    const T ba = fmaT(T(-2), rs, -re), bd = fmaT(T(2), re, rs);
+    const T bx = ba + rp, by = ba - rp, b5 = bd + rxy, b6 = bd - rxy, p = rx + ry, m = rx - ry;
+    acc[0] = T(4) * (rs - re);
+    acc[1] = fmaT(T(-2), rx, bx);
+    acc[2] = fmaT(T(-2), ry, by);
+    acc[3] = fmaT(T(2), rx, bx);
+    acc[4] = fmaT(T(2), ry, by);
+    acc[5] = b5 + p;
+    acc[6] = b6 - m;
+    acc[7] = b5 - p;
+    acc[8] = b6 + m;
 }
 
 // Collision of one node: out = g - C (g - g^eq) with the linear equilibrium
@@ -225,7 +243,7 @@ __device__ inline void mrt_apply(const T (&d)[Q], const C &c, T (&acc)[Q]) {
 // tau = 1/2: 16.2 us per step before, 14.2 after; its error 2.2e-6 and 2.0e-6).
 template <typename T, int Q, int KIND, typename C>
 __device__ inline void collide(const T (&g)[Q], T c2, const C &c, T (&out)[Q], T (&w)[Q]) {
-    static_assert(KIND < 3 || Q == 5, "kinds 3 to 5 are D2Q5's");
+    static_assert(KIND < 3 || Q == 5 || KIND == 4, "see step_kind");
     if constexpr (Q == 5 && KIND < 3) {
         weights<T, Q>(c2, c, w);
         const T s1 = g[1] + g[3], s2 = g[2] + g[4], rho = g[0] + (s1 + s2);
@@ -315,7 +333,8 @@ __device__ inline void collide(const T (&g)[Q], T c2, const C &c, T (&out)[Q], T
         for (int i = 0; i < Q; ++i) out[i] = fmaT(-om, d[i], g[i]);
     } else {
         T acc[Q];
-        mrt_apply<T, Q>(d, c, acc);
+        if constexpr (Q == 9 && KIND < 3) mrt_apply<T>(d, c, acc);
+        else mrt_rows<T, Q>(d, c, acc);
 #pragma unroll
         for (int i = 0; i < Q; ++i) out[i] = g[i] - acc[i];
     }
@@ -437,27 +456,7 @@ __device__ inline void adjoint_relax(const T (&m)[Q], const C &coll, T (&nu)[Q])
 #pragma unroll
         for (int i = 0; i < Q; ++i) nu[i] = KIND == 2 ? T(2) * m[i] : T(coll.omega) * m[i];
     } else {
-        T r[9];
-#pragma unroll
-        for (int k = 3; k < Q; ++k) {
-            T a = T(0);
-#pragma unroll
-            for (int i = 0; i < Q; ++i) {
-                const int c = mrow<Q>(k, i);
-                if (c != 0) a += T(c) * m[i];
-            }
-            r[k] = T(coll.srate[k]) * a;
-        }
-#pragma unroll
-        for (int i = 0; i < Q; ++i) {
-            T a = T(0);
-#pragma unroll
-            for (int k = 3; k < Q; ++k) {
-                const int c = mrow<Q>(k, i);
-                if (c != 0) a += T(c) * r[k];
-            }
-            nu[i] = a;
-        }
+        mrt_rows<T, Q>(m, coll, nu);
     }
 }
 

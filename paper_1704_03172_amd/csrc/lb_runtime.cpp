@@ -1534,7 +1534,8 @@ Collision make_collision(const lb_grid_desc *d) {
     Collision c;
     c.kind = d->collision;
     c.omega = 1.0 / d->tau;
-    c.momentum = d->lattice == LB_D2Q5 && (d->precision == LB_F16S || (d->precision == LB_F32 && (d->rho_tape || d->ckpt_every > 0)));
+    c.written = (d->precision == LB_F16S || (d->precision == LB_F32 && (d->rho_tape || d->ckpt_every > 0))) &&
+                (d->lattice == LB_D2Q5 || d->collision == LB_MRT);
     const double *norm = d->lattice == LB_D2Q5 ? kNormD2Q5 : kNormD2Q9;
     for (int k = 0; k < 9; ++k) c.srate[k] = (k >= 3 && k < d->lattice) ? d->s[k] / norm[k] : 0.0;
     c.ratio = d->lattice == LB_D2Q9 ? d->d2q9_ratio : 0.0;
