@@ -30,13 +30,15 @@
 // which a wave cannot be kept from its next bundle by bundles that wait for it.
 //
 // What bounds it: a launch of 16 steps of D2Q5 FP32 BGK at tau = 1/2 over
-// 4096^2 needs 92 us at the HBM peak and 109 us of the vector units (16
-// operations per update); it takes 242 us, 15.1 us per step (30.5 with the
+// 4096^2 needs 92 us at the HBM peak and 68 us of the vector units (10
+// operations per update); it takes 205 us, 12.8 per step (30.5 with the
 // marching kernel it replaced, whose waves recomputed 65 % of their updates and
-// waited on their own dependency chains).  About a third more updates than
-// stored ones (128 columns per strip for 96) and 19 instead of 16 instructions
-// per update bring the vector units' time to 170 us.  2048^2: 6.3 us per step
-// (13.5), 1024^2 3.2 (6.5), 256^2 1.8 (5.9).
+// waited on their own dependency chains).  It issues 21 vector instructions per
+// stored update: a third more updates than stored ones (128 columns per strip
+// for 96), 11 instructions each, and 4 for a step's hand-over and a bundle's
+// loads and stores.  At the 2.16 GHz that the chip then runs at they fill 77 %
+// of the launch, which moves 680 MB.  In calls of 97 steps, the last one alone:
+// 2048^2 5.5 us per step (13.5), 1024^2 2.9 (6.5), 256^2 1.7 (5.9).
 #pragma once
 
 #include "lb_iface.h"
@@ -50,20 +52,25 @@ namespace {
 // block, EU waves per SIMD (the register budget), E further bundles whose c^2
 // the ring keeps.  Wide shapes fill a CU with one block (LDS: two boundaries
 // per wave and the c^2 of W + E bundles); the small one has short bundles, so
-// that a small grid gives every CU some.  Measured (us per step at 4096^2 /
-// 2048^2 / 1024^2, best step count of each):
-//   FP32 D2Q5   V2 R7 W16 15.1 / 6.3 / 3.2 (R8, registers spilled: 17.0 / 6.3 /
-//               3.0 when both were tuned; R6 17.3 / 5.6 / 2.8 and R7 16.8 / 5.8
-//               / 2.8 then), R10 W12 18.7 / 6.8 / 3.1, R16 W8 24.8 / 9.3 / 3.8
-//   FP32 D2Q9   V2 R10 W8 46.0 / 16.9 / 7.1, V2 R7 W8 46.1 / 17.2 / 7.3,
-//               V1 R8 W12 52.4 / 16.9 / 5.7
-//   FP64 D2Q5   V1 R7 W16 36.7 / 11.5 / 4.1, V2 R6 W8 36.5 / 13.0 / 5.5,
-//               V1 R12 W12 38.9 / 12.2 / 5.1
+// that a small grid gives every CU some.  Measured (us per step, best step
+// count of each; the D2Q5 FP32 figures with * before its collision lost the
+// momentum, 16 operations an update):
+//   FP32 D2Q5 at 4096^2 / 2048^2 / 1024^2
+//               V2 R7 W16 14.0 / 5.5 / 2.9, V2 R8 W16 (10 registers spilled)
+//               15.0 / 6.0 / 3.0, V2 R6 W16 with E = 3 14.5 / 5.4 / 2.7;
+//               * V2 R7 W16 16.8 / 5.8 / 2.8, V2 R10 W12 18.7 / 6.8 / 3.1,
+//               V2 R16 W8 24.8 / 9.3 / 3.8
+//   FP32 D2Q9   V2 R10 W8 44.0 / 15.2, V2 R6 W12 46.5 / 13.2, V2 R5 W12 46.7 /
+//               13.7, V1 R7 W16 48.8 / 13.8; small V1 R4 W16 - / - / 5.4
+//   FP64 D2Q5   V1 R7 W16 31.5 / 10.1 / 3.7, with E = 2 31.6 / 9.8 / 3.7
+//               (before: V2 R6 W8 36.5 / 13.0 / 5.5 and V1 R12 W12 38.9 / 12.2 /
+//               5.1 where R7 W16 had 36.7 / 11.5 / 4.1)
 //   FP64 D2Q9 (MRT)  V1 R5 W12 132 / 40.6 / 14.9, V1 R7 W8 136 / 42.6 / 15.8,
 //               V1 R9 W8 134 / 42.7 / 16.1
-//   small, FP32 D2Q5 (512^2 / 256^2 / 128^2)  R4 1.92 / 1.69 / 1.12, R3 2.18 /
-//               1.93 / 1.13, R5 2.20 / 1.83 / 1.26 (before the receivers were
-//               looked up together); the wide shape 2.36 / 2.25 / 1.91
+//   small FP32 D2Q5 at 512^2 / 256^2 / 128^2
+//               V1 R4 W16 1.84 / 1.69 / 1.43, V1 R5 W16 1.86 / 1.82 / 1.49;
+//               * V1 R3 W16 2.18 / 1.93 / 1.13 where R4 had 1.92 / 1.69 / 1.12
+//               (128^2 without receivers), the wide shape 2.36 / 2.25 / 1.91
 template <typename S, int Q, bool SMALL> struct FlowShape {
     static constexpr int V = 2, R = 7, W = 16, EU = 4, E = 0;
 };

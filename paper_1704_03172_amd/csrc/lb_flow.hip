@@ -68,30 +68,34 @@ FlowInfo flow_info(int storage, int q, bool small) {
     return q == 5 ? flow_info_f16_q5(small) : flow_info_f16_q9(small);
 }
 
-// Measured with a 64-node sponge and 64 receivers on square grids of 128^2 to
-// 4096^2 nodes (us per step; small shape / wide one, each at its best step
-// count):
-//   FP32 D2Q5   768^2 2.61 (8 steps) / 2.74 (14)    1024^2 3.47 (8) / 3.23 (12)
-//   FP64 D2Q5   768^2 3.09 (8) / 3.24 (8)           1024^2 4.59 (8) / 4.06 (8)
-//   FP32 D2Q9  1536^2 10.15 (8) / 11.91 (8)         2048^2 17.68 (8) / 16.86 (8)
-//   FP64 D2Q9   768^2 9.63 (6) / 9.68 (6)           1536^2 27.06 (8) / 26.67 (8)
+// Measured with a 64-node sponge and 64 receivers on square grids (us per step
+// in calls of 97 steps; small shape / wide one, each at its best step count):
+//   FP32 D2Q5   512^2 1.84 (8 steps) / 2.20 (16)    768^2 2.48 (8) / 2.50 (12)
+//               1024^2 3.29 (8) / 2.84 (12)
+//   FP64 D2Q5   768^2 2.99 (8) / 2.92 (8)           1024^2 4.40 (8) / 3.70 (8)
+//   FP32 D2Q9   2048^2 14.6 (8) / 15.3 (8)          2400^2 19.1 (8) / 19.2 (8)
+//               2700^2 30.9 (8) / 24.8 (8)
+//   FP64 D2Q9   512^2 3.85 (6) / 4.08 (8)           600^2 4.71 (6) / 4.62 (8)
+//               800^2 6.88 (6) / 6.57 (8)
 // More steps per launch cost halo rows and columns computed twice, fewer cost
 // launches and passes over memory.  Small shape: 16 steps pay while the GPU is
-// not filled by the rows a block stores (FP32 D2Q5 128^2 1.12 at 16 steps,
-// 1.36 at 8; 256^2 1.79 at 8, 1.84 at 12), after that the narrow strips' halo
+// not filled by the rows a block stores (FP32 D2Q5 128^2 1.41 at 16 steps,
+// 1.61 at 8; 256^2 1.67 at 8, 1.78 at 12), after that the narrow strips' halo
 // columns of 8 steps do.  Wide shape: 16 steps need grids whose blocks have
-// many more rows than the 2 x 16 at their head (FP32 D2Q5 1024^2 3.23 at 12
-// steps, 3.56 at 16; 2048^2 6.91 and 6.34; 4096^2 18.6 and 15.1; FP64 D2Q5
-// 1024^2 4.06 at 8, 4.98 at 16; 1536^2 7.93 and 7.51).  D2Q9's and FP64's
-// larger states leave fewer waves per CU, which then wait for each other
-// beyond 8 steps (FP32 D2Q9 4096^2 46.0 at 8 steps, 52.4 at 12).
+// many more rows than the 2 x 16 at their head (FP32 D2Q5 1024^2 2.84 at 12
+// steps, 3.19 at 16; 1600^2 4.23 and 4.57; 1700^2 4.95 and 4.75; 4096^2 17.3
+// and 14.1; half storage 2048^2 7.50 and 7.69; FP64 D2Q5 1024^2 3.70 at 8, 4.36
+// at 16; 1448^2 6.68 and 6.40).  D2Q9's and FP64's larger states leave fewer
+// waves per CU, which then wait for each other beyond 8 steps (FP32 D2Q9
+// 4096^2 43.9 at 8 steps, 53.1 at 12).
 FlowChoice flow_choose(int storage, int q, int64_t nodes) {
     FlowChoice c;
     const bool f64 = storage == ST_F64;
-    c.small = nodes < (q == 9 && !f64 ? 3000000 : 800000);
+    c.small = nodes < (q == 5 ? 800000 : f64 ? 320000 : 5500000);
     if (q == 9) c.steps = !c.small ? 8 : f64 ? 6 : nodes <= 32768 ? 12 : 8;
     else if (c.small) c.steps = nodes <= 32768 ? 16 : 8;
-    else c.steps = f64 ? (nodes < 1600000 ? 8 : 16) : (nodes < 2000000 ? 12 : 16);
+    else if (f64) c.steps = nodes < 1600000 ? 8 : 16;
+    else c.steps = nodes < (storage == ST_F16 ? 4500000 : 2700000) ? 12 : 16;
     return c;
 }
 
