@@ -13,11 +13,10 @@ HBM before the timed region.
 
 Prints ONE JSON line: MLUPS (value), roofline of the dominant kernel (its
 launch duration measured with HIP events as the difference of two runs that
-differ only in the number of multi-step launches, against the rate of the
-vector units, which has the higher floor, and the 8 TB/s HBM peak), a measured device-copy bandwidth, comparison variants (MRT, D2Q9,
-FP64, FP16 storage with its error against an FP64 run, refinement, the 128^2
-pulse), the adjoint and serving measurements and the CPU oracle timed on a
-bounded sample.
+differ only in the number of multi-step launches, against the 8 TB/s HBM peak),
+a measured device-copy bandwidth, comparison variants (MRT, D2Q9, FP64, FP16
+storage with its error against an FP64 run, refinement, the 128^2 pulse), the
+adjoint and serving measurements and the CPU oracle timed on a bounded sample.
 """
 import argparse
 import json
@@ -47,12 +46,12 @@ def steps_per_launch(n, q, precision):
     workload (see steps_per_launch in include/lbwave.h)."""
     nodes = n * n
     if q == 9:
-        return 6 if precision == "f64" and nodes < 800000 else 12 if precision != "f64" and nodes <= 32768 else 8
+        return 6 if precision == "f64" and nodes < 320000 else 12 if precision != "f64" and nodes <= 32768 else 8
     if nodes < 800000:
         return 16 if nodes <= 32768 else 8
     if precision == "f64":
         return 8 if nodes < 1600000 else 16
-    return 12 if nodes < 2000000 else 16
+    return 12 if nodes < (4500000 if precision == "f16s" else 2700000) else 16
 
 
 def launch_plan(nsteps, most):
@@ -195,10 +194,12 @@ def adjoint_bench(torch, lbwave, inputs, n, nshots, nsteps, K=55, tape=True):
            "forward_ms_per_shot": round(t_fwd / nshots * 1e3, 2),
            "adjoint_ms_per_shot": round(t_adj / nshots * 1e3, 2),
            "misfit": float(phi.item()), "gradient_finite": finite}
-    # algorithmic bytes per node and step of the backward launches, three
-    # steps each (D2Q5): lambda in and out 40 B, c^2 4 B and the FP64
-    # gradient read and written 16 B once per launch, the rho of every step 4 B
-    adj_b = (40.0 + 4 + 16) / 3 + 4
+    # algorithmic bytes per node and step of the backward launches (D2Q5, up
+    # to 16 steps on 100 000 nodes or fewer and from 2 M, 8 between): lambda in
+    # and out 40 B, c^2 4 B and the FP64 gradient read and written 16 B once
+    # per launch, the rho of every step 4 B
+    ns_back = min(16 if N <= 100000 or N >= 2000000 else 8, nsteps if tape else K)
+    adj_b = (40.0 + 4 + 16) / ns_back + 4
     if tape:
         out["adjoint_phase_GB_s"] = round(adj_b * N * nsteps / (t_adj / nshots) / 1e9, 1)
     else:
@@ -207,7 +208,7 @@ def adjoint_bench(torch, lbwave, inputs, n, nshots, nsteps, K=55, tape=True):
         ns_rec = min(steps_per_launch(n, 5, "f32"), K)
         out["adjoint_phase_GB_s"] = round((44.0 / ns_rec + 4 + adj_b) * N * nsteps / (t_adj / nshots) / 1e9, 1)
         out["recompute_steps_per_launch"] = ns_rec
-    out["backward_steps_per_launch"] = 3
+    out["backward_steps_per_launch"] = ns_back
     return out
 
 
@@ -498,21 +499,18 @@ def main():
                                "(lattice units), 64-node sponge, Ricker source, 256 receivers",
                    "nx": wl["nx"], "ny": wl["ny"], "lattice": "D2Q5", "collision": "BGK tau=1/2",
                    "steps_timed": steps, "receivers": int(len(wl["receivers"]))},
-        # bound: of the kernel's two floors, that of the vector units (16 FP32
-        # operations per update, unpacked, at 256 CUs x 64 lanes x 2.4 GHz)
-        # lies above the compulsory HBM traffic's (44 B per node per launch at
-        # 8 TB/s)
-        "roofline": {"bound": "valu", "achieved": round(16.0 * nsl * N / kern_s / 1e9, 1),
-                     "peak": round(256 * 64 * 2.4, 1), "unit": "Gop/s",
-                     "frac": round(16.0 * nsl * N / kern_s / (256 * 64 * 2.4e9), 4),
-                     "hbm_achieved_GBs": round(achieved, 1), "hbm_frac": round(achieved / HBM_PEAK_GBS, 4),
+        # bound: of the kernel's two floors, the compulsory HBM traffic (44 B per
+        # node per launch at 8 TB/s) lies above that of the vector units (10
+        # FP32 operations per update, unpacked, at 256 CUs x 64 lanes x 2.4 GHz)
+        "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                     "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": traffic,
                      "traffic_unit": "HBM bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-kernel scaled)",
                      "kernel": "k_flow<float,5,BGK tau=1/2> (%d steps per launch)" % nsl,
                      "algorithmic_bytes_per_launch": bpl * N, "lattice_updates_per_launch": nsl * N,
                      "avg_kernel_us": round(kern_s * 1e6, 3),
                      "hbm_floor_us": round(bpl * N / HBM_PEAK_GBS / 1e3, 3),
-                     "alu_floor_us": round(16.0 * nsl * N / (256 * 64 * 2.4e9) * 1e6, 3)},
+                     "alu_floor_us": round(10.0 * nsl * N / (256 * 64 * 2.4e9) * 1e6, 3)},
         # the bytes a one-step-per-launch path would move per step (44 per
         # node), over the measured time per step: temporal blocking lifts this
         # above the HBM peak

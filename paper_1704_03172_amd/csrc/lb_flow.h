@@ -36,8 +36,9 @@
 // waited on their own dependency chains).  It issues 21 vector instructions per
 // stored update: a third more updates than stored ones (128 columns per strip
 // for 96), 11 instructions each, and 4 for a step's hand-over and a bundle's
-// loads and stores.  At the 2.16 GHz that the chip then runs at they fill 77 %
-// of the launch, which moves 680 MB.  In calls of 97 steps, the last one alone:
+// loads and stores.  At the 2.26 GHz that the chip then runs at they fill 73 %
+// of the launch, whose 1050 MB (halo columns read twice) are 78 % of the rate
+// of a plain copy.  In calls of 97 steps, the last one alone:
 // 2048^2 5.5 us per step (13.5), 1024^2 2.9 (6.5), 256^2 1.7 (5.9).
 #pragma once
 

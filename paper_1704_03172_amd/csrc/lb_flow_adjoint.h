@@ -18,7 +18,7 @@
 // What bounds it: a step of FP32 D2Q5 at tau = 1/2 takes 45 vector operations
 // a node (13 of them the FP64 gradient's), 73 with the nodes of halo columns
 // and head rows; at 2048^2 and 16 steps the vector units are busy for 107 us
-// of a launch's 163, which moves 430 MB.  12.4 us per step, where the kernel
+// of a launch's 163, which moves 740 MB.  12.4 us per step, where the kernel
 // it replaced (three steps a launch, every wave with halo rows of its own)
 // took 24.8; FP64 39.5 and 22.7, D2Q9 FP32 46.1 and 23.7, FP64 87 and 36;
 // 256^2 FP32 6.8 and 3.2.
