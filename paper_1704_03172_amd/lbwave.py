@@ -189,7 +189,8 @@ def validate(**kw):
 
 
 def blocked_steps(**kw):
-    """Most time steps one launch of lb_step_n takes for this descriptor."""
+    """Time steps a launch of a long lb_step_n call can be counted on to take
+    (it may take more; see lb_blocked_steps in include/lbwave.h)."""
     d = make_desc(**kw)
     ns = ctypes.c_int32()
     _check(lib().lb_blocked_steps(ctypes.byref(d), ctypes.byref(ns)), "lb_blocked_steps")
@@ -460,7 +461,7 @@ def shot_desc(nx, ny, src, nsteps, nrec, sponge_width=0, sponge_sigma_max=0.0):
 
 class Batch:
     """Batched executor: many shots advance together, several steps per
-    launch (as lb_blocked_steps gives; steps_per_launch caps it), captured as
+    launch (by the active shots' sizes; steps_per_launch caps it), captured as
     a HIP graph per tick (lb_batch_* calls).
 
     Runs on its own (default-priority) stream so that ticks can be captured.

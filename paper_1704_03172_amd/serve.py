@@ -5,7 +5,7 @@ receivers, step count) arrive over time.  The server keeps every admitted
 shot's state resident in HBM, admits new shots whenever a slot and the memory
 budget allow (footprint = the shot workspace reported by the library plus its
 trace buffer), and advances all active shots together: each tick is k time
-steps in batched launches of several steps each (as lb_blocked_steps gives),
+steps in batched launches of several steps each (by the active shots' sizes),
 replayed from a captured HIP graph.  A shot that reaches its last step stops
 updating inside the tick; once the tick has run, its traces are copied out
 and its slot and memory are freed.
