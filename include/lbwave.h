@@ -129,10 +129,10 @@ typedef struct lb_grid lb_grid;
  *                  checkpoints (no ckpt_every needed).  Steps per launch as
  *                  without the tape (the multi-step kernels also write
  *                  rho).  Not with a patch.  0: off.
- *                  LB_F32 grids with rho_tape or ckpt_every evaluate the
- *                  D2Q5 and the D2Q9 MRT collision in another order than
- *                  those without: the same values to FP32 rounding, not the
- *                  same bits.
+ *                  LB_F32 grids with rho_tape or ckpt_every, and those of up
+ *                  to 2^18 nodes, evaluate the D2Q5 and the D2Q9 MRT collision
+ *                  in another order than the others: the same values to FP32
+ *                  rounding, not the same bits.
  */
 typedef struct {
     int32_t nx, ny;

@@ -361,6 +361,7 @@ int lb_batch_create(const lb_grid_desc *scheme, int32_t max_shots, void *d_works
     b->ssize = lbw::storage_bytes(scheme->precision);
     b->tsize = lbw::compute_bytes(scheme->precision);
     b->coll = lbw::make_collision(scheme);
+    if (scheme->precision == LB_F32) b->coll.written = 0;   // each shot's own
     b->stream = (hipStream_t)stream;
     b->use_graph = use_graph ? 1 : 0;
     b->max_shots = max_shots;
@@ -495,6 +496,7 @@ int lb_batch_add_shot(lb_batch *b, const lb_shot_desc *s, void *d_ws, size_t ws_
     e.sponge_smax = s->sponge_sigma_max;
     e.src_x = s->src_x;
     e.src_y = s->src_y;
+    e.written = b->scheme.precision == LB_F32 && lbw::has_two_forms(&b->scheme) && n <= lbw::kWrittenNodes;
 
     // collision of time 0 (records time 0): pop0 (at rest) -> pop1
     lbw::StepParams p;
@@ -506,6 +508,7 @@ int lb_batch_add_shot(lb_batch *b, const lb_shot_desc *s, void *d_ws, size_t ws_
     p.pstride = e.pstride;
     p.q = b->q;
     p.coll = b->coll;
+    if (e.written) p.coll.written = 1;
     p.sponge_width = e.sponge_width;
     p.sponge_smax = e.sponge_smax;
     p.src_x = e.src_x;

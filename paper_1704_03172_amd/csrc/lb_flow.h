@@ -217,6 +217,7 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
     const bool frho = OUT && p->rho_out != nullptr, fsum = OUT && p->sum != nullptr;
     const int wp = w > 0 ? w - 1 : W - 1, wc = w < W - 1 ? w + 1 : 0;
     const int L = p->sponge_width;
+    const bool written = KIND >= 6 && p->coll.written != 0;
     CollisionT<T> coll;
     if constexpr (KIND % 3 == 0) coll.omega = uniform(T(p->coll.omega));
     if constexpr (KIND % 3 == 1)
@@ -554,7 +555,9 @@ __device__ __attribute__((always_inline)) inline void flow_body(KernFlow p, int 
                     T gj[Q], wt[Q];
 #pragma unroll
                     for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
-                    collide<T, Q, KIND>(gj, cm[j], coll, pj[j], wt);
+                    if constexpr (KIND < 6) collide<T, Q, KIND>(gj, cm[j], coll, pj[j], wt);
+                    else if (written) collide<T, Q, KIND - 3>(gj, cm[j], coll, pj[j], wt);
+                    else collide<T, Q, KIND - 6>(gj, cm[j], coll, pj[j], wt);
                 }
                 if (__builtin_expect((bpost >> r) & 1, 0)) {
                     if ((msrc >> (sh + r)) & 1) {
@@ -716,10 +719,18 @@ hipError_t flow_launch(const FlowParams &p, const FlowBatch &fb, int64_t nblk, i
     using F = FlowShape<S, Q, SMALL>;
     if (nblk < 1 || nblk > (1 << 30)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)nblk), block(F::W * 64);
-    return for_kind<S, Q>(kind, [&](auto kc) {
+    auto go = [&](auto kc) {
         hipLaunchKernelGGL((k_flow<S, Q, decltype(kc)::value, SMALL, OUT>), grid, block, 0, s, p, fb);
         return hipGetLastError();
-    });
+    };
+    if constexpr (sizeof(S) == 4 && !OUT) {   // a batch: the form is each shot's own
+        if (kind == 7) return go(std::integral_constant<int, 7>());
+        if constexpr (Q == 5) {
+            if (kind == 6) return go(std::integral_constant<int, 6>());
+            if (kind == 8) return go(std::integral_constant<int, 8>());
+        }
+    }
+    return for_kind<S, Q>(kind, go);
 }
 
 template <typename S, int Q, bool SMALL>

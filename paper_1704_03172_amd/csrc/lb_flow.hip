@@ -32,6 +32,7 @@ __global__ __launch_bounds__(kAdvBlock) void k_batch_prep(BatchParams bp, int ru
     p.src_x = e.src_x;
     p.src_y = e.src_y;
     p.coll = bp.coll;
+    if (e.written) p.coll.written = 1;
     p.rec = e.rec;
     const int64_t tn = ss.t + 1;
     p.rec.col = tn;
@@ -45,8 +46,7 @@ __global__ __launch_bounds__(kAdvBlock) void k_batch_prep(BatchParams bp, int ru
 }
 
 hipError_t dispatch(int storage, int q, bool small, const FlowParams &p, const FlowBatch &fb, int64_t nblk,
-                    const Collision &coll, hipStream_t s) {
-    const int kind = step_kind(coll);
+                    int kind, hipStream_t s) {
     if (storage == ST_F32) return q == 5 ? launch_flow_f32_q5(small, p, fb, nblk, kind, s) : launch_flow_f32_q9(small, p, fb, nblk, kind, s);
     if (storage == ST_F64) return q == 5 ? launch_flow_f64_q5(small, p, fb, nblk, kind, s) : launch_flow_f64_q9(small, p, fb, nblk, kind, s);
     return q == 5 ? launch_flow_f16_q5(small, p, fb, nblk, kind, s) : launch_flow_f16_q9(small, p, fb, nblk, kind, s);
@@ -107,7 +107,7 @@ void flow_geometry(const FlowInfo &f, int steps, int blocks, FlowParams &p) {
 
 hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipStream_t s) {
     if ((q != 5 && q != 9) || !flow_fits(flow_info(storage, q, small), p)) return hipErrorInvalidValue;
-    return dispatch(storage, q, small, p, FlowBatch(), p.nblk, p.coll, s);
+    return dispatch(storage, q, small, p, FlowBatch(), p.nblk, step_kind(p.coll), s);
 }
 
 namespace {
@@ -186,7 +186,9 @@ hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &
     fb.order = bp.order;
     fb.prefix = bp.prefix;
     fb.nact = bp.nact;
-    return dispatch(storage, q, small, FlowParams(), fb, nblk, bp.coll, s);
+    // FP32 shots of schemes with two forms have each its own
+    const bool own = storage == ST_F32 && (q == 5 || bp.coll.kind == 1);
+    return dispatch(storage, q, small, FlowParams(), fb, nblk, own ? step_kind(bp.coll) % 3 + 6 : step_kind(bp.coll), s);
 }
 
 }  // namespace lbw

@@ -28,6 +28,10 @@ inline double c2_max(int lattice, double ratio) {
 // Collision constants of a scheme descriptor (MRT rates divided by the row
 // norms |M_k|^2 of the moment matrices of Appendix A).
 Collision make_collision(const lb_grid_desc *d);
+// Whether the scheme's collision has two forms, and whether a grid of `nodes`
+// takes the older one (Collision::written).
+bool has_two_forms(const lb_grid_desc *d);
+bool written_form(const lb_grid_desc *d, int64_t nodes);
 
 // Argument checks shared by the trace-misfit entry points (lb_trace_misfit
 // and its variant without workspace): LB_OK, LB_E_INVALID or LB_E_RANGE.

@@ -44,13 +44,18 @@ struct Collision {
 // 2 BGK with omega = 2 (tau = 1/2), whose collision is written as
 // 2 g^eq - g.  With `written` 3 more: the same collision with the equilibrium
 // of each mover and, for MRT, each moment written out, as half storage (which
-// turns a last bit into 2^-11 of a value at every step) and FP32 runs recorded
-// for a gradient (an FP64 result) have it: both keep the values that they have
-// always given.  D2Q9 BGK has one form only.
+// turns a last bit into 2^-11 of a value at every step), FP32 runs recorded for
+// a gradient and small FP32 grids, where a diagnostic such as the sum of rho
+// (both FP64 results) is taken at every step and the cheaper form gains nothing
+// (256^2: 404 us per 200 steps with either), have it: they keep the values that
+// they have always given.  D2Q9 BGK has one form only.  With 6 more the form is
+// each grid's own (batched launches of FP32 shots of all sizes).
 // The adjoint keeps Collision::kind.
 inline int step_kind(const Collision &c) {
     return (c.kind == 1 ? 1 : c.omega == 2.0 ? 2 : 0) + (c.written ? 3 : 0);
 }
+
+constexpr int64_t kWrittenNodes = 1 << 18;
 
 // f(std::integral_constant<int, KIND>) for the kind of a launch over storage S
 // and lattice Q.
@@ -314,6 +319,7 @@ struct ShotEntry {
     int32_t sponge_width = 0;
     double sponge_smax = 0.0;
     int32_t src_x = -1, src_y = -1;
+    int32_t written = 0;                     // the collision's older form (FP32 schemes with two)
 };
 
 // Dynamic state of a shot, advanced on the device.

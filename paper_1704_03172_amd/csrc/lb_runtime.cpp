@@ -1530,12 +1530,18 @@ static void momentum_exact_pair(double ratio, double *kax, double *kdg) {
     *kdg = ratio / (2.0 + 4.0 * ratio);
 }
 
+bool has_two_forms(const lb_grid_desc *d) { return d->lattice == LB_D2Q5 || d->collision == LB_MRT; }
+
+bool written_form(const lb_grid_desc *d, int64_t nodes) {
+    return has_two_forms(d) && (d->precision == LB_F16S ||
+                                (d->precision == LB_F32 && (d->rho_tape || d->ckpt_every > 0 || nodes <= kWrittenNodes)));
+}
+
 Collision make_collision(const lb_grid_desc *d) {
     Collision c;
     c.kind = d->collision;
     c.omega = 1.0 / d->tau;
-    c.written = (d->precision == LB_F16S || (d->precision == LB_F32 && (d->rho_tape || d->ckpt_every > 0))) &&
-                (d->lattice == LB_D2Q5 || d->collision == LB_MRT);
+    c.written = written_form(d, (int64_t)d->nx * d->ny);
     const double *norm = d->lattice == LB_D2Q5 ? kNormD2Q5 : kNormD2Q9;
     for (int k = 0; k < 9; ++k) c.srate[k] = (k >= 3 && k < d->lattice) ? d->s[k] / norm[k] : 0.0;
     c.ratio = d->lattice == LB_D2Q9 ? d->d2q9_ratio : 0.0;

@@ -72,8 +72,8 @@ def test_sum_rho_of_many_steps(n, precision):
 @pytest.mark.parametrize("q,collision,tau,s", [(5, "bgk", 0.5, None), (5, "bgk", 0.8, None), (5, "mrt", 0.5, MRT5),
                                                (9, "mrt", 0.5, MRT9)])
 def test_two_forms_of_the_collision(n, q, collision, tau, s):
-    """An FP32 grid that records for a gradient writes each mover's equilibrium
-    and each moment out, others use the sums of opposite movers: both are the
+    """An FP32 grid that records for a gradient, or of up to 2^18 nodes, writes
+    each mover's equilibrium and each moment out, others use the sums of opposite movers: both are the
     FP64 run to rounding, at one step per launch and at many (the same bits)."""
     from paper_1704_03172_amd import lbwave
     c = case(n, 617, q, collision, tau, s, 25)
@@ -88,6 +88,8 @@ def test_two_forms_of_the_collision(n, q, collision, tau, s):
         g.step(25)
         got[precision, tape, launch] = np.stack([g.field(f).cpu().numpy().astype(np.float64) for f in FIELDS])
     exact = got["f64", 0, 0]
+    if n * 617 <= 1 << 18:
+        np.testing.assert_array_equal(got["f32", 1, 0], got["f32", 0, 0])
     for tape in (0, 1):
         np.testing.assert_array_equal(got["f32", tape, 1], got["f32", tape, 0])
         # a step rounds a population at most 8 times, a field sums q of them
@@ -188,3 +190,29 @@ def test_batch_uploads_in_one_and_in_parts(nsteps, nrec):
         want = g.traces.cpu().numpy().reshape(nrec, 41)
         assert np.abs(want).max() > 0
         np.testing.assert_array_equal(traces[:, :41], want)
+
+
+@pytest.mark.parametrize("q,collision,s", [(5, "bgk", None), (5, "mrt", MRT5), (9, "mrt", MRT9)])
+def test_batched_shots_take_the_form_of_their_size(q, collision, s):
+    """Shots below and above 2^18 nodes in one batch, each with the bits of a
+    grid of its own (the two sizes evaluate the collision in different orders)."""
+    from paper_1704_03172_amd import lbwave
+    b = lbwave.Batch(2, lattice=q, collision=collision, s=s)
+    want, slots = [], []
+    for nx, ny in [(301, 129), (701, 401)]:
+        c = case(nx, ny, q, collision, 0.5, s, 37)
+        g = lbwave.Grid(nx, ny, lattice=q, collision=collision, s=s, sponge_width=9, sponge_sigma_max=0.1, trace_capacity=38,
+                        max_receivers=64)
+        g.set_medium(c["c2"])
+        g.set_state(np.zeros((ny, nx)))
+        g.set_source(96, 7, c["wavelet"])
+        g.record(c["receivers"][:64])
+        g.step(37)
+        want.append(g.traces.cpu().numpy().reshape(64, 38))
+        slots.append(b.add(lbwave.shot_desc(nx, ny, (96, 7), 37, 64, 9, 0.1), c["c2"], c["wavelet"], c["receivers"][:64]))
+    b.tick(37)
+    got = [b.remove(k).cpu().numpy() for k in slots]
+    b.close()
+    for a, w in zip(got, want):
+        assert np.abs(w).max() > 0
+        np.testing.assert_array_equal(a, w)
