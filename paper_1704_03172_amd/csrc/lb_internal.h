@@ -391,6 +391,8 @@ hipError_t launch_restrict(int storage, const InterfaceParams &p,
 // The fine outer-ring states of one coarse step (p.ring_out), see
 // InterfaceParams::ring_out.
 hipError_t launch_prolong_pair(int storage, const InterfaceParams &p, hipStream_t s);
+// The ring-line snapshot (p.snap) of the time of p.coarse.
+hipError_t launch_ring_line(int storage, const InterfaceParams &p, hipStream_t s);
 hipError_t launch_copy(void *dst, const void *src, size_t bytes,
                        hipStream_t s);
 

@@ -721,6 +721,23 @@ __global__ __launch_bounds__(kBlock) void k_restrict(InterfaceParams p) {
     rescale_collide_store_impl<S, KIND>(p, gf, x, y);
 }
 
+// The ring-line snapshot of p.coarse's time, where no coarse launch has kept it.
+template <typename S>
+__global__ __launch_bounds__(kBlock) void k_ring_line(InterfaceParams p) {
+    using T = typename Tr<S>::T;
+    const PatchGeom &g = p.g;
+    const int nh = g.W + 3, nv = g.H + 3;
+    const int t = blockIdx.x * kBlock + threadIdx.x;
+    if (t >= g.nsnap) return;
+    int x, y;
+    if (t < 2 * nh) { x = g.X0 - 1 + t % nh; y = g.Y0 + (t < nh ? 0 : g.H); }
+    else { x = g.X0 + (t - 2 * nh < nv ? 0 : g.W); y = g.Y0 - 1 + (t - 2 * nh) % nv; }
+    T gn[5];
+    pre_at<S, T>(p.coarse, x, y, gn);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) reinterpret_cast<T *>(p.snap)[i * g.nsnap + t] = gn[i];
+}
+
 template <typename S, int KIND>
 __global__ __launch_bounds__(kBlock) void k_prolong_pair(InterfaceParams p) {
     prolong_pair_tile<S, KIND, kBlock>(p, blockIdx.x);
@@ -919,6 +936,15 @@ hipError_t launch_prolong(int storage, const InterfaceParams &p, hipStream_t s) 
 hipError_t launch_prolong_pair(int storage, const InterfaceParams &p, hipStream_t s) {
     LBW_IFACE(k_prolong_pair, (unsigned)ring_tile_blocks<kBlock>(p.g))   // one side's nodes per block
 }
+
+hipError_t launch_ring_line(int storage, const InterfaceParams &p, hipStream_t s) {
+    const dim3 grid(blocks_for(p.g.nsnap));
+    if (storage == ST_F32) hipLaunchKernelGGL((k_ring_line<float>), grid, dim3(kBlock), 0, s, p);
+    else if (storage == ST_F64) hipLaunchKernelGGL((k_ring_line<double>), grid, dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL((k_ring_line<_Float16>), grid, dim3(kBlock), 0, s, p);
+    return hipGetLastError();
+}
+
 hipError_t launch_restrict(int storage, const InterfaceParams &p, hipStream_t s) { LBW_IFACE(k_restrict, blocks_for(p.g.ninner)) }
 
 }  // namespace lbw

@@ -1296,6 +1296,15 @@ int lb_set_raw_state(lb_grid *h, const void *d_in) {
     h->tape_valid = false;
     h->main.prev_pre = hd.main_prev_pre;
     h->fine.prev_pre = hd.fine_prev_pre;
+    if (h->patch && h->collided) {
+        // the next coarse step interpolates in time from the ring-line snapshot
+        // of time t, which the state does not hold: g(t) is read from the
+        // buffer of the step before, as the launch of time t read it
+        InterfaceParams p = iface_base(h);
+        p.coarse = ref_prev(h->main);
+        p.snap = snap_buffer(h, h->t);
+        LB_TRY(h, lbw::launch_ring_line(h->storage, p, h->stream));
+    }
     return LB_OK;
 }
 
