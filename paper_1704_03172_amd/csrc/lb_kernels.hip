@@ -591,11 +591,22 @@ __global__ __launch_bounds__(kBlock) void k_misfit_finalize(const double *partia
     if (threadIdx.x == 0) *phi = 0.5 * s;
 }
 
+// One block adds a time's partials (a row and strip each: 176 k on 4096^2), so
+// a thread has many loads in flight at once: with one at a time the chain took
+// 340 us there, a 50-step call with the sum recorded 131 us per step; 62 so.
 __global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, int64_t n, double *out,
                                                           const GraphTab *gtab) {
     double s = 0.0;
     partial += n * blockIdx.x;   // one time per block
-    for (int64_t i = threadIdx.x; i < n; i += kBlock) s += partial[i];
+    constexpr int U = 32;
+    for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
+        double a[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) a[k] = partial[min(i + k * kBlock, n - 1)];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            if (i + k * kBlock < n) s += a[k];
+    }
     __shared__ double sh[kBlock];
     sh[threadIdx.x] = s;
     __syncthreads();
