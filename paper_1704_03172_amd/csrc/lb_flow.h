@@ -168,25 +168,6 @@ __device__ inline int share_bundles(int R, int ny, int ns, int nbs, int b0, int 
     return total;
 }
 
-// Sum over the lanes, in lane 63: DPP row rotations by 8, 4, 2, 1 (every lane
-// of a row of 16 then holds that row's sum), then row_bcast:15 into rows 1 and
-// 3 and row_bcast:31 into rows 2 and 3.
-template <int CTRL, int ROWS>
-__device__ inline double dpp_add(double a) {
-    const uint64_t u = __builtin_bit_cast(uint64_t, a);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xF, false);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xF, false);
-    return a + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ inline double wave_total(double a) {
-    a = dpp_add<0x128, 0xF>(a);
-    a = dpp_add<0x124, 0xF>(a);
-    a = dpp_add<0x122, 0xF>(a);
-    a = dpp_add<0x121, 0xF>(a);
-    a = dpp_add<0x142, 0xA>(a);
-    return dpp_add<0x143, 0xC>(a);
-}
-
 // MODE 1: the launch writes rho or its sums; 2: the fine steps of a patch (p is
 // the f of a FlowPatchParams).  Kernels of their own: the code costs the
 // others scalar registers, 2 % of a 4096^2 shot.

@@ -142,7 +142,9 @@ struct StepParams {
     int32_t src_x = -1, src_y = -1;    // source node
     double s_n = 0.0;                  // source amplitude of this time
     Receivers rec;
-    double *partial = nullptr;         // per-block sums of rho (nullptr: off)
+    double *sum = nullptr;             // partial sums of rho, one per row and strip of the flowing
+    int32_t sum_v = 1, sum_hx = 0;     // kernel (nullptr: off): its columns per lane, halo columns
+    int32_t sum_nstrip = 0;            // and strips
     void *rho_out = nullptr;           // [ny][nx] pre-collision rho (nullptr: off)
     void *snap = nullptr;              // refinement ring-line snapshot [5][snap_n]
     int32_t snap_x0 = 0, snap_y0 = 0;  // ring line: rows Y0, Y0+H over x in
@@ -367,10 +369,11 @@ hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipS
 // images.
 hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const FlowInfo &f, hipStream_t s);
 hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &bp, int64_t nblk, hipStream_t s);
-int64_t step_blocks(int storage, int32_t nx, int32_t ny, bool pull);
-// Sums of `times` consecutive groups of nblocks partials to out[0 ..], or
+// Sums of `times` (at most kFlowSteps) consecutive groups of n partials to out[0 ..], or
 // (gtab set: a replayed graph) to out[gtab->t0 ..].
-hipError_t launch_sum_finalize(const double *partial, int64_t nblocks, int times,
+// fold: kFlowSteps * kSumFolds doubles of scratch.
+constexpr int kSumFolds = 64;
+hipError_t launch_sum_finalize(const double *partial, int64_t n, int times, double *fold,
                                double *out, const GraphTab *gtab, hipStream_t s);
 // *dst = val on the device, in stream order (before a graph replay).
 hipError_t launch_graph_prime(GraphTab *dst, const GraphTab &val, hipStream_t s);

@@ -28,6 +28,7 @@
 #include "lb_iface.h"
 #include "lb_internal.h"
 #include "lb_node.h"
+#include "lb_rows.h"
 
 #include <algorithm>
 
@@ -233,7 +234,8 @@ __device__ inline void prolong_pair_tile(const InterfaceParams &p, int b) {
 
 // ---- fused step -------------------------------------------------------------
 // One thread's share of the update: V consecutive nodes (x0 .. x0+V-1) of row
-// y.  Returns the FP64 sum of rho over them when p.partial is set.
+// y, of which those from x1 on are another block's.  Their rho goes to rho_row
+// if it is not nullptr.
 template <typename S>
 constexpr bool kIsF64 = sizeof(S) == 8;
 
@@ -297,12 +299,11 @@ __device__ inline void record_wave(const Receivers &rc, int rb, int re, int x0, 
 }
 
 template <typename S, int Q, int KIND, bool PULL>
-__device__ inline double update_tile(const StepParams &p, int x0, int y) {
+__device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, typename Tr<S>::T *rho_row) {
     using T = typename Tr<S>::T;
     constexpr int V = PULL ? Tr<S>::V : 1;
-    const int nx = p.nx, ny = p.ny, x1 = p.x1;
-    double local = 0.0;
-    if (x0 >= x1) return local;
+    const int nx = p.nx, ny = p.ny;
+    if (x0 >= x1) return;
 
     const S *src = reinterpret_cast<const S *>(p.src);
     T g[Q][V];
@@ -368,11 +369,11 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
 #pragma unroll
         for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
         const int x = x0 + j;
-        if ((p.partial || p.rho_out) && x < x1) {
+        if ((p.sum || p.rho_out) && x < x1) {
             T rho = T(0);
 #pragma unroll
             for (int i = 0; i < Q; ++i) rho += gj[i];
-            local += double(rho);
+            if (p.sum) rho_row[j] = rho;
             if (p.rho_out) reinterpret_cast<T *>(p.rho_out)[(int64_t)y * nx + x] = rho;
         }
         T po[Q];
@@ -404,8 +405,11 @@ __device__ inline double update_tile(const StepParams &p, int x0, int y) {
 #pragma unroll
     for (int i = 0; i < Q; ++i)
         store_x<S, V>(dst + i * p.dst_pstride + (int64_t)y * nx, x0, x1, outv[i]);
-    return local;
 }
+
+// Columns of a block that takes the sum of rho: whole strips of `ow` columns.
+__host__ __device__ inline int sum_columns(int columns, int ow) { return columns / ow * ow; }
+
 
 template <typename S, int Q, int KIND, bool PULL>
 __device__ __attribute__((always_inline)) inline void step_body(const StepParams &p) {
@@ -421,20 +425,27 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepParams
         }
     }
     const int y = blockIdx.y - p.pre_rows + p.y0;
-    const int x0 = p.x0 + (blockIdx.x * kStepBlock + threadIdx.x) * V;
-    double local = update_tile<S, Q, KIND, PULL>(p, x0, y);
-
-    if (p.partial) {   // uniform branch: per-block sum of rho in FP64
-        for (int off = 32; off > 0; off >>= 1) local += __shfl_down(local, off, 64);
-        __shared__ double sh[kStepBlock / 64];
-        if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = local;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double s = 0.0;
-#pragma unroll
-            for (int k = 0; k < kStepBlock / 64; ++k) s += sh[k];
-            p.partial[(int64_t)y * gridDim.x + blockIdx.x] = s;
+    // The sum of rho by row and strip, added as the flowing kernel adds it, so
+    // that a time's sum does not depend on the launch that records it.  (A single
+    // step of 4096^2 and its sum: 131 us in FP32 and 254 in FP64; through the
+    // flowing kernel, whose blocks read a third more columns, 206 and 399.)
+    using T = typename Tr<S>::T;
+    __shared__ T rho_row[V * kStepBlock];
+    const bool sums = p.sum != nullptr;
+    const int ow = 64 * p.sum_v - 2 * p.sum_hx, n = sums ? sum_columns(V * kStepBlock, ow) : V * kStepBlock;
+    const int xb = p.x0 + (int)blockIdx.x * n, x1 = sums ? min(xb + n, p.x1) : p.x1, own = (int)threadIdx.x * V;
+    update_tile<S, Q, KIND, PULL>(p, xb + own, x1, y, rho_row + own);
+    if (!sums) return;
+    __syncthreads();
+    const int lane = threadIdx.x & 63;
+    for (int k = threadIdx.x >> 6; k * ow < x1 - xb; k += kStepBlock / 64) {
+        double a = 0.0;
+        for (int j = 0; j < p.sum_v; ++j) {
+            const int c = lane * p.sum_v + j - p.sum_hx;
+            if (c >= 0 && c < ow && k * ow + c < x1 - xb) a += double(rho_row[k * ow + c]);
         }
+        a = wave_total(a);
+        if (lane == 63) p.sum[(int64_t)y * p.sum_nstrip + xb / ow + k] = a;
     }
 }
 
@@ -591,18 +602,16 @@ __global__ __launch_bounds__(kBlock) void k_misfit_finalize(const double *partia
     if (threadIdx.x == 0) *phi = 0.5 * s;
 }
 
-// One block adds a time's partials (a row and strip each: 176 k on 4096^2), so
-// a thread has many loads in flight at once: with one at a time the chain took
-// 340 us there, a 50-step call with the sum recorded 131 us per step; 62 so.
-__global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, int64_t n, double *out,
-                                                          const GraphTab *gtab) {
+// Sum of n partials over a block, in thread 0: a thread's loads come in groups
+// that are in flight together (one at a time they were a chain of 340 us for the
+// 176 k of a time on 4096^2).
+__device__ inline double sum_partials(const double *p, int64_t n) {
+    constexpr int U = 16;
     double s = 0.0;
-    partial += n * blockIdx.x;   // one time per block
-    constexpr int U = 32;
     for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
         double a[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) a[k] = partial[min(i + k * kBlock, n - 1)];
+        for (int k = 0; k < U; ++k) a[k] = p[min(i + k * kBlock, n - 1)];
 #pragma unroll
         for (int k = 0; k < U; ++k)
             if (i + k * kBlock < n) s += a[k];
@@ -614,7 +623,21 @@ __global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, 
         if (threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) out[(gtab ? gtab->t0 : 0) + blockIdx.x] = sh[0];
+    return sh[0];
+}
+
+// Many partials per time: kSumFolds sums of equal shares first (block x of
+// time y).  One CU reads the 4 MB of a time on 4096^2 in FP64 in 80 us.
+__global__ __launch_bounds__(kBlock) void k_sum_fold(const double *partial, int64_t n, double *fold) {
+    const int64_t share = (n + kSumFolds - 1) / kSumFolds, b = share * blockIdx.x;
+    const double s = b < n ? sum_partials(partial + n * blockIdx.y + b, min(share, n - b)) : 0.0;
+    if (threadIdx.x == 0) fold[blockIdx.y * kSumFolds + blockIdx.x] = s;
+}
+
+__global__ __launch_bounds__(kBlock) void k_sum_finalize(const double *partial, int64_t n, double *out,
+                                                          const GraphTab *gtab) {
+    const double s = sum_partials(partial + n * blockIdx.x, n);   // one time per block
+    if (threadIdx.x == 0) out[(gtab ? gtab->t0 : 0) + blockIdx.x] = s;
 }
 
 // The chunk table of a graph replay, copied from the kernel arguments.
@@ -780,8 +803,15 @@ hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
         p.dst_pstride = p.pstride;
     }
     if (p.x0 < 0 || p.y0 < 0 || p.x0 >= p.x1 || p.y0 >= p.y1 || p.x1 > p.nx || p.y1 > p.ny) return hipErrorInvalidValue;
-    dim3 grid((unsigned)(((int64_t)p.x1 - p.x0 + (int64_t)V * kStepBlock - 1) / ((int64_t)V * kStepBlock)),
-              (unsigned)(p.y1 - p.y0));
+    int cols = V * kStepBlock;   // of a block
+    if (p.sum) {   // the whole grid, in strips of whole vectors
+        const int ow = 64 * p.sum_v - 2 * p.sum_hx;
+        if (ow < V || ow % V || ow > cols || p.x1 != p.nx || p.y1 != p.ny || p.x0 || p.y0 || p.prolong_on ||
+            (int64_t)p.sum_nstrip * ow < p.nx)
+            return hipErrorInvalidValue;
+        cols = sum_columns(cols, ow);
+    }
+    dim3 grid((unsigned)(((int64_t)p.x1 - p.x0 + cols - 1) / cols), (unsigned)(p.y1 - p.y0));
     if (p0.prolong_on) {
         const int rows = (int)((ring_tile_blocks<kStepBlock>(p0.iface.g) + grid.x - 1) / grid.x);
         if (!kIsF64<S> && (int64_t)grid.y + rows <= 65535) {
@@ -814,10 +844,6 @@ hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
 }  // namespace
 
 // ---- launchers -------------------------------------------------------------------
-int64_t step_blocks(int storage, int32_t nx, int32_t ny, bool pull) {
-    int V = storage == ST_F32 ? vwidth<float>(pull) : storage == ST_F64 ? vwidth<double>(pull) : vwidth<_Float16>(pull);
-    return (((int64_t)nx + (int64_t)V * kStepBlock - 1) / ((int64_t)V * kStepBlock)) * ny;
-}
 
 hipError_t launch_step(int storage, const StepParams &p, bool pull, hipStream_t s) {
     switch (storage) {
@@ -866,9 +892,17 @@ hipError_t launch_misfit(int storage, const void *traces, const void *obs, void 
     return hipGetLastError();
 }
 
-hipError_t launch_sum_finalize(const double *partial, int64_t nblocks, int times, double *out, const GraphTab *gtab,
+// The shares are a launch more: a single step and its sum take 15.1 us with
+// them and 14.5 without on 700^2 (10.5 k partials), 25.0 and 27.0 on 1024^2 in
+// FP64 (22.5 k).
+hipError_t launch_sum_finalize(const double *partial, int64_t n, int times, double *fold, double *out, const GraphTab *gtab,
                                hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_finalize, dim3((unsigned)times), dim3(kBlock), 0, s, partial, nblocks, out, gtab);
+    if (n > 16384) {
+        hipLaunchKernelGGL(k_sum_fold, dim3(kSumFolds, (unsigned)times), dim3(kBlock), 0, s, partial, n, fold);
+        partial = fold;
+        n = kSumFolds;
+    }
+    hipLaunchKernelGGL(k_sum_finalize, dim3((unsigned)times), dim3(kBlock), 0, s, partial, n, out, gtab);
     return hipGetLastError();
 }
 

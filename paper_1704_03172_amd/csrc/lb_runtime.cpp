@@ -181,9 +181,8 @@ WindowPlan window_plan(const lb_grid_desc *d) {
 struct Layout {
     int64_t pstride = 0, fpstride = 0, wpstride = 0;
     size_t win = 0;
-    int64_t nblocks = 0;
     size_t pop[2] = {0, 0}, c2 = 0, rrow = 0, rxs = 0, rslot = 0;
-    size_t frow = 0, fxs = 0, fslot = 0, partial = 0, scratch = 0, misfit = 0;
+    size_t frow = 0, fxs = 0, fslot = 0, partial = 0, fold = 0, scratch = 0, misfit = 0;
     size_t fpop[2] = {0, 0}, fc2 = 0, snap = 0, ring = 0, total = 0;
     size_t ckpt = 0, seg = 0, lam[2] = {0, 0};
     size_t gtab = 0, tape = 0;
@@ -205,11 +204,9 @@ Layout make_layout(const lb_grid_desc *d) {
     L.rrow = take(((size_t)d->ny + 1) * 4);
     L.rxs = take((size_t)std::max(d->max_receivers, 1) * 4);
     L.rslot = take((size_t)std::max(d->max_receivers, 1) * 4);
-    // partial sums of rho: of time 0, per block of the collide-only launch, and
-    // of the steps of one flowing launch, per row and strip
-    L.nblocks = lbw::step_blocks(storage_kind(d->precision), d->nx, d->ny, false);
-    const int64_t rows = (int64_t)sum_steps(n) * d->ny * flow_plan(d).nstrip;
-    L.partial = take((size_t)std::max(L.nblocks, rows) * 8);
+    // partial sums of rho of the steps of a launch, per row and strip
+    L.partial = take((size_t)sum_steps(n) * d->ny * flow_plan(d).nstrip * 8);
+    L.fold = take((size_t)lbw::kFlowSteps * lbw::kSumFolds * 8);
     L.scratch = take(256);
     L.misfit = take((size_t)lbw::kMisfitMaxBlocks * 8);
     L.gtab = take(sizeof(lbw::GraphTab));
@@ -405,7 +402,15 @@ int launch_update(lb_grid *h, Lattice &g, bool is_main, bool pull, int64_t col, 
     p.dst = g.prevp();
     if (is_main) p.s_n = source_at(h, col);
     if (record) attach_receivers(h, g, p, col);
-    if (sum) p.partial = h->partial;
+    if (sum) {
+        FlowParams f;
+        f.nx = g.nx;
+        lbw::flow_strips(h->flow.f, h->flow.steps, f);
+        p.sum = h->partial;
+        p.sum_v = h->flow.f.V;
+        p.sum_hx = f.hx;
+        p.sum_nstrip = f.nstrip;
+    }
     if (is_main && h->tape_valid) p.rho_out = tape_field(h, col);
     const int64_t base = graph_time(h, p, col);
     if (is_main && h->patch) keep_snapshot(h, p, col);
@@ -422,8 +427,8 @@ int launch_update(lb_grid *h, Lattice &g, bool is_main, bool pull, int64_t col, 
     }
     LB_TRY(h, lbw::launch_step(h->storage, p, pull, h->stream));
     if (sum) {
-        const int64_t nb = lbw::step_blocks(h->storage, g.nx, g.ny, pull);
-        LB_TRY(h, lbw::launch_sum_finalize(h->partial, nb, 1, h->sum_rho + (col - base), p.gtab, h->stream));
+        LB_TRY(h, lbw::launch_sum_finalize(h->partial, (int64_t)p.ny * p.sum_nstrip, 1, (double *)(h->ws + h->L.fold),
+                                           h->sum_rho + (col - base), p.gtab, h->stream));
     }
     g.cur = 1 - g.cur;
     g.prev_pre = pull ? 0 : 1;
@@ -1082,7 +1087,9 @@ int flow_launch(lb_grid *h, int ns) {
     }
     const int64_t base = graph_time(h, p, col);
     LB_TRY(h, lbw::launch_flow(h->storage, h->q, h->flow.small, p, h->stream));
-    if (h->sum_rho) LB_TRY(h, lbw::launch_sum_finalize(h->partial, parts, ns, h->sum_rho + (col - base), p.gtab, h->stream));
+    if (h->sum_rho)
+        LB_TRY(h, lbw::launch_sum_finalize(h->partial, parts, ns, (double *)(h->ws + h->L.fold), h->sum_rho + (col - base),
+                                           p.gtab, h->stream));
     h->main.cur = 1 - h->main.cur;
     h->main.prev_pre = 0;
     h->t = col + ns - 1;
@@ -1090,8 +1097,7 @@ int flow_launch(lb_grid *h, int ns) {
 }
 
 // The next launch of a call with `left` steps to take; *ns: the steps taken.
-// Single steps go through the one-step kernel unless the sum of rho is
-// recorded (see flow_launch).  With a patch a call's last step goes one launch
+// Single steps go through the one-step kernel.  With a patch a call's last step goes one launch
 // at a time: the fields and the saved states are read from the states before.
 int next_launch(lb_grid *h, int64_t left, int *ns) {
     if (h->patch && left > 1 && h->d.steps_per_launch != 1) {
@@ -1099,7 +1105,7 @@ int next_launch(lb_grid *h, int64_t left, int *ns) {
         return *ns > 1 ? window_steps(h, *ns) : one_step(h, true);
     }
     *ns = next_steps(h, left);
-    return *ns > 1 || (h->sum_rho && !h->patch) ? flow_launch(h, *ns) : one_step(h);
+    return *ns > 1 ? flow_launch(h, *ns) : one_step(h);
 }
 
 // Whether lb_step_n may replay graphs now: enabled, no patch (three
