@@ -136,10 +136,6 @@ FlowPlan flow_plan(const lb_grid_desc *d) {
     return pl;
 }
 
-// Most steps of a launch that records the sum of rho: bounds the partials'
-// workspace, one per row, strip and step.
-int sum_steps(int64_t nodes) { return nodes <= (1 << 21) ? lbw::kFlowSteps : 4; }
-
 constexpr int kPairSide = 16;               // smallest fine side for both fine steps in one launch
 constexpr int kWindowSteps = 8;            // most coarse steps taken together
 constexpr int kWindowShare = 3;            // smallest ratio of grid to window nodes
@@ -205,7 +201,8 @@ Layout make_layout(const lb_grid_desc *d) {
     L.rxs = take((size_t)std::max(d->max_receivers, 1) * 4);
     L.rslot = take((size_t)std::max(d->max_receivers, 1) * 4);
     // partial sums of rho of the steps of a launch, per row and strip
-    L.partial = take((size_t)sum_steps(n) * d->ny * flow_plan(d).nstrip * 8);
+    const FlowPlan flow = flow_plan(d);
+    L.partial = take((size_t)flow.steps * d->ny * flow.nstrip * 8);
     L.fold = take((size_t)lbw::kFlowSteps * lbw::kSumFolds * 8);
     L.scratch = take(256);
     L.misfit = take((size_t)lbw::kMisfitMaxBlocks * 8);
@@ -1015,7 +1012,6 @@ namespace {
 int most_steps(const lb_grid *h) {
     if (h->patch) return 1;
     int ns = h->flow.steps;
-    if (h->sum_rho) ns = std::min(ns, sum_steps((int64_t)h->d.nx * h->d.ny));
     if (h->d.steps_per_launch > 0) ns = std::min(ns, h->d.steps_per_launch);
     return ns;
 }
