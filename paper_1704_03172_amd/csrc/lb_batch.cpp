@@ -100,6 +100,7 @@ struct lb_batch {
     std::vector<int32_t> prefix;
     bool small = false;                // shape of the flowing kernel for the active shots
     int steps = 1;                     // steps of a round
+    int64_t nodes = 0;                 // of the active shots
     bool dirty = true;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -213,6 +214,7 @@ int rebuild(lb_batch *b, size_t *off) {
     // at least one block), so that the blocks end at about the same time
     const size_t na = b->order.size();
     const lbw::FlowChoice c = lbw::flow_choose(b->storage, b->q, nodes);
+    b->nodes = nodes;
     b->small = c.small;
     b->steps = c.steps;
     if (b->scheme.steps_per_launch > 0) b->steps = std::min(b->steps, (int)b->scheme.steps_per_launch);
@@ -271,14 +273,15 @@ BatchParams params(const lb_batch *b) {
 }
 
 // k steps of every active shot (a shot stops at its last step), in rounds of
-// b->steps steps.
+// b->steps steps; a round of one step goes through the one-step kernel.
 int enqueue_steps(lb_batch *b, int64_t k) {
     const BatchParams p = params(b);
     const lbw::FlowInfo f = lbw::flow_info(b->storage, b->q, b->small);
     while (k > 0) {
         const int run = (int)std::min<int64_t>(b->steps, k);
         BT_TRY(b, lbw::launch_batch_prep(p, run, b->steps, f, b->stream));
-        BT_TRY(b, lbw::launch_flow_batch(b->storage, b->q, b->small, p, b->prefix.back(), b->stream));
+        if (run > 1) BT_TRY(b, lbw::launch_flow_batch(b->storage, b->q, b->small, p, b->prefix.back(), b->stream));
+        else BT_TRY(b, lbw::launch_step_batch(b->storage, b->q, p, b->prefix.back(), b->nodes, b->stream));
         k -= run;
     }
     return LB_OK;

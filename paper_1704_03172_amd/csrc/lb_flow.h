@@ -704,14 +704,8 @@ hipError_t flow_launch(const FlowParams &p, const FlowBatch &fb, int64_t nblk, i
         hipLaunchKernelGGL((k_flow<S, Q, decltype(kc)::value, SMALL, OUT>), grid, block, 0, s, p, fb);
         return hipGetLastError();
     };
-    if constexpr (sizeof(S) == 4 && !OUT) {   // a batch: the form is each shot's own
-        if (kind == 7) return go(std::integral_constant<int, 7>());
-        if constexpr (Q == 5) {
-            if (kind == 6) return go(std::integral_constant<int, 6>());
-            if (kind == 8) return go(std::integral_constant<int, 8>());
-        }
-    }
-    return for_kind<S, Q>(kind, go);
+    if constexpr (OUT) return for_kind<S, Q>(kind, go);
+    else return for_batch_kind<S, Q>(kind, go);
 }
 
 template <typename S, int Q, bool SMALL>

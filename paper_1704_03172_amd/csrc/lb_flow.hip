@@ -181,14 +181,7 @@ hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const Fl
 hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &bp, int64_t nblk, hipStream_t s) {
     if (nblk <= 0 || bp.nact <= 0) return hipSuccess;
     if (bp.img == nullptr || (q != 5 && q != 9)) return hipErrorInvalidValue;
-    FlowBatch fb;
-    fb.img = bp.img;
-    fb.order = bp.order;
-    fb.prefix = bp.prefix;
-    fb.nact = bp.nact;
-    // FP32 shots of schemes with two forms have each its own
-    const bool own = storage == ST_F32 && (q == 5 || bp.coll.kind == 1);
-    return dispatch(storage, q, small, FlowParams(), fb, nblk, own ? step_kind(bp.coll) % 3 + 6 : step_kind(bp.coll), s);
+    return dispatch(storage, q, small, FlowParams(), flow_batch(bp), nblk, batch_kind(storage, q, bp.coll), s);
 }
 
 }  // namespace lbw

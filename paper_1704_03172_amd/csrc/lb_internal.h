@@ -77,6 +77,23 @@ hipError_t for_kind(int kind, F &&f) {
     return hipErrorInvalidValue;
 }
 
+// The kind of a batched launch: FP32 shots of schemes with two forms have each
+// its own.
+inline int batch_kind(int storage, int q, const Collision &c) {
+    return storage == ST_F32 && (q == 5 || c.kind == 1) ? step_kind(c) % 3 + 6 : step_kind(c);
+}
+template <typename S, int Q, typename F>
+hipError_t for_batch_kind(int kind, F &&f) {
+    if constexpr (sizeof(S) == 4) {
+        if (kind == 7) return f(std::integral_constant<int, 7>());
+        if constexpr (Q == 5) {
+            if (kind == 6) return f(std::integral_constant<int, 6>());
+            if (kind == 8) return f(std::integral_constant<int, 8>());
+        }
+    }
+    return for_kind<S, Q>(kind, f);
+}
+
 // Interface geometry of a factor-2 refinement patch (coarse units).
 struct PatchGeom {
     int32_t X0 = 0, Y0 = 0;            // fine node (0, 0) at coarse (X0, Y0)
@@ -342,6 +359,15 @@ struct BatchParams {
     Collision coll;
 };
 
+inline FlowBatch flow_batch(const BatchParams &bp) {
+    FlowBatch fb;
+    fb.img = bp.img;
+    fb.order = bp.order;
+    fb.prefix = bp.prefix;
+    fb.nact = bp.nact;
+    return fb;
+}
+
 // Launchers (lb_kernels.hip).  All return the launch status.
 hipError_t launch_adjoint(int storage, const AdjointParams &p, hipStream_t s);
 // The shape and the steps per launch of the backward flowing kernel; its
@@ -369,6 +395,9 @@ hipError_t launch_flow(int storage, int q, bool small, const FlowParams &p, hipS
 // images.
 hipError_t launch_batch_prep(const BatchParams &bp, int run, int steps, const FlowInfo &f, hipStream_t s);
 hipError_t launch_flow_batch(int storage, int q, bool small, const BatchParams &bp, int64_t nblk, hipStream_t s);
+// The same for a round of one step, through the one-step kernel; nodes: of the
+// active shots together.
+hipError_t launch_step_batch(int storage, int q, const BatchParams &bp, int64_t nblk, int64_t nodes, hipStream_t s);
 // Sums of `times` (at most kFlowSteps) consecutive groups of n partials to out[0 ..], or
 // (gtab set: a replayed graph) to out[gtab->t0 ..].
 // fold: kFlowSteps * kSumFolds doubles of scratch.

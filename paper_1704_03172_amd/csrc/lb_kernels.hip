@@ -461,6 +461,59 @@ __global__ __launch_bounds__(kStepBlock) void k_step_graph(StepParams p) {
     step_body<S, Q, KIND, true>(q);
 }
 
+// One step of every active shot of a batch, from its params image of the round.
+// `per` blocks stand for each of the flowing kernel's shares, and go through the
+// shot's tiles in turn.  (Two shots of 4096^2: 263 us a step with a tile per
+// block, 283 and 304 with 4 and 16; 370 through the flowing kernel, whose blocks
+// read a third more columns.)
+template <typename S, int Q, int KIND>
+__global__ __launch_bounds__(kStepBlock) void k_step_batch(FlowBatch fb, int per) {
+    constexpr int V = Tr<S>::V;
+    const int share = blockIdx.x / per;
+    int lo = 0, hi = fb.nact - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (fb.prefix[mid] <= share) lo = mid; else hi = mid - 1;
+    }
+    lo = __builtin_amdgcn_readfirstlane(lo);
+    const auto &f = *(const __attribute__((address_space(4))) FlowParams *)(fb.img + __builtin_amdgcn_readfirstlane(fb.order[lo]));
+    if (f.nrun < 1) return;
+    StepParams p;
+    p.src = f.src;
+    p.dst = f.dst;
+    p.c2 = f.c2;
+    p.nx = f.nx;
+    p.ny = f.ny;
+    p.pstride = p.dst_pstride = f.pstride;
+    p.coll.omega = f.coll.omega;
+    for (int k = 3; k < Q; ++k) p.coll.srate[k] = f.coll.srate[k];
+    p.coll.kax = f.coll.kax;
+    p.coll.kdg = f.coll.kdg;
+    p.coll.kw = f.coll.kw;
+    p.coll.ratio = f.coll.ratio;
+    p.sponge_width = f.sponge_width;
+    p.sponge_smax = f.sponge_smax;
+    p.src_x = f.src_x;
+    p.src_y = f.src_y;
+    p.s_n = f.s[0];
+    p.rec.row_ptr = f.rec.row_ptr;
+    p.rec.xs = f.rec.xs;
+    p.rec.slot = f.rec.slot;
+    p.rec.traces = f.rec.traces;
+    p.rec.nslots = f.rec.nslots;
+    p.rec.what = f.rec.what;
+    p.rec.cap = f.rec.cap;
+    p.rec.col = f.rec.col;
+    const int bx = (f.nx + V * kStepBlock - 1) / (V * kStepBlock), first = __builtin_amdgcn_readfirstlane(fb.prefix[lo]) * per;
+    const int64_t tiles = (int64_t)bx * f.ny, blocks = (int64_t)__builtin_amdgcn_readfirstlane(fb.prefix[lo + 1]) * per - first;
+    for (int64_t t = blockIdx.x - first; t < tiles; t += blocks) {
+        const int y = (int)(t / bx), x0 = ((int)(t - (int64_t)y * bx) * kStepBlock + (int)threadIdx.x) * V;
+        if constexpr (KIND < 6) update_tile<S, Q, KIND, true>(p, x0, f.nx, y, nullptr);
+        else if (f.coll.written) update_tile<S, Q, KIND - 3, true>(p, x0, f.nx, y, nullptr);
+        else update_tile<S, Q, KIND - 6, true>(p, x0, f.nx, y, nullptr);
+    }
+}
+
 // ---- discrete adjoint (gradient of the trace misfit w.r.t. c^2) -----------------
 // Backward step n: mu(x) = (1 - sigma(x)) lambda(n+1)(x + c_i) (transpose of
 // the pull), nu = C mu (C symmetric; its conserved rows drop out of every
@@ -852,6 +905,27 @@ hipError_t launch_step(int storage, const StepParams &p, bool pull, hipStream_t 
     case ST_F16: return step_dispatch<_Float16>(p, pull, s);
     }
     return hipErrorInvalidValue;
+}
+
+template <typename S, int Q>
+static hipError_t step_batch(const FlowBatch &fb, int64_t nblk, int64_t nodes, int kind, hipStream_t s) {
+    const int64_t tile = Tr<S>::V * kStepBlock;   // about a tile per block
+    const int per = (int)std::max<int64_t>(1, std::min<int64_t>(256, (nodes / tile + nblk - 1) / nblk));
+    return for_batch_kind<S, Q>(kind, [&](auto kc) {
+        hipLaunchKernelGGL((k_step_batch<S, Q, decltype(kc)::value>), dim3((unsigned)(nblk * per)), dim3(kStepBlock), 0, s, fb,
+                           per);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_step_batch(int storage, int q, const BatchParams &bp, int64_t nblk, int64_t nodes, hipStream_t s) {
+    if (nblk <= 0 || bp.nact <= 0) return hipSuccess;
+    if (bp.img == nullptr || (q != 5 && q != 9) || nblk > (1 << 22)) return hipErrorInvalidValue;
+    const FlowBatch fb = flow_batch(bp);
+    const int kind = batch_kind(storage, q, bp.coll);
+    if (storage == ST_F32) return q == 5 ? step_batch<float, 5>(fb, nblk, nodes, kind, s) : step_batch<float, 9>(fb, nblk, nodes, kind, s);
+    if (storage == ST_F64) return q == 5 ? step_batch<double, 5>(fb, nblk, nodes, kind, s) : step_batch<double, 9>(fb, nblk, nodes, kind, s);
+    return q == 5 ? step_batch<_Float16, 5>(fb, nblk, nodes, kind, s) : step_batch<_Float16, 9>(fb, nblk, nodes, kind, s);
 }
 
 hipError_t launch_adjoint(int storage, const AdjointParams &p, hipStream_t s) {
