@@ -54,6 +54,17 @@ def steps_per_launch(n, q, precision):
     return 12 if nodes < (4500000 if precision == "f16s" else 2700000) else 16
 
 
+def backward_steps_per_launch(n, q):
+    """Most backward steps lb_adjoint takes per launch on an n x n grid."""
+    return 16 if q == 5 and (n * n <= 100000 or n * n >= 2000000) else 8
+
+
+def even_steps(m, most):
+    """Steps of the next launch when m are to be taken by as few launches of up
+    to `most` as needed, of about equal length, as the library divides them."""
+    return 1 if m <= 1 else -(-m // -(-m // most))
+
+
 def launch_plan(nsteps, most):
     """{steps per launch: launches} of one lb_step_n(nsteps) call on a grid
     without patch or checkpoints, as the library takes it: as few launches of
@@ -61,8 +72,7 @@ def launch_plan(nsteps, most):
     plan = {}
     k = 0
     while k < nsteps:
-        m = nsteps - k - 1
-        ns = 1 if m <= 1 else -(-m // -(-m // most))
+        ns = even_steps(nsteps - k - 1, most)
         plan[ns] = plan.get(ns, 0) + 1
         k += ns
     return plan
@@ -194,19 +204,21 @@ def adjoint_bench(torch, lbwave, inputs, n, nshots, nsteps, K=55, tape=True):
            "forward_ms_per_shot": round(t_fwd / nshots * 1e3, 2),
            "adjoint_ms_per_shot": round(t_adj / nshots * 1e3, 2),
            "misfit": float(phi.item()), "gradient_finite": finite}
-    # algorithmic bytes per node and step of the backward launches (D2Q5, up
-    # to 16 steps on 100 000 nodes or fewer and from 2 M, 8 between): lambda in
+    # algorithmic bytes per node and step of the backward launches: lambda in
     # and out 40 B, c^2 4 B and the FP64 gradient read and written 16 B once
     # per launch, the rho of every step 4 B
-    ns_back = min(16 if N <= 100000 or N >= 2000000 else 8, nsteps if tape else K)
-    adj_b = (40.0 + 4 + 16) / ns_back + 4
+    m = nsteps if tape else K
+    most = backward_steps_per_launch(n, 5)
+    ns_back, launches = even_steps(m, most), -(-m // most)
+    adj_b = (40.0 + 4 + 16) * launches / m + 4
     if tape:
         out["adjoint_phase_GB_s"] = round(adj_b * N * nsteps / (t_adj / nshots) / 1e9, 1)
     else:
         # plus the recompute (44 B per ns-step launch and the 4-byte rho
         # field of each step), through the rho-writing kernel
-        ns_rec = min(steps_per_launch(n, 5, "f32"), K)
-        out["adjoint_phase_GB_s"] = round((44.0 / ns_rec + 4 + adj_b) * N * nsteps / (t_adj / nshots) / 1e9, 1)
+        most = steps_per_launch(n, 5, "f32")
+        ns_rec = even_steps(K, most)
+        out["adjoint_phase_GB_s"] = round((44.0 * -(-K // most) / K + 4 + adj_b) * N * nsteps / (t_adj / nshots) / 1e9, 1)
         out["recompute_steps_per_launch"] = ns_rec
     out["backward_steps_per_launch"] = ns_back
     return out

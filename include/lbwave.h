@@ -131,8 +131,10 @@ typedef struct lb_grid lb_grid;
  *                  rho).  Not with a patch.  0: off.
  *                  LB_F32 grids with rho_tape or ckpt_every, and those of up
  *                  to 2^18 nodes, evaluate the D2Q5 and the D2Q9 MRT collision
- *                  in another order than the others: the same values to FP32
- *                  rounding, not the same bits.
+ *                  in another order than the others (batched shots by their
+ *                  own size): the same values to FP32 rounding, not the same
+ *                  bits.  Traces that are to match such a run's bit for bit
+ *                  come from a grid with rho_tape or ckpt_every too.
  */
 typedef struct {
     int32_t nx, ny;
@@ -168,12 +170,13 @@ void lb_default_desc(lb_grid_desc *d);
  * lb_create_grid would return for it. */
 int lb_validate_desc(const lb_grid_desc *d);
 
-/* Time steps that a kernel launch of a long lb_step_n call can be counted on
- * to take for a grid with this descriptor (temporal blocking; the launches
- * take at least as many, see steps_per_launch): 3 to 8 by lattice, collision,
- * precision and size (1 for D2Q9 with FP16 storage), at most
- * steps_per_launch; 1 with a patch.  No GPU needed.  Returns LB_OK and
- * writes *ns, or the error lb_validate_desc gives (LB_E_INVALID for NULL). */
+/* Time steps per kernel launch that can be counted on for a grid with this
+ * descriptor (temporal blocking): an lb_step_n call of n steps takes at most
+ * ceil((n - 1) / *ns) launches and one (more where checkpoints fall between
+ * them).  A fixed table by lattice, collision, precision and size: 3 to 8 (1 for
+ * D2Q9 with FP16 storage), at most steps_per_launch; 1 with a patch.  The
+ * launches may take more (see steps_per_launch).  No GPU needed.  Returns LB_OK
+ * and writes *ns, or the error lb_validate_desc gives (LB_E_INVALID for NULL). */
 int lb_blocked_steps(const lb_grid_desc *d, int32_t *ns);
 
 /* Device bytes the workspace of a grid with this descriptor needs
@@ -239,9 +242,11 @@ int lb_record_sum_rho(lb_grid *h, double *d_sum);
  * return.  The first call after lb_set_state also performs the collision of
  * time 0.  Every launch fuses pull-stream, collision, source, sponge and
  * recording; a launch takes several steps (see steps_per_launch), and the
- * last launch of each call takes one.  A coarse step of a patch takes three
- * launches (the coarse step with the interface
- * work, then the two fine sub-steps). */
+ * last launch of each call takes one.  With a patch up to eight coarse steps
+ * share one launch over the coarse grid, and each takes two more (the coarse
+ * nodes around the patch with the interface work, and both fine sub-steps); a
+ * call's last coarse step takes three (the coarse step with the interface work,
+ * then the fine sub-steps one by one). */
 int lb_step_n(lb_grid *h, int64_t n);
 
 /* Graph replay of lb_step_n, for grids whose steps are too short to hide

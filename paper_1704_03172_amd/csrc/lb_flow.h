@@ -54,24 +54,25 @@ namespace {
 // the ring keeps.  Wide shapes fill a CU with one block (LDS: two boundaries
 // per wave and the c^2 of W + E bundles); the small one has short bundles, so
 // that a small grid gives every CU some.  Measured (us per step, best step
-// count of each; the D2Q5 FP32 figures with * before its collision lost the
-// momentum, 16 operations an update):
-//   FP32 D2Q5 at 4096^2 / 2048^2 / 1024^2
-//               V2 R7 W16 14.0 / 5.5 / 2.9, V2 R8 W16 (10 registers spilled)
-//               15.0 / 6.0 / 3.0, V2 R6 W16 with E = 3 14.5 / 5.4 / 2.7;
-//               * V2 R7 W16 16.8 / 5.8 / 2.8, V2 R10 W12 18.7 / 6.8 / 3.1,
+// count of each), at 4096^2 / 2048^2 / 1024^2 where no size is given:
+//   FP32 D2Q5   V2 R7 W16 14.0 / 5.5 / 2.9, V2 R8 W16 (10 registers spilled)
+//               15.0 / 6.0 / 3.0, V2 R6 W16 with E = 3 14.5 / 5.4 / 2.7
+//   FP32 D2Q5 with the collision written out (step_kind), 16 operations for 10
+//               V2 R7 W16 16.8 / 5.8 / 2.8, V2 R10 W12 18.7 / 6.8 / 3.1,
 //               V2 R16 W8 24.8 / 9.3 / 3.8
 //   FP32 D2Q9   V2 R10 W8 44.0 / 15.2, V2 R6 W12 46.5 / 13.2, V2 R5 W12 46.7 /
 //               13.7, V1 R7 W16 48.8 / 13.8; small V1 R4 W16 - / - / 5.4
 //   FP64 D2Q5   V1 R7 W16 31.5 / 10.1 / 3.7, with E = 2 31.6 / 9.8 / 3.7
-//               (before: V2 R6 W8 36.5 / 13.0 / 5.5 and V1 R12 W12 38.9 / 12.2 /
-//               5.1 where R7 W16 had 36.7 / 11.5 / 4.1)
+//   FP64 D2Q5 with the collision written out, as no FP64 grid has it now
+//               V1 R7 W16 36.7 / 11.5 / 4.1, V2 R6 W8 36.5 / 13.0 / 5.5,
+//               V1 R12 W12 38.9 / 12.2 / 5.1
 //   FP64 D2Q9 (MRT)  V1 R5 W12 132 / 40.6 / 14.9, V1 R7 W8 136 / 42.6 / 15.8,
 //               V1 R9 W8 134 / 42.7 / 16.1
 //   small FP32 D2Q5 at 512^2 / 256^2 / 128^2
-//               V1 R4 W16 1.84 / 1.69 / 1.43, V1 R5 W16 1.86 / 1.82 / 1.49;
-//               * V1 R3 W16 2.18 / 1.93 / 1.13 where R4 had 1.92 / 1.69 / 1.12
-//               (128^2 without receivers), the wide shape 2.36 / 2.25 / 1.91
+//               V1 R4 W16 1.84 / 1.69 / 1.43, V1 R5 W16 1.86 / 1.82 / 1.49
+//   the same with the collision written out (128^2 without receivers)
+//               V1 R4 W16 1.92 / 1.69 / 1.12, V1 R3 W16 2.18 / 1.93 / 1.13, the
+//               wide shape 2.36 / 2.25 / 1.91
 template <typename S, int Q, bool SMALL> struct FlowShape {
     static constexpr int V = 2, R = 7, W = 16, EU = 4, E = 0;
 };

@@ -43,18 +43,24 @@ struct Collision {
 // Collision kind the forward kernels are instantiated for: 0 BGK, 1 MRT,
 // 2 BGK with omega = 2 (tau = 1/2), whose collision is written as
 // 2 g^eq - g.  With `written` 3 more: the same collision with the equilibrium
-// of each mover and, for MRT, each moment written out, as half storage (which
-// turns a last bit into 2^-11 of a value at every step), FP32 runs recorded for
-// a gradient and small FP32 grids, where a diagnostic such as the sum of rho
-// (both FP64 results) is taken at every step and the cheaper form gains nothing
-// (256^2: 404 us per 200 steps with either), have it: they keep the values that
-// they have always given.  D2Q9 BGK has one form only.  With 6 more the form is
+// of each mover and, for MRT, each moment written out.  Half storage has it (the
+// storage turns a last bit into 2^-11 of a value at every step), and so have
+// FP32 runs recorded for a gradient and FP32 grids of up to kWrittenNodes: what
+// they hold in FP64 (the gradient, the sum of rho) keeps its values, which the
+// shorter form moves by 1e-6 and 4e-7, and a small grid has the same bits
+// whatever it records.  Larger grids have the shorter form, which is nearer to
+// 64 bits (4096^2, 400 steps: 1.1e-6 against 1.6e-6; MRT with a patch on 2048^2
+// 3.7e-7 against 1.5e-6).  D2Q9 BGK has one form only.  With 6 more the form is
 // each grid's own (batched launches of FP32 shots of all sizes).
 // The adjoint keeps Collision::kind.
 inline int step_kind(const Collision &c) {
     return (c.kind == 1 ? 1 : c.omega == 2.0 ? 2 : 0) + (c.written ? 3 : 0);
 }
 
+// Where the line lies (us per step, written out / shorter): BGK 256^2 1.75 / 1.71,
+// 512^2 1.91 / 1.87, 1024^2 2.94 / 2.71, 2048^2 6.4 / 5.7, 4096^2 16.6 / 14.3; MRT
+// 256^2 1.95 / 1.78, 512^2 2.18 / 1.96, 1024^2 4.11 / 3.04; D2Q9 MRT 256^2 3.29 /
+// 2.75, 512^2 4.14 / 3.53: below it BGK, the usual collision, gains 2 %.
 constexpr int64_t kWrittenNodes = 1 << 18;
 
 // f(std::integral_constant<int, KIND>) for the kind of a launch over storage S

@@ -33,11 +33,12 @@ using lbw::storage_kind;
 
 double c2_max(const lb_grid_desc *d) { return lbw::c2_max(d->lattice, d->d2q9_ratio); }
 
-// Steps per launch that lb_blocked_steps promises: `near` on any grid, `far`
-// on grids of a width and height that allow it and (unless steps_per_launch
-// asks for it) with at least `fill` pieces of 20 rows and `width` columns; at
-// most steps_per_launch.  The flowing kernel takes at least as many on every
-// grid (up to kFlowSteps where no cap is set).
+// Steps per launch that lb_blocked_steps promises, a fixed table of the interface
+// and no description of the kernels: `near` on any grid, `far` on grids whose
+// width is a multiple of `cols`, that are tall enough and (unless
+// steps_per_launch asks for it) that have at least `fill` pieces of 20 rows and
+// `width` columns; at most steps_per_launch.  The launches' own bound
+// (most_steps) is at least that on every grid (a CPU test compares the two).
 int promised_steps(const lb_grid_desc *d) {
     const bool q5 = d->lattice == LB_D2Q5, mrt = d->collision == LB_MRT;
     int near, far, cols, lanes;   // cols: columns the width is a multiple of; lanes: columns of a lane
@@ -1104,8 +1105,8 @@ int next_launch(lb_grid *h, int64_t left, int *ns) {
     return *ns > 1 ? flow_launch(h, *ns) : one_step(h);
 }
 
-// Whether lb_step_n may replay graphs now: enabled, no patch (three
-// launches per coarse step with interface work), no checkpoints (their
+// Whether lb_step_n may replay graphs now: enabled, no patch (launches with
+// interface work, whose buffers alternate by time), no checkpoints (their
 // saves depend on the time) and a stream of the caller's (the null stream
 // cannot be captured).
 bool graph_ok(const lb_grid *h) {
