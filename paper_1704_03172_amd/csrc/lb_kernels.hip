@@ -249,9 +249,7 @@ template <typename T, int Q, int V>
 __device__ inline void record_wave(const Receivers &rc, int rb, int re, int x0, int x1, const T (&g)[Q][V], const T (&c2)[V]) {
     const int lane = threadIdx.x & 63, m = __builtin_popcountll(__ballot(true));
     const int xa = __builtin_amdgcn_readfirstlane(x0), xe = min(xa + m * V, x1);
-    // a short end of a row, or states that leave no registers (D2Q9 of half
-    // storage: 138 instead of 118)
-    if (V * Q > 64 || m < 16) {
+    if (m < 16) {   // a short end of a row
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             T gj[Q];
@@ -360,7 +358,12 @@ __device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, t
         rb = p.rec.row_ptr[y];
         re = p.rec.row_ptr[y + 1];
     }
-    if (rb < re) record_wave<T, Q, V>(p.rec, rb, re, x0, x1, g, c2v);
+    // Registers are short for the 8 x 9 populations of D2Q9 with half storage:
+    // its nodes search for themselves as they are updated (2300^2: 57 us per
+    // step, 62 with a search before the updates)
+    constexpr bool by_node = V * Q > 64;
+    if constexpr (!by_node)
+        if (rb < re) record_wave<T, Q, V>(p.rec, rb, re, x0, x1, g, c2v);
 
     S outv[Q][V];
 #pragma unroll
@@ -369,6 +372,8 @@ __device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, t
 #pragma unroll
         for (int i = 0; i < Q; ++i) gj[i] = g[i][j];
         const int x = x0 + j;
+        if constexpr (by_node)
+            if (rb < re && x < x1) record_node<T, Q>(p.rec, rb, re, x, gj, c2v[j]);
         if ((p.sum || p.rho_out) && x < x1) {
             T rho = T(0);
 #pragma unroll
