@@ -6,6 +6,7 @@ buffers) and the stream.  There is no CPU fallback: if the library is not
 built, importing the binding's entry points raises.
 """
 import collections
+import contextlib
 import ctypes
 import os
 
@@ -198,7 +199,12 @@ def blocked_steps(**kw):
 
 
 class Grid:
-    """One lattice (optionally with a refinement patch) on one HIP stream."""
+    """One lattice (optionally with a refinement patch) on one HIP stream.
+
+    Tensors passed in and returned belong to the caller's current stream: where
+    that is not the grid's, each call that reads or fills some is ordered after
+    the caller's work so far and before its later work, without a wait on the
+    host.  step() is not: traces and sums are complete after sync()."""
 
     def __init__(self, nx, ny, device=None, stream=None, **kw):
         import torch
@@ -217,9 +223,10 @@ class Grid:
         self.workspace = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
         self.stream = torch.cuda.current_stream(self.device) if stream is None else stream
         h = ctypes.c_void_p()
-        _check(L.lb_create_grid(ctypes.byref(self.desc), ctypes.c_void_p(self.workspace.data_ptr()),
-                                ctypes.c_size_t(int(nbytes)), ctypes.c_void_p(self.stream.cuda_stream),
-                                ctypes.byref(h)), "lb_create_grid")
+        with self._ordered():
+            _check(L.lb_create_grid(ctypes.byref(self.desc), ctypes.c_void_p(self.workspace.data_ptr()),
+                                    ctypes.c_size_t(int(nbytes)), ctypes.c_void_p(self.stream.cuda_stream),
+                                    ctypes.byref(h)), "lb_create_grid")
         self._h = h
         self.traces = None
         self.sum_rho = None
@@ -230,6 +237,20 @@ class Grid:
             self.fine_shape = (2 * H + 1, 2 * W + 1)
 
     # ---- marshalling helpers ------------------------------------------------
+    @contextlib.contextmanager
+    def _ordered(self):
+        """The grid's work enqueued inside runs between the caller's before and
+        after it."""
+        cur = self._torch.cuda.current_stream(self.device)
+        if cur.cuda_stream == self.stream.cuda_stream:
+            yield
+            return
+        self.stream.wait_stream(cur)
+        try:
+            yield
+        finally:
+            cur.wait_stream(self.stream)
+
     def _arg(self, a, keep):
         """(pointer, dtype code, on_device) for a numpy array or torch tensor."""
         torch = self._torch
@@ -260,7 +281,8 @@ class Grid:
         keep = []
         p, t, dev = self._arg(c2, keep)
         fn = lib().lb_set_medium_fine if fine else lib().lb_set_medium
-        _check(fn(self.handle, p, t, dev), "lb_set_medium")
+        with self._ordered():
+            _check(fn(self.handle, p, t, dev), "lb_set_medium")
 
     def set_state(self, rho, jx=None, jy=None, fine=False):
         keep = []
@@ -270,7 +292,8 @@ class Grid:
         if (jx is not None and tx != t) or (jy is not None and ty != t):
             raise TypeError("rho, jx, jy must share one dtype")
         fn = lib().lb_set_state_fine if fine else lib().lb_set_state
-        _check(fn(self.handle, pr, px, py, t, dev), "lb_set_state")
+        with self._ordered():
+            _check(fn(self.handle, pr, px, py, t, dev), "lb_set_state")
 
     def set_source(self, x, y, wavelet):
         w = np.ascontiguousarray(wavelet, dtype=np.float64)
@@ -294,15 +317,17 @@ class Grid:
         nf = bin(what).count("1")
         self.traces = torch.zeros((nf, nrec, self.trace_capacity), dtype=self.dtype, device=self.device)
         self.trace_fields = tuple(f for f in FIELD_ORDER if what & FIELD[f])
-        _check(lib().lb_record(self.handle, rec.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), nrec,
-                               ctypes.c_void_p(self.traces.data_ptr()), what), "lb_record")
+        with self._ordered():
+            _check(lib().lb_record(self.handle, rec.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), nrec,
+                                   ctypes.c_void_p(self.traces.data_ptr()), what), "lb_record")
         return self.traces
 
     def record_sum_rho(self):
         torch = self._torch
         self.sum_rho = torch.zeros(self.trace_capacity, dtype=torch.float64, device=self.device)
-        _check(lib().lb_record_sum_rho(self.handle, ctypes.c_void_p(self.sum_rho.data_ptr())),
-               "lb_record_sum_rho")
+        with self._ordered():
+            _check(lib().lb_record_sum_rho(self.handle, ctypes.c_void_p(self.sum_rho.data_ptr())),
+                   "lb_record_sum_rho")
         return self.sum_rho
 
     def step(self, n=1):
@@ -324,18 +349,21 @@ class Grid:
         shape = self.fine_shape if fine else (self.ny, self.nx)
         out = torch.empty(shape, dtype=self.dtype, device=self.device)
         fn = lib().lb_get_field_fine if fine else lib().lb_get_field
-        _check(fn(self.handle, FIELD[what], ctypes.c_void_p(out.data_ptr())), "lb_get_field")
+        with self._ordered():
+            _check(fn(self.handle, FIELD[what], ctypes.c_void_p(out.data_ptr())), "lb_get_field")
         return out
 
     def get_state(self):
         torch = self._torch
         n = lib().lb_state_bytes(self.handle)
         out = torch.empty(int(n), dtype=torch.uint8, device=self.device)
-        _check(lib().lb_get_state(self.handle, ctypes.c_void_p(out.data_ptr())), "lb_get_state")
+        with self._ordered():
+            _check(lib().lb_get_state(self.handle, ctypes.c_void_p(out.data_ptr())), "lb_get_state")
         return out
 
     def set_raw_state(self, blob):
-        _check(lib().lb_set_raw_state(self.handle, ctypes.c_void_p(blob.data_ptr())), "lb_set_raw_state")
+        with self._ordered():
+            _check(lib().lb_set_raw_state(self.handle, ctypes.c_void_p(blob.data_ptr())), "lb_set_raw_state")
 
     def _trace_shaped(self, a, name):
         """a as a contiguous device tensor [nrec][trace_capacity] of the
@@ -359,8 +387,9 @@ class Grid:
         d_obs = self._trace_shaped(d_obs, "d_obs")
         res = torch.zeros_like(d_obs)
         phi = torch.zeros((), dtype=torch.float64, device=self.device)
-        _check(lib().lb_misfit(self.handle, ctypes.c_void_p(d_obs.data_ptr()), int(nt),
-                               ctypes.c_void_p(res.data_ptr()), ctypes.c_void_p(phi.data_ptr())), "lb_misfit")
+        with self._ordered():
+            _check(lib().lb_misfit(self.handle, ctypes.c_void_p(d_obs.data_ptr()), int(nt),
+                                   ctypes.c_void_p(res.data_ptr()), ctypes.c_void_p(phi.data_ptr())), "lb_misfit")
         return phi, res
 
     def adjoint(self, res, nt):
@@ -369,8 +398,9 @@ class Grid:
         torch = self._torch
         res = self._trace_shaped(res, "res")
         grad = torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device)
-        _check(lib().lb_adjoint(self.handle, ctypes.c_void_p(res.data_ptr()), int(nt),
-                                ctypes.c_void_p(grad.data_ptr())), "lb_adjoint")
+        with self._ordered():
+            _check(lib().lb_adjoint(self.handle, ctypes.c_void_p(res.data_ptr()), int(nt),
+                                    ctypes.c_void_p(grad.data_ptr())), "lb_adjoint")
         return grad
 
     def sync(self):
