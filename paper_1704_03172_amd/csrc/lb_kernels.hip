@@ -233,9 +233,6 @@ __device__ inline void prolong_pair_tile(const InterfaceParams &p, int b) {
 }
 
 // ---- fused step -------------------------------------------------------------
-// One thread's share of the update: V consecutive nodes (x0 .. x0+V-1) of row
-// y, of which those from x1 on are another block's.  Their rho goes to rho_row
-// if it is not nullptr.
 template <typename S>
 constexpr bool kIsF64 = sizeof(S) == 8;
 
@@ -296,7 +293,10 @@ __device__ inline void record_wave(const Receivers &rc, int rb, int re, int x0, 
     }
 }
 
-template <typename S, int Q, int KIND, bool PULL>
+// One thread's share of the update: V consecutive nodes (x0 .. x0+V-1) of row
+// y, of which those from x1 on are another block's.  SUM: their rho goes to
+// rho_row.
+template <typename S, int Q, int KIND, bool PULL, bool SUM>
 __device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, typename Tr<S>::T *rho_row) {
     using T = typename Tr<S>::T;
     constexpr int V = PULL ? Tr<S>::V : 1;
@@ -374,11 +374,11 @@ __device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, t
         const int x = x0 + j;
         if constexpr (by_node)
             if (rb < re && x < x1) record_node<T, Q>(p.rec, rb, re, x, gj, c2v[j]);
-        if ((p.sum || p.rho_out) && x < x1) {
+        if ((SUM || p.rho_out) && x < x1) {
             T rho = T(0);
 #pragma unroll
             for (int i = 0; i < Q; ++i) rho += gj[i];
-            if (p.sum) rho_row[j] = rho;
+            if constexpr (SUM) rho_row[j] = rho;
             if (p.rho_out) reinterpret_cast<T *>(p.rho_out)[(int64_t)y * nx + x] = rho;
         }
         T po[Q];
@@ -416,10 +416,10 @@ __device__ inline void update_tile(const StepParams &p, int x0, int x1, int y, t
 __host__ __device__ inline int sum_columns(int columns, int ow) { return columns / ow * ow; }
 
 
-template <typename S, int Q, int KIND, bool PULL>
+template <typename S, int Q, int KIND, bool PULL, bool SUM>
 __device__ __attribute__((always_inline)) inline void step_body(const StepParams &p) {
     constexpr int V = PULL ? Tr<S>::V : 1;
-    if constexpr (Q == 5 && !kIsF64<S>) {
+    if constexpr (Q == 5 && !kIsF64<S> && !SUM) {
         // leading block rows of a coarse launch: the fine outer-ring states
         // of this coarse step (they read only what this launch reads; FP64
         // runs them as a launch of their own, whose registers would lower
@@ -430,40 +430,43 @@ __device__ __attribute__((always_inline)) inline void step_body(const StepParams
         }
     }
     const int y = blockIdx.y - p.pre_rows + p.y0;
-    // The sum of rho by row and strip, added as the flowing kernel adds it, so
-    // that a time's sum does not depend on the launch that records it.  (A single
-    // step of 4096^2 and its sum: 131 us in FP32 and 254 in FP64; through the
-    // flowing kernel, whose blocks read a third more columns, 206 and 399.)
-    using T = typename Tr<S>::T;
-    __shared__ T rho_row[V * kStepBlock];
-    const bool sums = p.sum != nullptr;
-    const int ow = 64 * p.sum_v - 2 * p.sum_hx, n = sums ? sum_columns(V * kStepBlock, ow) : V * kStepBlock;
-    const int xb = p.x0 + (int)blockIdx.x * n, x1 = sums ? min(xb + n, p.x1) : p.x1, own = (int)threadIdx.x * V;
-    update_tile<S, Q, KIND, PULL>(p, xb + own, x1, y, rho_row + own);
-    if (!sums) return;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
-    for (int k = threadIdx.x >> 6; k * ow < x1 - xb; k += kStepBlock / 64) {
-        double a = 0.0;
-        for (int j = 0; j < p.sum_v; ++j) {
-            const int c = lane * p.sum_v + j - p.sum_hx;
-            if (c >= 0 && c < ow && k * ow + c < x1 - xb) a += double(rho_row[k * ow + c]);
+    if constexpr (!SUM) {
+        update_tile<S, Q, KIND, PULL, false>(p, p.x0 + (blockIdx.x * kStepBlock + threadIdx.x) * V, p.x1, y, nullptr);
+    } else {
+        // The sum of rho by row and strip, added as the flowing kernel adds it,
+        // so that a time's sum does not depend on the launch that records it.
+        // (A single step of 4096^2 and its sum: 131 us in FP32 and 254 in FP64;
+        // through the flowing kernel, whose blocks read a third more columns,
+        // 206 and 399.)
+        using T = typename Tr<S>::T;
+        __shared__ T rho_row[V * kStepBlock];
+        const int ow = 64 * p.sum_v - 2 * p.sum_hx, n = sum_columns(V * kStepBlock, ow);
+        const int xb = (int)blockIdx.x * n, x1 = min(xb + n, p.nx), own = (int)threadIdx.x * V;
+        update_tile<S, Q, KIND, PULL, true>(p, xb + own, x1, y, rho_row + own);
+        __syncthreads();
+        const int lane = threadIdx.x & 63;
+        for (int k = threadIdx.x >> 6; k * ow < x1 - xb; k += kStepBlock / 64) {
+            double a = 0.0;
+            for (int j = 0; j < p.sum_v; ++j) {
+                const int c = lane * p.sum_v + j - p.sum_hx;
+                if (c >= 0 && c < ow && k * ow + c < x1 - xb) a += double(rho_row[k * ow + c]);
+            }
+            a = wave_total(a);
+            if (lane == 63) p.sum[(int64_t)y * p.sum_nstrip + xb / ow + k] = a;
         }
-        a = wave_total(a);
-        if (lane == 63) p.sum[(int64_t)y * p.sum_nstrip + xb / ow + k] = a;
     }
 }
 
-template <typename S, int Q, int KIND, bool PULL>
+template <typename S, int Q, int KIND, bool PULL, bool SUM>
 __global__ __launch_bounds__(kStepBlock) void k_step(StepParams p) {
-    step_body<S, Q, KIND, PULL>(p);
+    step_body<S, Q, KIND, PULL, SUM>(p);
 }
 
 // A one-step launch of a replayed graph (pull-stream, no interface work).
-template <typename S, int Q, int KIND>
+template <typename S, int Q, int KIND, bool SUM>
 __global__ __launch_bounds__(kStepBlock) void k_step_graph(StepParams p) {
     const StepParams q = graph_params(p);
-    step_body<S, Q, KIND, true>(q);
+    step_body<S, Q, KIND, true, SUM>(q);
 }
 
 // One step of every active shot of a batch, from its params image of the round.
@@ -513,9 +516,9 @@ __global__ __launch_bounds__(kStepBlock) void k_step_batch(FlowBatch fb, int per
     const int64_t tiles = (int64_t)bx * f.ny, blocks = (int64_t)__builtin_amdgcn_readfirstlane(fb.prefix[lo + 1]) * per - first;
     for (int64_t t = blockIdx.x - first; t < tiles; t += blocks) {
         const int y = (int)(t / bx), x0 = ((int)(t - (int64_t)y * bx) * kStepBlock + (int)threadIdx.x) * V;
-        if constexpr (KIND < 6) update_tile<S, Q, KIND, true>(p, x0, f.nx, y, nullptr);
-        else if (f.coll.written) update_tile<S, Q, KIND - 3, true>(p, x0, f.nx, y, nullptr);
-        else update_tile<S, Q, KIND - 6, true>(p, x0, f.nx, y, nullptr);
+        if constexpr (KIND < 6) update_tile<S, Q, KIND, true, false>(p, x0, f.nx, y, nullptr);
+        else if (f.coll.written) update_tile<S, Q, KIND - 3, true, false>(p, x0, f.nx, y, nullptr);
+        else update_tile<S, Q, KIND - 6, true, false>(p, x0, f.nx, y, nullptr);
     }
 }
 
@@ -884,19 +887,19 @@ hipError_t step_dispatch(const StepParams &p0, bool pull, hipStream_t s) {
             if (e != hipSuccess) return e;
         }
     }
-    if (p.gtab) {   // a launch of a captured chunk: its own entry kernel
-        if (!pull || p.prolong_on || p.restrict_on || p.snap || p.ring_buf) return hipErrorInvalidValue;
+    // a launch of a captured chunk has its own entry kernel
+    if (p.gtab && (!pull || p.prolong_on || p.restrict_on || p.snap || p.ring_buf)) return hipErrorInvalidValue;
+    auto launch = [&](auto sc) {
+        constexpr bool SUM = decltype(sc)::value;
         return step_by_lattice<S>(p.q, kind, [&](auto qc, auto kc) {
-            hipLaunchKernelGGL((k_step_graph<S, decltype(qc)::value, decltype(kc)::value>), grid, dim3(kStepBlock), 0, s, p);
+            constexpr int Q = decltype(qc)::value, KIND = decltype(kc)::value;
+            if (p.gtab) hipLaunchKernelGGL((k_step_graph<S, Q, KIND, SUM>), grid, dim3(kStepBlock), 0, s, p);
+            else if (pull) hipLaunchKernelGGL((k_step<S, Q, KIND, true, SUM>), grid, dim3(kStepBlock), 0, s, p);
+            else hipLaunchKernelGGL((k_step<S, Q, KIND, false, SUM>), grid, dim3(kStepBlock), 0, s, p);
             return hipGetLastError();
         });
-    }
-    return step_by_lattice<S>(p.q, kind, [&](auto qc, auto kc) {
-        constexpr int Q = decltype(qc)::value, KIND = decltype(kc)::value;
-        if (pull) hipLaunchKernelGGL((k_step<S, Q, KIND, true>), grid, dim3(kStepBlock), 0, s, p);
-        else hipLaunchKernelGGL((k_step<S, Q, KIND, false>), grid, dim3(kStepBlock), 0, s, p);
-        return hipGetLastError();
-    });
+    };
+    return p.sum ? launch(std::true_type()) : launch(std::false_type());
 }
 
 }  // namespace
