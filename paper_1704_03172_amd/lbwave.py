@@ -6,7 +6,6 @@ buffers) and the stream.  There is no CPU fallback: if the library is not
 built, importing the binding's entry points raises.
 """
 import collections
-import contextlib
 import ctypes
 import os
 
@@ -201,10 +200,11 @@ def blocked_steps(**kw):
 class Grid:
     """One lattice (optionally with a refinement patch) on one HIP stream.
 
-    Tensors passed in and returned belong to the caller's current stream: where
-    that is not the grid's, each call that reads or fills some is ordered after
-    the caller's work so far and before its later work, without a wait on the
-    host.  step() is not: traces and sums are complete after sync()."""
+    Tensors passed in and returned belong to the caller's current stream.  Where
+    that is not the grid's, a call that reads or fills some is ordered after the
+    caller's work so far, and what it returns is ready for the caller's later
+    work, without a wait on the host.  An input may be dropped at once, but
+    overwritten only after sync(), as traces and sums are complete only then."""
 
     def __init__(self, nx, ny, device=None, stream=None, **kw):
         import torch
@@ -222,11 +222,12 @@ class Grid:
             _check(L.lb_validate_desc(ctypes.byref(self.desc)), "lb_validate_desc")
         self.workspace = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
         self.stream = torch.cuda.current_stream(self.device) if stream is None else stream
+        self._raw_stream = self.stream.cuda_stream
+        self._index = torch.cuda.current_device() if self.device.index is None else self.device.index
         h = ctypes.c_void_p()
-        with self._ordered():
-            _check(L.lb_create_grid(ctypes.byref(self.desc), ctypes.c_void_p(self.workspace.data_ptr()),
-                                    ctypes.c_size_t(int(nbytes)), ctypes.c_void_p(self.stream.cuda_stream),
-                                    ctypes.byref(h)), "lb_create_grid")
+        _check(self._read((), L.lb_create_grid, ctypes.byref(self.desc), ctypes.c_void_p(self.workspace.data_ptr()),
+                          ctypes.c_size_t(int(nbytes)), ctypes.c_void_p(self._raw_stream), ctypes.byref(h)),
+               "lb_create_grid")
         self._h = h
         self.traces = None
         self.sum_rho = None
@@ -237,19 +238,35 @@ class Grid:
             self.fine_shape = (2 * H + 1, 2 * W + 1)
 
     # ---- marshalling helpers ------------------------------------------------
-    @contextlib.contextmanager
-    def _ordered(self):
-        """The grid's work enqueued inside runs between the caller's before and
-        after it."""
+    def _after_caller(self):
+        """Order the grid's stream after the caller's work so far; returns the
+        caller's stream, or None if it is the grid's."""
+        if self._torch._C._cuda_getCurrentRawStream(self._index) == self._raw_stream:
+            return None
         cur = self._torch.cuda.current_stream(self.device)
-        if cur.cuda_stream == self.stream.cuda_stream:
-            yield
-            return
-        self.stream.wait_stream(cur)
+        if not cur.query():
+            self.stream.wait_stream(cur)
+        return cur
+
+    def _read(self, keep, fn, *args):
+        """fn(*args), which reads the arrays of `keep`."""
+        cur = self._after_caller()
+        code = fn(*args)
+        if cur is not None:
+            for a in keep:
+                if isinstance(a, self._torch.Tensor):   # not to be handed out again before it is read
+                    a.record_stream(self.stream)
+        return code
+
+    def _fill(self, fn, *args):
+        """fn(*args), which fills (and may read) tensors: the caller's later work
+        comes after it."""
+        cur = self._after_caller()
         try:
-            yield
+            return fn(*args)
         finally:
-            cur.wait_stream(self.stream)
+            if cur is not None:
+                cur.wait_stream(self.stream)
 
     def _arg(self, a, keep):
         """(pointer, dtype code, on_device) for a numpy array or torch tensor."""
@@ -281,8 +298,7 @@ class Grid:
         keep = []
         p, t, dev = self._arg(c2, keep)
         fn = lib().lb_set_medium_fine if fine else lib().lb_set_medium
-        with self._ordered():
-            _check(fn(self.handle, p, t, dev), "lb_set_medium")
+        _check(self._read(keep, fn, self.handle, p, t, dev), "lb_set_medium")
 
     def set_state(self, rho, jx=None, jy=None, fine=False):
         keep = []
@@ -292,8 +308,7 @@ class Grid:
         if (jx is not None and tx != t) or (jy is not None and ty != t):
             raise TypeError("rho, jx, jy must share one dtype")
         fn = lib().lb_set_state_fine if fine else lib().lb_set_state
-        with self._ordered():
-            _check(fn(self.handle, pr, px, py, t, dev), "lb_set_state")
+        _check(self._read(keep, fn, self.handle, pr, px, py, t, dev), "lb_set_state")
 
     def set_source(self, x, y, wavelet):
         w = np.ascontiguousarray(wavelet, dtype=np.float64)
@@ -317,17 +332,15 @@ class Grid:
         nf = bin(what).count("1")
         self.traces = torch.zeros((nf, nrec, self.trace_capacity), dtype=self.dtype, device=self.device)
         self.trace_fields = tuple(f for f in FIELD_ORDER if what & FIELD[f])
-        with self._ordered():
-            _check(lib().lb_record(self.handle, rec.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), nrec,
-                                   ctypes.c_void_p(self.traces.data_ptr()), what), "lb_record")
+        _check(self._read((self.traces,), lib().lb_record, self.handle, rec.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
+                          nrec, ctypes.c_void_p(self.traces.data_ptr()), what), "lb_record")
         return self.traces
 
     def record_sum_rho(self):
         torch = self._torch
         self.sum_rho = torch.zeros(self.trace_capacity, dtype=torch.float64, device=self.device)
-        with self._ordered():
-            _check(lib().lb_record_sum_rho(self.handle, ctypes.c_void_p(self.sum_rho.data_ptr())),
-                   "lb_record_sum_rho")
+        _check(self._read((self.sum_rho,), lib().lb_record_sum_rho, self.handle, ctypes.c_void_p(self.sum_rho.data_ptr())),
+               "lb_record_sum_rho")
         return self.sum_rho
 
     def step(self, n=1):
@@ -349,21 +362,18 @@ class Grid:
         shape = self.fine_shape if fine else (self.ny, self.nx)
         out = torch.empty(shape, dtype=self.dtype, device=self.device)
         fn = lib().lb_get_field_fine if fine else lib().lb_get_field
-        with self._ordered():
-            _check(fn(self.handle, FIELD[what], ctypes.c_void_p(out.data_ptr())), "lb_get_field")
+        _check(self._fill(fn, self.handle, FIELD[what], ctypes.c_void_p(out.data_ptr())), "lb_get_field")
         return out
 
     def get_state(self):
         torch = self._torch
         n = lib().lb_state_bytes(self.handle)
         out = torch.empty(int(n), dtype=torch.uint8, device=self.device)
-        with self._ordered():
-            _check(lib().lb_get_state(self.handle, ctypes.c_void_p(out.data_ptr())), "lb_get_state")
+        _check(self._fill(lib().lb_get_state, self.handle, ctypes.c_void_p(out.data_ptr())), "lb_get_state")
         return out
 
     def set_raw_state(self, blob):
-        with self._ordered():
-            _check(lib().lb_set_raw_state(self.handle, ctypes.c_void_p(blob.data_ptr())), "lb_set_raw_state")
+        _check(self._read((blob,), lib().lb_set_raw_state, self.handle, ctypes.c_void_p(blob.data_ptr())), "lb_set_raw_state")
 
     def _trace_shaped(self, a, name):
         """a as a contiguous device tensor [nrec][trace_capacity] of the
@@ -387,9 +397,8 @@ class Grid:
         d_obs = self._trace_shaped(d_obs, "d_obs")
         res = torch.zeros_like(d_obs)
         phi = torch.zeros((), dtype=torch.float64, device=self.device)
-        with self._ordered():
-            _check(lib().lb_misfit(self.handle, ctypes.c_void_p(d_obs.data_ptr()), int(nt),
-                                   ctypes.c_void_p(res.data_ptr()), ctypes.c_void_p(phi.data_ptr())), "lb_misfit")
+        _check(self._fill(lib().lb_misfit, self.handle, ctypes.c_void_p(d_obs.data_ptr()), int(nt),
+                          ctypes.c_void_p(res.data_ptr()), ctypes.c_void_p(phi.data_ptr())), "lb_misfit")
         return phi, res
 
     def adjoint(self, res, nt):
@@ -398,9 +407,8 @@ class Grid:
         torch = self._torch
         res = self._trace_shaped(res, "res")
         grad = torch.empty((self.ny, self.nx), dtype=torch.float64, device=self.device)
-        with self._ordered():
-            _check(lib().lb_adjoint(self.handle, ctypes.c_void_p(res.data_ptr()), int(nt),
-                                    ctypes.c_void_p(grad.data_ptr())), "lb_adjoint")
+        _check(self._fill(lib().lb_adjoint, self.handle, ctypes.c_void_p(res.data_ptr()), int(nt),
+                          ctypes.c_void_p(grad.data_ptr())), "lb_adjoint")
         return grad
 
     def sync(self):

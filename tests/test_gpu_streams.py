@@ -1,7 +1,8 @@
 """A grid on a stream of its own, called from another stream: every call that
-reads or fills tensors is ordered after the caller's work so far and before its
-later work.  The caller's stream is kept busy for milliseconds before each call,
-and the results are used at once, without a wait on the host."""
+reads or fills tensors is ordered after the caller's work so far, and what it
+returns is ready for the caller's later work.  The caller's stream is kept busy
+for milliseconds before each call, inputs are dropped at once and their memory
+used again, and the results are used without a wait on the host."""
 import numpy as np
 import pytest
 import torch
@@ -40,9 +41,8 @@ def run(stream, wait):
         busy()
     g = lbwave.Grid(NX, NY, trace_capacity=NSTEPS + 1, max_receivers=20, rho_tape=1, stream=stream)
     g.set_medium(hand(c2))
-    state = hand(rho)
-    g.set_state(state)
-    state.zero_() if wait else None   # the caller's later work
+    g.set_state(hand(rho))
+    again = [torch.full_like(rho, 7.0) for _ in range(3)] if wait else None   # the memory of dropped inputs
     g.set_source(100, 50, 1e-2 * inputs.ricker_wavelet(NSTEPS + 1, 0.1))
     if wait:
         busy()
@@ -59,6 +59,7 @@ def run(stream, wait):
     out.append(g.adjoint(hand(res), NSTEPS).clone())
     g.sync()
     torch.cuda.synchronize()
+    del again
     return out + [traces.clone(), sums.clone()]
 
 
