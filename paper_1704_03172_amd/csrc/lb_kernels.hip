@@ -241,12 +241,13 @@ constexpr bool kIsF64 = sizeof(S) == 8;
 // pre-collision state g; x1 ends the row.  The lanes look at m entries at a
 // time, and each writes the fields of its entry, taken from the lane that
 // holds the column.  (A search by each lane was a chain of loads: 8.5 us for a
-// step of 256^2 with 64 receivers in a row, 5.1 so.)
+// step of 256^2 with 64 receivers in a row, 5.1 so; of 300^2, whose rows end
+// with 11 lanes, 8.7 and 6.3.)
 template <typename T, int Q, int V>
 __device__ inline void record_wave(const Receivers &rc, int rb, int re, int x0, int x1, const T (&g)[Q][V], const T (&c2)[V]) {
     const int lane = threadIdx.x & 63, m = __builtin_popcountll(__ballot(true));
     const int xa = __builtin_amdgcn_readfirstlane(x0), xe = min(xa + m * V, x1);
-    if (m < 16) {   // a short end of a row
+    if (m < 4) {   // a short end of a row
 #pragma unroll
         for (int j = 0; j < V; ++j) {
             T gj[Q];
@@ -669,7 +670,9 @@ __global__ __launch_bounds__(kBlock) void k_misfit_finalize(const double *partia
 __device__ inline double sum_partials(const double *p, int64_t n) {
     constexpr int U = 16;
     double s = 0.0;
-    for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
+    if (n <= kBlock) {   // a small grid: no groups
+        if (threadIdx.x < n) s += p[threadIdx.x];
+    } else for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
         double a[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) a[k] = p[min(i + k * kBlock, n - 1)];

@@ -1093,16 +1093,30 @@ int flow_launch(lb_grid *h, int ns) {
     return LB_OK;
 }
 
+// Whether a single step that records the sum of rho goes through the flowing
+// kernel, too: small grids, of half storage up to larger ones (the one-step
+// kernel's threads hold 8 columns there).  us per call of one step, flowing /
+// one-step kernel: FP32 D2Q5 50^2 8.9 / 11.4, 120^2 9.9 / 10.0, 300^2 11.4 / 10.0;
+// D2Q9 150^2 10.7 / 14.3, 256^2 11.5 / 11.7, 500^2 15.7 / 14.1; FP64 D2Q9 120^2 10.2
+// / 11.2, 200^2 11.3 / 10.3; half storage D2Q5 500^2 13.5 / 15.8, 900^2 19.4 / 17.4;
+// D2Q9 500^2 14.8 / 26.7, 1200^2 28.7 / 36.4, 1600^2 47.3 / 42.9.
+bool sum_by_flow(const lb_grid *h) {
+    const int64_t nodes = (int64_t)h->d.nx * h->d.ny;
+    if (h->storage == lbw::ST_F16) return nodes <= (h->q == 9 ? 2000000 : 600000);
+    return nodes <= (h->q == 9 ? 32768 : 16384);
+}
+
 // The next launch of a call with `left` steps to take; *ns: the steps taken.
-// Single steps go through the one-step kernel.  With a patch a call's last step goes one launch
-// at a time: the fields and the saved states are read from the states before.
+// Single steps go through the one-step kernel (but see sum_by_flow).  With a
+// patch a call's last step goes one launch at a time: the fields and the saved
+// states are read from the states before.
 int next_launch(lb_grid *h, int64_t left, int *ns) {
     if (h->patch && left > 1 && h->d.steps_per_launch != 1) {
         *ns = left > 2 && h->window.steps > 1 ? even_steps(left - 1, h->window.steps) : 1;
         return *ns > 1 ? window_steps(h, *ns) : one_step(h, true);
     }
     *ns = next_steps(h, left);
-    return *ns > 1 ? flow_launch(h, *ns) : one_step(h);
+    return *ns > 1 || (h->sum_rho && !h->patch && sum_by_flow(h)) ? flow_launch(h, *ns) : one_step(h);
 }
 
 // Whether lb_step_n may replay graphs now: enabled, no patch (launches with
