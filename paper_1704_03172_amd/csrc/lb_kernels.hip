@@ -664,15 +664,11 @@ __global__ __launch_bounds__(kBlock) void k_misfit_finalize(const double *partia
     if (threadIdx.x == 0) *phi = 0.5 * s;
 }
 
-// Sum of n partials over a block, in thread 0: a thread's loads come in groups
-// that are in flight together (one at a time they were a chain of 340 us for the
-// 176 k of a time on 4096^2).
-__device__ inline double sum_partials(const double *p, int64_t n) {
-    constexpr int U = 16;
+// A thread's share of n partials, U loads in flight together.
+template <int U>
+__device__ inline double sum_groups(const double *p, int64_t n) {
     double s = 0.0;
-    if (n <= kBlock) {   // a small grid: no groups
-        if (threadIdx.x < n) s += p[threadIdx.x];
-    } else for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
+    for (int64_t i = threadIdx.x; i < n; i += U * kBlock) {
         double a[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) a[k] = p[min(i + k * kBlock, n - 1)];
@@ -680,6 +676,13 @@ __device__ inline double sum_partials(const double *p, int64_t n) {
         for (int k = 0; k < U; ++k)
             if (i + k * kBlock < n) s += a[k];
     }
+    return s;
+}
+
+// Sum of n partials over a block, in thread 0.  (One load at a time was a chain
+// of 340 us for the 176 k of a time on 4096^2.)
+__device__ inline double sum_partials(const double *p, int64_t n) {
+    const double s = n <= kBlock ? sum_groups<1>(p, n) : n <= 4 * kBlock ? sum_groups<4>(p, n) : sum_groups<16>(p, n);
     __shared__ double sh[kBlock];
     sh[threadIdx.x] = s;
     __syncthreads();
