@@ -243,7 +243,7 @@ class Grid:
         caller's stream, or None if it is the grid's."""
         if self._torch._C._cuda_getCurrentRawStream(self._index) == self._raw_stream:
             return None
-        cur = self._torch.cuda.current_stream(self.device)
+        cur = self._torch.cuda.current_stream(self._index)
         if not cur.query():
             self.stream.wait_stream(cur)
         return cur
